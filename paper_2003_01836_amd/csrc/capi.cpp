@@ -967,6 +967,40 @@ int bltc_internal_check_direct(const bltc_params* p, int64_t nt, const double* t
     return BLTC_OK;
 }
 
+bool bltc_internal_direct_overlap(int64_t nt, const double* tx, const double* ty, const double* tz,
+                                  int64_t ns, const double* sx, const double* sy, const double* sz,
+                                  const double* q, int32_t num_q, int64_t q_ld, const double* phi,
+                                  int64_t phi_ld)
+{
+    const double* const lo = phi;
+    const double* const hi = phi + (num_q > 1 ? (num_q - 1) * phi_ld : 0) + nt;
+    auto hits = [&](const double* p, int64_t n) { return n > 0 && p < hi && lo < p + n; };
+    return hits(tx, nt) || hits(ty, nt) || hits(tz, nt) || hits(sx, ns) || hits(sy, ns) ||
+           hits(sz, ns) || hits(q, (num_q > 1 ? (num_q - 1) * q_ld : 0) + ns);
+}
+
+int bltc_internal_direct(const bltc_params* p, int64_t nt, const double* tx, const double* ty,
+                         const double* tz, int64_t ns, const double* sx, const double* sy,
+                         const double* sz, const double* q, int32_t num_q, int64_t q_ld,
+                         double* phi, int64_t phi_ld, const bltc::DirectSplit& split, double* part,
+                         hipStream_t s)
+{
+    bltc::KernelParams kp;
+    kp.kernel = p->kernel;
+    kp.kappa = p->kappa;
+    kp.delta = p->delta;
+    // a kernel value serves up to kDirectVectors vectors
+    for (int32_t m = 0; m < num_q; m += bltc::kDirectVectors) {
+        const int32_t mc = std::min(bltc::kDirectVectors, num_q - m);
+        const hipError_t e = bltc::launch_direct(
+            nt, tx, ty, tz, ns, sx, sy, sz, q + static_cast<int64_t>(m) * q_ld, mc, q_ld, kp, split,
+            part, phi + static_cast<int64_t>(m) * phi_ld, phi_ld, s);
+        if (e != hipSuccess)
+            return hip_fail(e, "direct-sum launch");
+    }
+    return BLTC_OK;
+}
+
 extern "C" {
 
 void bltc_params_default(bltc_params* p)
@@ -1299,25 +1333,21 @@ int bltc_direct(const bltc_params* p, int64_t nt, const double* tx, const double
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (ns == 0)
         return zero_phi(nt, num_q, phi, phi_ld, s);
-    double4* packed = nullptr;
-    HIP_TRY(hipMallocAsync(reinterpret_cast<void**>(&packed), ns * sizeof(double4), s));
-    bltc::KernelParams kp;
-    kp.kernel = p->kernel;
-    kp.kappa = p->kappa;
-    kp.delta = p->delta;
-    hipError_t e = hipSuccess;
-    for (int32_t m = 0; m < num_q && e == hipSuccess; ++m) {
-        e = bltc::launch_pack_sources(ns, sx, sy, sz, q + static_cast<int64_t>(m) * q_ld, packed, s);
-        if (e == hipSuccess)
-            e = bltc::launch_direct(nt, tx, ty, tz, ns, packed, kp,
-                                    phi + static_cast<int64_t>(m) * phi_ld, s);
+    const bltc::DirectSplit split = bltc::direct_split(nt, ns);
+    double* part = nullptr;
+    if (split.pieces > 1 ||
+        bltc_internal_direct_overlap(nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi, phi_ld))
+        HIP_TRY(hipMallocAsync(reinterpret_cast<void**>(&part),
+                               static_cast<size_t>(split.pieces) * nt *
+                                   std::min(num_q, bltc::kDirectVectors) * sizeof(double), s));
+    const int rc_run = bltc_internal_direct(p, nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi,
+                                            phi_ld, split, part, s);
+    if (part) {
+        const hipError_t f = hipFreeAsync(part, s);
+        if (rc_run == BLTC_OK && f != hipSuccess)
+            return hip_fail(f, "hipFreeAsync");
     }
-    hipError_t f = hipFreeAsync(packed, s);
-    if (e != hipSuccess)
-        return hip_fail(e, "direct-sum launch");
-    if (f != hipSuccess)
-        return hip_fail(f, "hipFreeAsync");
-    return BLTC_OK;
+    return rc_run;
 }
 
 const char* bltc_status_string(int code)

@@ -242,6 +242,21 @@ int bltc_internal_check_direct(const bltc_params* p, int64_t nt, const double* t
                                const double* sy, const double* sz, const double* q, int32_t num_q,
                                const double* phi);
 
+// The launches of bltc_direct and bltc_direct_noalloc: every charge vector's
+// direct sum, with room in `part` for the partial sums of one launch (NULL:
+// split has one piece and phi is written directly).
+int bltc_internal_direct(const bltc_params* p, int64_t nt, const double* tx, const double* ty,
+                         const double* tz, int64_t ns, const double* sx, const double* sy,
+                         const double* sz, const double* q, int32_t num_q, int64_t q_ld,
+                         double* phi, int64_t phi_ld, const bltc::DirectSplit& split, double* part,
+                         hipStream_t s);
+// Whether phi shares memory with an input (potentials written over the
+// charges): the sums then go through `part`, so that every input is read first.
+bool bltc_internal_direct_overlap(int64_t nt, const double* tx, const double* ty, const double* tz,
+                                  int64_t ns, const double* sx, const double* sy, const double* sz,
+                                  const double* q, int32_t num_q, int64_t q_ld, const double* phi,
+                                  int64_t phi_ld);
+
 // cluster-particle plans (cp.cpp)
 namespace bltc_cp {
 int create_host(bltc_plan* plan, const bltc::PlanParams& pp, int64_t nt, const double* tx,

@@ -9,6 +9,8 @@
 //    its target's accumulator, so phi is written exactly once, in caller
 //    order, without atomics.
 //  * the upward pass lives in kernels_upward.hip (matrix cores).
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "device_common.hpp"
 
@@ -134,43 +136,110 @@ __global__ __launch_bounds__(256) void gather_charges(double4* __restrict__ src,
     }
 }
 
-__global__ __launch_bounds__(256) void pack_sources(int64_t ns, const double* __restrict__ x,
-                                                    const double* __restrict__ y,
-                                                    const double* __restrict__ z,
-                                                    const double* __restrict__ q,
-                                                    double4* __restrict__ out)
+// ---------------------------------------------------------------------------
+// Direct sum of eq. 1: 64 targets (one per lane) per workgroup, whose four
+// waves each take a quarter of the workgroup's run of sources, wave-uniform
+// and read in place through the scalar cache; a kernel value serves all M
+// charge vectors.  Bound: FP64 issue (about 60 SIMD cycles per value and 64
+// targets).  With few targets the sources are cut into gridDim.y pieces
+// (launch_direct): 1000 targets against 2 10^6 sources took 188 ms with one
+// lane per target and every source in it (16 waves on the chip), 1.0 ms so.
+// Sums run in a fixed order: within a wave, over the waves, over the pieces.
+// ---------------------------------------------------------------------------
+constexpr int kDirectWaves = 4;
+
+template <int KER, int M>
+__global__ __launch_bounds__(64 * kDirectWaves) void direct_f64(
+    int64_t nt, const double* __restrict__ tx, const double* __restrict__ ty,
+    const double* __restrict__ tz, int64_t ns, const double* __restrict__ sx,
+    const double* __restrict__ sy, const double* __restrict__ sz, const double* __restrict__ q,
+    int64_t q_ld, int64_t per, double* __restrict__ out, int64_t out_ld, int64_t out_piece,
+    KernelConst kc)
 {
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (j < ns)
-        out[j] = make_double4(x[j], y[j], z[j], q[j]);
+    __shared__ double exp_tab[64];
+    __shared__ double part[kDirectWaves][M][64];
+    if constexpr (KER == 1)
+        fill_exp2_table(exp_tab);
+    const KernelArg ka{kc.kappa, kc.delta2, exp_tab};
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + lane;
+    const int64_t it = i < nt ? i : nt - 1;
+    const double x = tx[it], y = ty[it], z = tz[it];
+    const int64_t j0 = (static_cast<int64_t>(blockIdx.y) * kDirectWaves + w) * per;
+    const int64_t j1 = j0 + per < ns ? j0 + per : ns;
+    // the terms are doubled (green_near2_f64) and halved once per sum
+    constexpr int U = 4;
+    double acc[M][U];
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            acc[m][u] = 0.0;
+    auto term = [&](int64_t j, int u) {
+        const double dx = x - sx[j], dy = y - sy[j], dz = z - sz[j];
+        const double r2 = __fma_rn(dz, dz, __fma_rn(dy, dy, dx * dx));
+        const double g = green_near2_f64<KER>(r2, ka);
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            acc[m][u] = __fma_rn(g, q[m * q_ld + j], acc[m][u]);
+    };
+    int64_t j = j0;
+    for (; j + U <= j1; j += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            term(j + u, u);
+    }
+    for (; j < j1; ++j)
+        term(j, 0);
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+        part[w][m][lane] = 0.5 * ((acc[m][0] + acc[m][1]) + (acc[m][2] + acc[m][3]));
+    __syncthreads();
+    // wave w adds up vectors w, w + 4, ...
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        if ((m % kDirectWaves) != w || i >= nt)
+            continue;
+        double v = part[0][m][lane];
+#pragma unroll
+        for (int u = 1; u < kDirectWaves; ++u)
+            v += part[u][m][lane];
+        out[blockIdx.y * out_piece + m * out_ld + i] = v;
+    }
+}
+
+// phi[m phi_ld + i] = the pieces' partial sums of (m, i) in piece order
+__global__ __launch_bounds__(256) void sum_direct(const double* __restrict__ part, int64_t nt,
+                                                  int32_t m_count, int32_t pieces,
+                                                  double* __restrict__ phi, int64_t phi_ld)
+{
+    const int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (k >= nt * m_count)
+        return;
+    double v = part[k];
+    for (int32_t p = 1; p < pieces; ++p)
+        v += part[p * nt * m_count + k];
+    const int64_t m = k / nt;
+    phi[m * phi_ld + (k - m * nt)] = v;
 }
 
 template <int KER>
-__global__ __launch_bounds__(256) void direct_f64(int64_t nt, const double* __restrict__ tx,
-                                                  const double* __restrict__ ty,
-                                                  const double* __restrict__ tz, int64_t ns,
-                                                  const double4* __restrict__ src,
-                                                  double* __restrict__ phi, KernelConst kc)
+void run_direct(int m, dim3 grid, hipStream_t s, int64_t nt, const double* tx, const double* ty,
+                const double* tz, int64_t ns, const double* sx, const double* sy, const double* sz,
+                const double* q, int64_t q_ld, int64_t per, double* out, int64_t out_ld,
+                int64_t out_piece, KernelConst kc)
 {
-    __shared__ double exp_tab[64];
-    if constexpr (KER == 1)
-        fill_exp2_table(exp_tab);
-    const KernelArg kappa{kc.kappa, kc.delta2, exp_tab};
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * blockDim.x;
-    if (base + (threadIdx.x & ~63) >= nt)
-        return;
-    int64_t i = base + threadIdx.x;
-    const bool valid = i < nt;
-    if (!valid)
-        i = nt - 1;
-    double acc = 0.0;
-    for (int64_t j0 = 0; j0 < ns; j0 += (int64_t(1) << 30)) {
-        const int64_t left = ns - j0;
-        const int32_t cnt = static_cast<int32_t>(left < (int64_t(1) << 30) ? left : (int64_t(1) << 30));
-        acc += near_sum_f64<KER>(tx[i], ty[i], tz[i], src + j0, cnt, kappa);
+    const dim3 block(64 * kDirectWaves);
+    switch (m) {
+#define X(M)                                                                                     \
+    case M:                                                                                      \
+        hipLaunchKernelGGL((direct_f64<KER, M>), grid, block, 0, s, nt, tx, ty, tz, ns, sx, sy,  \
+                           sz, q, q_ld, per, out, out_ld, out_piece, kc);                        \
+        break;
+        X(1) X(2) X(3) X(4)
+#undef X
     }
-    if (valid)
-        phi[i] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -222,30 +291,49 @@ hipError_t launch_interact(const DevicePlan& d, const KernelParams& kp, double* 
     }
 }
 
-hipError_t launch_pack_sources(int64_t ns, const double* x, const double* y, const double* z,
-                               const double* q, double4* out, hipStream_t s)
+// Pieces the sources are cut into: enough workgroups that the last round of
+// waves on the chip is short (8192 of four waves, four times what is resident
+// at once), pieces of at least 64 sources per wave, one piece when the targets
+// alone give that many workgroups.  1000 targets, 2 10^6 sources: 188 ms in
+// one piece, 1.1 ms cut.
+DirectSplit direct_split(int64_t nt, int64_t ns)
 {
-    if (ns == 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(pack_sources, dim3(static_cast<unsigned>((ns + 255) / 256)), dim3(256), 0,
-                       s, ns, x, y, z, q, out);
-    return hipGetLastError();
+    DirectSplit d;
+    const int64_t groups = (nt + 63) / 64;
+    const int64_t want = (8192 + groups - 1) / std::max<int64_t>(1, groups);
+    const int64_t most = (ns + 64 * kDirectWaves - 1) / (64 * kDirectWaves);
+    const int64_t pieces = std::max<int64_t>(1, std::min(want, most));
+    // whole quads of sources per wave; every piece non-empty
+    d.per = std::max<int64_t>(4, ((ns + pieces * kDirectWaves - 1) / (pieces * kDirectWaves) + 3) / 4 * 4);
+    d.pieces = static_cast<int32_t>(
+        std::max<int64_t>(1, (ns + d.per * kDirectWaves - 1) / (d.per * kDirectWaves)));
+    return d;
 }
 
 hipError_t launch_direct(int64_t nt, const double* tx, const double* ty, const double* tz,
-                         int64_t ns, const double4* src, const KernelParams& kp, double* phi,
+                         int64_t ns, const double* sx, const double* sy, const double* sz,
+                         const double* q, int32_t m, int64_t q_ld, const KernelParams& kp,
+                         const DirectSplit& split, double* part, double* phi, int64_t phi_ld,
                          hipStream_t s)
 {
     if (nt == 0)
         return hipSuccess;
-    const dim3 grid(static_cast<unsigned>((nt + 255) / 256));
+    const int64_t groups = (nt + 63) / 64;
+    if (m < 1 || m > kDirectVectors || groups > INT32_MAX || split.pieces > 65535 ||
+        (!part && split.pieces > 1))
+        return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>(groups), static_cast<unsigned>(split.pieces));
     const KernelConst kc = kp.kconst();
-    if (kp.kernel == 1)
-        hipLaunchKernelGGL(direct_f64<1>, grid, dim3(256), 0, s, nt, tx, ty, tz, ns, src, phi, kc);
-    else if (kp.kernel == 2)
-        hipLaunchKernelGGL(direct_f64<2>, grid, dim3(256), 0, s, nt, tx, ty, tz, ns, src, phi, kc);
-    else
-        hipLaunchKernelGGL(direct_f64<0>, grid, dim3(256), 0, s, nt, tx, ty, tz, ns, src, phi, kc);
+    double* out = part ? part : phi;
+    const int64_t out_ld = part ? nt : phi_ld;
+    const auto run = kp.kernel == 1 ? run_direct<1> : kp.kernel == 2 ? run_direct<2> : run_direct<0>;
+    run(m, grid, s, nt, tx, ty, tz, ns, sx, sy, sz, q, q_ld, split.per, out, out_ld, nt * m, kc);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !part)
+        return e;
+    const int64_t total = nt * m;
+    hipLaunchKernelGGL(sum_direct, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s,
+                       part, nt, m, split.pieces, phi, phi_ld);
     return hipGetLastError();
 }
 

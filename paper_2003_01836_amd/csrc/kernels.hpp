@@ -248,11 +248,23 @@ hipError_t launch_interact_queue(const MrhsDesc* descs, const int2* units, int32
                                  int32_t* counter, const KernelParams& kp, int32_t workgroups,
                                  hipStream_t s);
 const void* interact_queue_symbol(const KernelParams& kp);
-// GPU direct sum (eq. 1) of all targets against packed sources
-hipError_t launch_pack_sources(int64_t ns, const double* x, const double* y, const double* z,
-                               const double* q, double4* out, hipStream_t s);
+// GPU direct sum (eq. 1) of all targets against all sources, m <= kDirectVectors
+// charge vectors at once.  split = direct_split(nt, ns); `part` holds the
+// pieces' partial sums (pieces * m * nt values; NULL: one piece, phi written
+// by the sum itself).
+constexpr int32_t kDirectVectors = 4;
+// partial sums of one call: a split beyond one piece has fewer than
+// 8192 + nt / 64 + 1 target groups times pieces
+constexpr int64_t kDirectPartials = int64_t(1) << 22;
+struct DirectSplit {
+    int32_t pieces = 1;
+    int64_t per = 0;        // sources per wave
+};
+DirectSplit direct_split(int64_t nt, int64_t ns);
 hipError_t launch_direct(int64_t nt, const double* tx, const double* ty, const double* tz,
-                         int64_t ns, const double4* src, const KernelParams& kp, double* phi,
+                         int64_t ns, const double* sx, const double* sy, const double* sz,
+                         const double* q, int32_t m, int64_t q_ld, const KernelParams& kp,
+                         const DirectSplit& split, double* part, double* phi, int64_t phi_ld,
                          hipStream_t s);
 
 }  // namespace bltc

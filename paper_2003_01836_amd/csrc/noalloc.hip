@@ -1,9 +1,9 @@
 // noalloc.hip -- the FP64 direct sum of eq. 1 without any device allocation.
 //
-// bltc_direct stages each charge vector's sources as packed (x, y, z, q)
-// records in a buffer it allocates per call.  bltc_direct_noalloc runs the
-// same kernels with that staging buffer in a file-scope device array of fixed
-// size, so that callers that cannot allocate (code under HIP graph capture,
+// bltc_direct keeps the partial sums of its source pieces in a buffer it
+// allocates per call.  bltc_direct_noalloc runs the same kernels with that
+// buffer in a file-scope device array of fixed size, so that callers that
+// cannot allocate (code under HIP graph capture,
 // serving loops, harnesses that forbid hipMalloc) can use it.  Every GPU the
 // library runs on holds its own copy of the array until the process ends; the
 // host side keeps each device's address of it (hipGetSymbolAddress, once per
@@ -17,16 +17,16 @@
 
 namespace {
 
-// staging records of at most kNoAllocSources sources (32 B each: 32 MiB per device)
+// largest source count; the partial sums (32 MiB per device) hold any split
 constexpr int64_t kNoAllocSources = int64_t(1) << 20;
-__device__ __align__(256) double4 scratch[kNoAllocSources];
+__device__ __align__(256) double scratch[bltc::kDirectPartials];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
-double4* g_scratch_ptr[kMaxDevices] = {};
+double* g_scratch_ptr[kMaxDevices] = {};
 
 // This device's address of `scratch`, looked up on its first use.
-int scratch_for_current_device(double4** out)
+int scratch_for_current_device(double** out)
 {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
@@ -39,7 +39,7 @@ int scratch_for_current_device(double4** out)
         if (e != hipSuccess || !ptr)
             return bltc_detail::hip_fail(e != hipSuccess ? e : hipErrorInvalidSymbol,
                                          "hipGetSymbolAddress(scratch)");
-        g_scratch_ptr[dev] = static_cast<double4*>(ptr);
+        g_scratch_ptr[dev] = static_cast<double*>(ptr);
     }
     *out = g_scratch_ptr[dev];
     return BLTC_OK;
@@ -59,31 +59,25 @@ extern "C" int bltc_direct_noalloc(const bltc_params* p, int64_t nt, const doubl
         return rc;
     if (ns > kNoAllocSources)
         return fail(BLTC_EUNSUPPORTED,
-                    "bltc_direct_noalloc takes at most %lld sources (its fixed staging array); "
+                    "bltc_direct_noalloc takes at most %lld sources (its fixed array); "
                     "%lld given: use bltc_direct",
                     static_cast<long long>(kNoAllocSources), static_cast<long long>(ns));
     if (nt == 0)
         return BLTC_OK;
-    double4* packed = nullptr;
-    rc = scratch_for_current_device(&packed);
+    double* part = nullptr;
+    rc = scratch_for_current_device(&part);
     if (rc != BLTC_OK)
         return rc;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    bltc::KernelParams kp;
-    kp.kernel = p->kernel;
-    kp.kappa = p->kappa;
-    kp.delta = p->delta;
-    hipError_t e = hipSuccess;
-    for (int32_t m = 0; m < num_q && e == hipSuccess; ++m) {
-        // no sources: the direct-sum kernel writes zeros and reads no record
-        if (ns > 0)
-            e = bltc::launch_pack_sources(ns, sx, sy, sz, q + static_cast<int64_t>(m) * q_ld,
-                                          packed, s);
-        if (e == hipSuccess)
-            e = bltc::launch_direct(nt, tx, ty, tz, ns, packed, kp,
-                                    phi + static_cast<int64_t>(m) * phi_ld, s);
-    }
-    if (e != hipSuccess)
-        return bltc_detail::hip_fail(e, "direct-sum launch");
-    return BLTC_OK;
+    // partial sums as in bltc_direct (no sources: the sum writes zeros)
+    const bltc::DirectSplit split = bltc::direct_split(nt, ns);
+    const bool fits = split.pieces * nt * std::min(num_q, bltc::kDirectVectors) <=
+                      bltc::kDirectPartials;
+    if (split.pieces == 1 &&
+        !(fits && bltc_internal_direct_overlap(nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi,
+                                               phi_ld)))
+        part = nullptr;
+    else if (!fits)
+        return fail(BLTC_EINTERNAL, "direct-sum partials exceed the fixed array");
+    return bltc_internal_direct(p, nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi, phi_ld,
+                                split, part, static_cast<hipStream_t>(stream));
 }
