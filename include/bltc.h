@@ -135,12 +135,11 @@ typedef struct {
                                  /* cached) when a plan is created from device          */
                                  /* coordinates; BLTC_EUNSUPPORTED for host plans.      */
                                  /* One of them 0 and the other not: BLTC_EINVAL        */
-    int32_t threads_per_target;  /* 1: one lane per target; 2 or 4: each batch's        */
-                                 /* interaction lists cut into that many contiguous     */
-                                 /* pieces, each evaluated by its own lane of the       */
-                                 /* target (in different waves) into a partial          */
-                                 /* potential, summed per target in piece order: more   */
-                                 /* waves for problems with few targets.                */
+    int32_t threads_per_target;  /* 1, 2 or 4: at least that many lanes per target, in  */
+                                 /* different waves of its workgroup, share the batch's */
+                                 /* interaction lists and add their sums in a fixed     */
+                                 /* order; the library takes more where the targets     */
+                                 /* alone would leave the GPU idle.                     */
                                  /* BLTC_PARTICLE_CLUSTER and BLTC_HERMITE with         */
                                  /* max_q = 1 only.  0: picked by the tuner among 1, 2, */
                                  /* 4 for those plans when created from device          */
@@ -258,7 +257,7 @@ typedef struct {
     int64_t mutual_pair_evals; /* kernel values computed once for two direct terms:   */
                              /* sum over mutual leaf pairs of N_B * N_C (no_symmetry */
                              /* = 0; counted once the device side exists), else 0    */
-    int32_t threads_per_target; /* lanes per target of the interaction launch (1, 2, 4) */
+    int32_t threads_per_target; /* lanes per target asked for (1, 2, 4)                 */
     int64_t workspace_bytes; /* device memory the plan holds (requested bytes; 0 before */
                              /* the device side exists)                              */
     int64_t mutual_pairs;    /* mutual leaf pairs evaluated once (no_symmetry = 0)      */

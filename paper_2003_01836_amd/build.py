@@ -74,7 +74,6 @@ def build(verbose: bool = False, defines=(), lib_path: str = LIB, build_dir: str
         "kernels_cp": os.path.join(build_dir, "kernels_cp.o"),
         "kernels_hermite": os.path.join(build_dir, "kernels_hermite.o"),
         "kernels_sym": os.path.join(build_dir, "kernels_sym.o"),
-        "kernels_split": os.path.join(build_dir, "kernels_split.o"),
         "noalloc": os.path.join(build_dir, "noalloc.o"),
     }
     cmds = [
@@ -98,8 +97,6 @@ def build(verbose: bool = False, defines=(), lib_path: str = LIB, build_dir: str
                                objs["kernels_hermite"]],
         [hipcc] + hip_flags + ["-c", os.path.join(CSRC, "kernels_sym.hip"), "-o",
                                objs["kernels_sym"]],
-        [hipcc] + hip_flags + ["-c", os.path.join(CSRC, "kernels_split.hip"), "-o",
-                               objs["kernels_split"]],
         [hipcc] + hip_flags + ["-c", os.path.join(CSRC, "noalloc.hip"), "-o", objs["noalloc"]],
     ]
     if verbose:

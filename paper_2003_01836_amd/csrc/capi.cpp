@@ -18,7 +18,6 @@
 
 #include "internal.hpp"
 #include "parallel.hpp"
-#include "kernels_split.hpp"
 #include "setup_gpu.hpp"
 
 using bltc_detail::fail;
@@ -234,93 +233,6 @@ void schedule_single_vector(bltc_plan* plan)
     plan->d.group_threads = bltc::kGroupSizeSym;
 }
 
-// Threads per target T > 1: batch b becomes the batches b T + p, p < T, whose
-// lists are contiguous pieces of b's far and (reduced) direct lists, over T
-// copies of the targets; copy p writes its partial potentials to row p of
-// plan->tpt_buf in caller order.  The mutual-pair results of b go with piece 0.
-int upload_split(bltc_plan* plan, hipStream_t s)
-{
-    const bltc::HostPlan& hp = plan->hp;
-    const bltc::DevicePlan& d = plan->d;
-    const int32_t T = plan->prm.threads_per_target;
-    const int64_t nb = d.nbatches, nt = d.nt;
-    bltc::DevicePlan& t = plan->dt;
-    t = d;
-    auto split = [&](const std::vector<int32_t>& off) {
-        std::vector<int32_t> out(static_cast<size_t>(nb * T + 1), 0);
-        for (int64_t b = 0; b < nb; ++b) {
-            const int64_t n = off[b + 1] - off[b];
-            for (int32_t p = 0; p < T; ++p)
-                out[b * T + p] = static_cast<int32_t>(off[b] + n * p / T);
-        }
-        out[nb * T] = nb > 0 ? off[nb] : 0;
-        return out;
-    };
-    HIP_TRY(plan->put(&t.far_off, split(hp.far_off), s));
-    if (d.sym) {
-        HIP_TRY(plan->put(&t.sym_near_off, split(plan->sym_near_off_h), s));
-        std::vector<int32_t> pc_off(static_cast<size_t>(nb * T + 1), 0);
-        std::vector<int64_t> bbeg(static_cast<size_t>(nb * T));
-        for (int64_t b = 0; b < nb; ++b)
-            for (int32_t p = 0; p < T; ++p) {
-                pc_off[b * T + p] = p == 0 ? plan->sym_pc_off_h[b] : plan->sym_pc_off_h[b + 1];
-                bbeg[b * T + p] = p * nt + hp.batch_begin[b];
-            }
-        pc_off[nb * T] = nb > 0 ? plan->sym_pc_off_h[nb] : 0;
-        HIP_TRY(plan->put(&t.sym_pc_off, pc_off, s));
-        HIP_TRY(plan->put(&t.batch_begin, bbeg, s));
-    } else {
-        HIP_TRY(plan->put(&t.near_off, split(hp.near_off), s));
-    }
-    // T copies of the targets, written on the device; copy p writes p nt +
-    // caller index
-    HIP_TRY(plan->alloc(&t.tgt, static_cast<size_t>(T * nt)));
-    int64_t* orig_t = nullptr;
-    HIP_TRY(plan->alloc(&orig_t, static_cast<size_t>(T * nt)));
-    t.tgt_orig = orig_t;
-    HIP_TRY(bltc::launch_replicate_targets(t.tgt, orig_t, d.tgt, d.tgt_orig, nt, T, s));
-    std::vector<int64_t> end_t(static_cast<size_t>(nb * T));
-    // batches, their boxes (FP32-mixed) and the workgroup schedule, each
-    // piece with 1/T of its batch's work
-    std::vector<int64_t> begin_t(static_cast<size_t>(nb * T)), count_t(begin_t.size()),
-        cost_t(begin_t.size());
-    for (int64_t b = 0; b < nb; ++b) {
-        const int64_t far = static_cast<int64_t>(hp.far_off[b + 1] - hp.far_off[b]) * hp.P;
-        const int64_t near = std::max<int64_t>(0, hp.batch_cost[b] - far);
-        const int64_t cost = far + (near * 22) / 10;
-        for (int32_t p = 0; p < T; ++p) {
-            begin_t[b * T + p] = p * nt + hp.batch_begin[b];
-            count_t[b * T + p] = hp.batch_count[b];
-            end_t[b * T + p] = begin_t[b * T + p] + hp.batch_count[b];
-            cost_t[b * T + p] = cost / T;
-        }
-    }
-    HIP_TRY(plan->put(&t.batch_end, end_t, s));
-    if (plan->prm.precision == BLTC_FP32_MIXED) {
-        std::vector<double4> bi(static_cast<size_t>(nb * T));
-        for (int64_t b = 0; b < nb; ++b) {
-            const int32_t bn = hp.batch_node[b];
-            for (int32_t p = 0; p < T; ++p)
-                bi[b * T + p] = make_double4(hp.tgt.center[3 * bn], hp.tgt.center[3 * bn + 1],
-                                             hp.tgt.center[3 * bn + 2], hp.tgt.radius[bn]);
-        }
-        HIP_TRY(plan->put(&t.batch_info, bi, s));
-    }
-    std::vector<int32_t> gb;
-    std::vector<int64_t> gf;
-    bltc::group_schedule(begin_t, count_t, cost_t, bltc::kGroupSizeSym, hp.prm.xcds, gb, gf);
-    HIP_TRY(plan->put(&t.group_batch, gb, s));
-    HIP_TRY(plan->put(&t.group_first, gf, s));
-    t.ngroups = static_cast<int64_t>(gb.size());
-    t.group_threads = bltc::kGroupSizeSym;
-    t.nbatches = nb * T;
-    t.nt = T * nt;
-    HIP_TRY(plan->alloc(&plan->tpt_buf, static_cast<size_t>(T * nt)));
-    HIP_TRY(hipStreamSynchronize(s));
-    plan->tpt = T;
-    return BLTC_OK;
-}
-
 }  // namespace
 
 namespace {
@@ -338,6 +250,7 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
     d.nchunks = static_cast<int64_t>(hp.chunk_slot.size());
     d.ngroups = static_cast<int64_t>(hp.group_batch.size());
     d.nbatches = static_cast<int64_t>(hp.batch_begin.size());
+    d.threads_per_target = std::max(1, plan->prm.threads_per_target);
 
     if (!plan->device_particles) {
         std::vector<double4> src(d.ns), tgt(d.nt);
@@ -445,11 +358,6 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
         HIP_TRY(plan->put(&d.batch_info, batch_info, s));
         HIP_TRY(plan->alloc(&d.qhat32, static_cast<size_t>(d.nslots) * hp.P));
         HIP_TRY(hipStreamSynchronize(s));
-    }
-    if (plan->prm.threads_per_target > 1) {
-        rc = upload_split(plan, s);
-        if (rc != BLTC_OK)
-            return rc;
     }
     // host staging vectors die at return: finish the copies first
     HIP_TRY(hipStreamSynchronize(s));
@@ -609,16 +517,7 @@ int execute(bltc_plan* plan, const double* q, int32_t num_q, int64_t q_ld, doubl
                 HIP_TRY(hipEventRecord(plan->ev_pairs, s));
             }
         }
-        if (plan->tpt > 1) {
-            // several lanes per target: partial potentials, then their sum
-            if (d.hermite)
-                HIP_TRY(bltc::launch_interact_hermite(plan->dt, kp, plan->tpt_buf, s));
-            else if (kp.precision == BLTC_FP32_MIXED)
-                HIP_TRY(bltc::launch_interact_mixed(plan->dt, kp, plan->tpt_buf, s));
-            else
-                HIP_TRY(bltc::launch_interact(plan->dt, kp, plan->tpt_buf, s));
-            HIP_TRY(bltc::launch_sum_parts(plan->tpt_buf, d.nt, plan->tpt, phi, s));
-        } else if (d.hermite) {
+        if (d.hermite) {
             HIP_TRY(bltc::launch_interact_hermite(d, kp, phi, s));
         } else if (kp.precision == BLTC_FP32_MIXED) {
             HIP_TRY(bltc::launch_interact_mixed(d, kp, phi, s));
@@ -724,10 +623,6 @@ int bltc_internal_upload_symmetric(bltc_plan* plan, bltc::DevicePlan& d,
     bltc::SymPlan sp;
     if (!bltc::plan_symmetric(dl, sub, INT64_MAX, kPairWorkspaceBytes / 4 / sizeof(double), sp))
         return BLTC_OK;
-    if (&d == &plan->d) {
-        plan->sym_near_off_h = sp.near_off;
-        plan->sym_pc_off_h = sp.pc_off;
-    }
     HIP_TRY(plan->put(&d.sym_near_off, sp.near_off, s));
     HIP_TRY(plan->put(&d.sym_near_begin, sp.near_begin, s));
     HIP_TRY(plan->put(&d.sym_near_count, sp.near_count, s));
@@ -780,9 +675,7 @@ int bltc_internal_finish_pairs(bltc_plan* plan, hipStream_t s)
         for (int64_t b = 0; b < nb; ++b)
             ntgt = std::max(ntgt, pr.batch_begin[b] + pr.batch_count[b]);
         const int64_t npc = nb > 0 ? sp.pc_off[nb] : 0;
-        // pieces of several lanes per target read the sums through their own table
-        const int64_t piece_bytes = (&d == &plan->d && plan->tpt > 1) ? (nb * plan->tpt + 1) * 4 : 0;
-        const int64_t fixed = units_bytes + ntgt * 8 + nb * 8 + npc * 8 + (nb + 1) * 4 + piece_bytes;
+        const int64_t fixed = units_bytes + ntgt * 8 + nb * 8 + npc * 8 + (nb + 1) * 4;
         int64_t rounds = 1;
         for (int it = 0;; ++it) {
             const int64_t room = std::min<int64_t>(kPairWorkspaceBytes,
@@ -895,28 +788,8 @@ int bltc_internal_finish_pairs(bltc_plan* plan, hipStream_t s)
         HIP_TRY(plan->put(&pc_off, ident, s));
         d.sym_pc_off = pc_off;
         d.sym_pc_base = d.batch_begin;
-        if (&d == &plan->d)
-            plan->sym_pc_off_h = ident;
-        if (&d == &plan->d && plan->tpt > 1) {
-            // pieces of several lanes per target: the sums go with piece 0
-            const int32_t T = plan->tpt;
-            std::vector<int32_t> pc_t(static_cast<size_t>(nb * T + 1), 0);
-            for (int64_t b = 0; b < nb; ++b)
-                for (int32_t p = 0; p < T; ++p)
-                    pc_t[b * T + p] = p == 0 ? static_cast<int32_t>(b) : static_cast<int32_t>(b + 1);
-            pc_t[nb * T] = static_cast<int32_t>(nb);
-            HIP_TRY(plan->put(&plan->dt.sym_pc_off, pc_t, s));
-            plan->dt.sym_pc_base = d.batch_begin;
-        }
     }
     d.sym_rounds = R;
-    if (&d == &plan->d && plan->tpt > 1) {
-        plan->dt.sym_unit = d.sym_unit;
-        plan->dt.sym_units = d.sym_units;
-        plan->dt.sym_out = d.sym_out;
-        plan->dt.sym_acc = d.sym_acc;
-        plan->dt.sym_rounds = R;
-    }
     HIP_TRY(hipStreamSynchronize(s));
     pr.round_unit = round_sub;
     pr.rounds = R;

@@ -1,18 +1,19 @@
 // kernels.hip -- gfx950 kernels of the barycentric Lagrange treecode.
 //
 // Mapping (CDNA4, wave64):
-//  * interactions: one target per lane, 256 targets of one batch per
+//  * interactions: one target per lane, 64 targets of one batch per
 //    workgroup; every lane of a wave walks the same interaction list (the MAC
 //    is applied per batch, Sec. III-B), so source particles, Chebyshev points
 //    and modified charges are wave-uniform and are read through the scalar
-//    data cache into SGPRs -- no LDS staging and no barriers.  Each lane owns
-//    its target's accumulator, so phi is written exactly once, in caller
-//    order, without atomics.
+//    data cache into SGPRs -- no LDS staging.  The waves of a workgroup share
+//    the lists of its targets (device_split.hpp); phi is written exactly once,
+//    in caller order, without atomics.
 //  * the upward pass lives in kernels_upward.hip (matrix cores).
 #include <algorithm>
 
 #include "kernels.hpp"
 #include "device_common.hpp"
+#include "device_split.hpp"
 
 namespace bltc {
 namespace {
@@ -20,15 +21,16 @@ namespace {
 using namespace dev;
 
 // ---------------------------------------------------------------------------
-// Batch/cluster approximation (eq. 11): sum_k G(x, s_k) qhat_k over the
-// (n+1)^3 tensor grid.  With the grid separable, r^2 = a_k1 + b_k2 + c_k3
+// Batch/cluster approximation (eq. 11): sum_k G(x, s_k) qhat_k over the planes
+// k1 in [ka, kb) of the (n+1)^3 tensor grid.  With the grid separable, r^2 = a_k1 + b_k2 + c_k3
 // where a, b, c are the squared 1-D distances, formed once per target.
 // `nd` ([3][n+1] points) and `qh` ([P] charges) are wave-uniform.
 // ---------------------------------------------------------------------------
 template <int N, int KER>
 __device__ __forceinline__ double far_sum_f64(double x, double y, double z,
                                               const double* __restrict__ nd,
-                                              const double* __restrict__ qh, const KernelArg& kappa)
+                                              const double* __restrict__ qh, int ka, int kb,
+                                              const KernelArg& kappa)
 {
     constexpr int NP = N + 1;
     double b2[NP], c2[NP];
@@ -41,7 +43,7 @@ __device__ __forceinline__ double far_sum_f64(double x, double y, double z,
     }
     double acc0 = 0.0, acc1 = 0.0;
 #pragma unroll 1
-    for (int k1 = 0; k1 < NP; ++k1) {
+    for (int k1 = ka; k1 < kb; ++k1) {
         const double dx = x - nd[k1];
         const double a2 = dx * dx;
         const double* __restrict__ q1 = qh + k1 * NP * NP;
@@ -63,10 +65,12 @@ __device__ __forceinline__ double far_sum_f64(double x, double y, double z,
 }
 
 // ---------------------------------------------------------------------------
-// Interactions of one workgroup: 256 consecutive targets of one batch.
+// Interactions of one workgroup: 64 consecutive targets of one batch, their
+// lists shared by the workgroup's waves.
 // ---------------------------------------------------------------------------
 template <int N, int KER>
-__global__ __launch_bounds__(kGroupSize) void interact_f64(
+__global__ __launch_bounds__(64 * kMaxWaves) void interact_f64(
+    int32_t ngroups, int32_t sub_shift, int32_t log_w,
     const double4* __restrict__ tgt, const int64_t* __restrict__ tgt_orig,
     const double4* __restrict__ src, const int32_t* __restrict__ group_batch,
     const int64_t* __restrict__ group_first, const int64_t* __restrict__ batch_end,
@@ -80,45 +84,52 @@ __global__ __launch_bounds__(kGroupSize) void interact_f64(
 {
     constexpr int NP = N + 1;
     constexpr int P = NP * NP * NP;
+    extern __shared__ double lds[];
     __shared__ double exp_tab[64];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg kappa{kc.kappa, kc.delta2, exp_tab};
-    const int g = blockIdx.x;
-    const int b = group_batch[g];
+    int sub;
+    const int g = group_of_block(blockIdx.x, sub_shift, sub);
+    const int b = g < ngroups ? group_batch[g] : -1;
     if (b < 0)
         return;  // empty slot of the per-die schedule
-    const int64_t first = group_first[g];
+    const int64_t first = group_first[g] + 64 * sub;
     const int64_t end = batch_end[b];
-    const int64_t wave_first = first + (threadIdx.x & ~63);
-    if (wave_first >= end)
-        return;  // the whole wave lies past the batch end
-    int64_t i = first + threadIdx.x;
+    if (first >= end)
+        return;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    int64_t i = first + lane;
     const bool valid = i < end;
     if (!valid)
         i = end - 1;
     const double4 t = tgt[i];
     double acc = 0.0;
 
-    const int f_end = far_off[b + 1];
-    for (int f = far_off[b]; f < f_end; ++f) {
-        const int64_t slot = far_slot[f];
-        acc += far_sum_f64<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP, qhat + slot * P,
-                                   kappa);
+    const int f0 = far_off[b];
+    const int n1 = near_off[b + 1];
+    const ListPart part =
+        list_part<NP, NP * NP, kBlockCost<KER, false>>(w, log_w, far_off[b + 1] - f0, near_off[b], n1, near_count,
+                               pc_off ? pc_off[b] : 0, pc_off ? pc_off[b + 1] : 0);
+    int f = part.plane0 / NP, ka = part.plane0 - f * NP;
+    for (int pl = part.plane0; pl < part.plane1; ++f) {
+        const int64_t slot = far_slot[f0 + f];
+        const int kb = ka + part.plane1 - pl < NP ? ka + part.plane1 - pl : NP;
+        acc += far_sum_f64<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP, qhat + slot * P, ka,
+                                   kb, kappa);
+        pl += kb - ka;
+        ka = 0;
     }
-    const int n_end = near_off[b + 1];
-    for (int e = near_off[b]; e < n_end; ++e)
-        acc += near_sum_f64<KER>(t.x, t.y, t.z, src + near_begin[e],
-                                 static_cast<int32_t>(near_count[e]), kappa);
-
+    for_direct_runs(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t) {
+        acc += near_sum_f64<KER>(t.x, t.y, t.z, src + j, cnt, kappa);
+    });
     if (pc_off) {
         // mutual leaf pairs: this target's row or column sums of each unit
-        const int64_t pos = i - batch_begin[b];
-        const int pc_end = pc_off[b + 1];
-        for (int e = pc_off[b]; e < pc_end; ++e)
-            acc += pair_out[pc_base[e] + pos];
+        acc += pair_results(part, pc_base, pair_out, i - batch_begin[b]);
     }
-    if (valid)
+    acc = sum_waves(acc, w, log_w, lds);
+    if (w == 0 && valid)
         phi[tgt_orig[i]] = acc;
 }
 
@@ -252,8 +263,11 @@ hipError_t run_interact(const DevicePlan& d, double* phi, KernelConst kc, hipStr
     if (d.ngroups == 0)
         return hipSuccess;
     const NearLists nl = near_lists(d);
-    hipLaunchKernelGGL((interact_f64<N, KER>), dim3(static_cast<unsigned>(d.ngroups)),
-                       dim3(d.group_threads), 0, s, d.tgt, d.tgt_orig, d.src, d.group_batch,
+    const GroupLaunch gl = group_launch(d);
+    hipLaunchKernelGGL((interact_f64<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w),
+                       gl.log_w ? sizeof(double) * (64u << gl.log_w) : 0, s,
+                       static_cast<int32_t>(d.ngroups), gl.sub_shift, gl.log_w, d.tgt, d.tgt_orig,
+                       d.src, d.group_batch,
                        d.group_first, d.batch_end, d.far_off, d.far_slot, nl.off, nl.begin,
                        nl.count, d.slot_nodes, d.qhat, nl.pc_off, nl.pc_base, nl.pair_out,
                        nl.batch_begin, phi, kc);

@@ -9,8 +9,9 @@ namespace bltc {
 
 constexpr int kMaxDegree = 16;
 constexpr int kMaxHermiteDegree = 10;   // Hermite treecode: 8 (n+1)^3 charges per cluster
-constexpr int kGroupSize = 256;      // targets (lanes) per interaction workgroup
-constexpr int kGroupSizeSym = 64;    // the same for plans with mutual pairs (finer tail)
+constexpr int kGroupSize = 256;      // targets of a group of the schedule
+constexpr int kGroupSizeSym = 64;    // the same for one-vector plans (finer tail)
+constexpr int kMaxWaves = 16;        // waves of an interaction workgroup
 
 // The direct lists the single-vector interaction kernels walk: the plan's own,
 // or, when mutual leaf pairs are evaluated by launch_near_pairs, the reduced
@@ -89,9 +90,11 @@ struct DevicePlan {
     // lists and add, per target, the unit results listed in sym_pc_*
     int32_t sym = 0;
     int64_t sym_units = 0;            // sub-units
-    // targets per workgroup of the single-vector interaction kernels (the plan's
-    // group size: kGroupSize, or kGroupSizeSym for plans with mutual pairs)
+    // targets per group of the schedule (kGroupSize or kGroupSizeSym); the
+    // single-vector interaction kernels take 64 of them per workgroup
     int32_t group_threads = 256;
+    // lanes per target asked for (waves of an interaction workgroup, at least)
+    int32_t threads_per_target = 1;
     SymUnit* sym_unit = nullptr;
     double* sym_out = nullptr;
     int32_t* sym_near_off = nullptr;
@@ -108,6 +111,36 @@ struct DevicePlan {
     int32_t sym_rounds = 0;
     double* sym_acc = nullptr;
 };
+
+// Launch of a single-vector interaction kernel: workgroups of 64 targets,
+// 1 << sub_shift per group of the schedule, 1 << log_w waves each.
+//
+// Waves per workgroup: a target's lists are one serial chain per lane, so a
+// problem of few targets leaves the chip (1024 SIMDs, up to 8 waves each) idle,
+// and one of many ends in a tail as long as its heaviest workgroup.  The waves
+// are doubled until about kWavesWanted of them are launched (four times what is
+// resident), up to 8 per workgroup, or 16 where 8 would still leave SIMDs with
+// less than four waves: 16 waves leave slots of a CU unused when the registers
+// allow fewer than 32 (Yukawa at n = 6, 2 10^5 targets: 17.5 ms at 16, 16.3 at 8,
+// 21.4 at 1; 30,011 regularized targets: 14.0 ms at 1, 3.2 at 16).
+constexpr int64_t kWavesWanted = 32768;
+constexpr int64_t kWavesFew = 4096;
+struct GroupLaunch {
+    uint32_t blocks;
+    int32_t sub_shift, log_w;
+};
+inline GroupLaunch group_launch(const DevicePlan& d, int max_waves = kMaxWaves)
+{
+    GroupLaunch g{0, d.group_threads == kGroupSizeSym ? 0 : 2, 0};
+    const int64_t padded = (d.ngroups + 7) / 8 * 8;
+    g.blocks = static_cast<uint32_t>(padded << g.sub_shift);
+    const int64_t targets = (d.nt + 63) / 64;
+    while ((2 << g.log_w) <= max_waves &&
+           ((1 << g.log_w) < d.threads_per_target ||
+            (targets << g.log_w) < (g.log_w < 3 ? kWavesWanted : kWavesFew)))
+        ++g.log_w;
+    return g;
+}
 
 // Constants of the kernel G passed to the interaction kernels: kappa of the
 // Yukawa kernel and delta^2 of the regularized Coulomb kernel.

@@ -11,18 +11,25 @@
 // so one grid point costs one reciprocal square root (and for Yukawa one
 // exponential), the recurrences for g1..g3 and eight products with its
 // charges.  Mapping as in the BLTC interaction kernel: one target per lane,
-// 256 targets of one batch per workgroup, wave-uniform lists, grid nodes and
+// 64 targets of one batch per workgroup whose waves share the batch's lists
+// (device_split.hpp), wave-uniform lists, grid nodes and
 // charges through the scalar cache (the eight charges of a grid point are
 // contiguous: one 64-byte load), phi written once per target in caller order.
 // An FP32-mixed form follows the FP64 kernel.
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "device_common.hpp"
 #include "device_mixed.hpp"
+#include "device_split.hpp"
 
 namespace bltc {
 namespace {
 
 using namespace dev;
+
+// waves of a workgroup: up to 256 VGPRs each (the larger degrees need over 128)
+constexpr int kHermiteWaves = 8;
 
 // G, g1, g2, g3 at r^2 > 0 (well-separated points; 1/sqrt by one Newton step)
 template <int KER>
@@ -58,7 +65,7 @@ __device__ __forceinline__ void green_derivatives(double r2, const KernelArg& ka
 template <int N, int KER>
 __device__ __forceinline__ double far_sum_hermite(double x, double y, double z,
                                                   const double* __restrict__ nd,
-                                                  const double* __restrict__ qh,
+                                                  const double* __restrict__ qh, int pa, int pb,
                                                   const KernelArg& ka)
 {
     constexpr int NP = N + 1;
@@ -72,7 +79,7 @@ __device__ __forceinline__ double far_sum_hermite(double x, double y, double z,
     }
     double acc0 = 0.0, acc1 = 0.0;
 #pragma unroll 1
-    for (int k1 = 0; k1 < NP; ++k1) {
+    for (int k1 = pa; k1 < pb; ++k1) {
         const double d1 = x - nd[k1];
         const double a2 = d1 * d1;
         const double* __restrict__ q1 = qh + k1 * NP * NP * 8;
@@ -106,7 +113,8 @@ __device__ __forceinline__ double far_sum_hermite(double x, double y, double z,
 }
 
 template <int N, int KER>
-__global__ __launch_bounds__(kGroupSize) void interact_hermite_f64(
+__global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_f64(
+    int32_t ngroups, int32_t sub_shift, int32_t log_w,
     const double4* __restrict__ tgt, const int64_t* __restrict__ tgt_orig,
     const double4* __restrict__ src, const int32_t* __restrict__ group_batch,
     const int64_t* __restrict__ group_first, const int64_t* __restrict__ batch_end,
@@ -120,42 +128,53 @@ __global__ __launch_bounds__(kGroupSize) void interact_hermite_f64(
 {
     constexpr int NP = N + 1;
     constexpr int P8 = 8 * NP * NP * NP;
+    extern __shared__ double lds[];
     __shared__ double exp_tab[64];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg ka{kc.kappa, kc.delta2, exp_tab};
-    const int g = blockIdx.x;
-    const int b = group_batch[g];
+    int sub;
+    const int g = group_of_block(blockIdx.x, sub_shift, sub);
+    const int b = g < ngroups ? group_batch[g] : -1;
     if (b < 0)
         return;  // empty slot of the per-die schedule
-    const int64_t first = group_first[g];
+    const int64_t first = group_first[g] + 64 * sub;
     const int64_t end = batch_end[b];
-    if (first + (threadIdx.x & ~63) >= end)
-        return;  // the whole wave lies past the batch end
-    int64_t i = first + threadIdx.x;
+    if (first >= end)
+        return;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    int64_t i = first + lane;
     const bool valid = i < end;
     if (!valid)
         i = end - 1;
     const double4 t = tgt[i];
     double acc = 0.0;
-    const int f_end = far_off[b + 1];
-    for (int f = far_off[b]; f < f_end; ++f) {
-        const int64_t slot = far_slot[f];
+    // a grid point costs four to five far-field kernel values of the BLTC
+    const int f0 = far_off[b];
+    const int n1 = near_off[b + 1];
+    const ListPart part =
+        list_part<NP, 4 * NP * NP, kBlockCost<KER, false>>(w, log_w, far_off[b + 1] - f0, near_off[b], n1,
+                                            near_count, pc_off ? pc_off[b] : 0,
+                                            pc_off ? pc_off[b + 1] : 0);
+    int f = part.plane0 / NP, pa = part.plane0 - f * NP;
+    for (int pl = part.plane0; pl < part.plane1; ++f) {
+        const int64_t slot = far_slot[f0 + f];
+        const int pb = pa + part.plane1 - pl < NP ? pa + part.plane1 - pl : NP;
         acc += far_sum_hermite<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP, qh + slot * P8,
-                                       ka);
+                                       pa, pb, ka);
+        pl += pb - pa;
+        pa = 0;
     }
-    const int n_end = near_off[b + 1];
-    for (int e = near_off[b]; e < n_end; ++e)
-        acc += near_sum_f64<KER>(t.x, t.y, t.z, src + near_begin[e],
-                                 static_cast<int32_t>(near_count[e]), ka);
+    for_direct_runs(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t) {
+        acc += near_sum_f64<KER>(t.x, t.y, t.z, src + j, cnt, ka);
+    });
     if (pc_off) {
         // mutual leaf pairs: this target's row or column sums of each unit
-        const int64_t pos = i - batch_begin[b];
-        const int pc_end = pc_off[b + 1];
-        for (int e = pc_off[b]; e < pc_end; ++e)
-            acc += pair_out[pc_base[e] + pos];
+        acc += pair_results(part, pc_base, pair_out, i - batch_begin[b]);
     }
-    if (valid)
+    acc = sum_waves(acc, w, log_w, lds);
+    if (w == 0 && valid)
         phi[tgt_orig[i]] = acc;
 }
 
@@ -204,7 +223,7 @@ __device__ __forceinline__ float hermite_term_f32(float r2, float d1, float d2, 
 template <int N, int KER>
 __device__ __forceinline__ double far_sum_hermite_f32(double x, double y, double z,
                                                       const double* __restrict__ nd,
-                                                      const float* __restrict__ qh,
+                                                      const float* __restrict__ qh, int pa, int pb,
                                                       const KernelArg32& nk, float kf)
 {
     constexpr int NP = N + 1;
@@ -218,7 +237,7 @@ __device__ __forceinline__ double far_sum_hermite_f32(double x, double y, double
     }
     double acc = 0.0;
 #pragma unroll 1
-    for (int k1 = 0; k1 < NP; ++k1) {
+    for (int k1 = pa; k1 < pb; ++k1) {
         const float d1 = static_cast<float>(x - nd[k1]);
         const float a2 = d1 * d1;
         const float* __restrict__ q1 = qh + k1 * NP * NP * 8;
@@ -250,7 +269,8 @@ template <int N>
 constexpr bool kStageHermite = N == 4;
 
 template <int N, int KER>
-__global__ __launch_bounds__(kGroupSize) void interact_hermite_mixed(
+__global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_mixed(
+    int32_t ngroups, int32_t sub_shift, int32_t log_w,
     const double4* __restrict__ tgt, const int64_t* __restrict__ tgt_orig,
     const double4* __restrict__ src, const float4* __restrict__ src32,
     const double4* __restrict__ node_info, const double4* __restrict__ batch_info,
@@ -266,64 +286,70 @@ __global__ __launch_bounds__(kGroupSize) void interact_hermite_mixed(
 {
     constexpr int NP = N + 1;
     constexpr int P8 = 8 * NP * NP * NP;
+    extern __shared__ double lds[];
     __shared__ double exp_tab[64];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg ka{kc.kappa, kc.delta2, exp_tab};
     const KernelArg32 nk = kernel_arg32(kc.kappa, kc.delta2);
     const float kf = static_cast<float>(kc.kappa);
-    const int g = blockIdx.x;
-    const int b = group_batch[g];
+    int sub;
+    const int g = group_of_block(blockIdx.x, sub_shift, sub);
+    const int b = g < ngroups ? group_batch[g] : -1;
     if (b < 0)
         return;  // empty slot of the per-die schedule
-    const int64_t first = group_first[g];
+    const int64_t first = group_first[g] + 64 * sub;
     const int64_t end = batch_end[b];
-    // (one-vector plans launch one wave per workgroup, so every wave of a
-    // workgroup reaches the barriers of the far-field loop below; a wave
-    // past the batch end evaluates its clamped targets and stores nothing)
-    int64_t i = first + threadIdx.x;
+    if (first >= end)
+        return;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    int64_t i = first + lane;
     const bool valid = i < end;
     if (!valid)
         i = end - 1;
     const double4 t = tgt[i];
     double acc = 0.0;
-    const int f_end = far_off[b + 1];
-    if constexpr (kStageHermite<N>) {
-        // the cluster's 8 (n+1)^3 modified charges staged in LDS, as in the
-        // FP32-mixed BLTC kernel
-        extern __shared__ float qs[];
-        for (int f = far_off[b]; f < f_end; ++f) {
-            const int64_t slot = far_slot[f];
-            const float* __restrict__ qg = qh32 + slot * P8;
-            __syncthreads();   // the previous cluster's charges are read
-            for (int k = threadIdx.x; k < P8; k += blockDim.x)
+    // a grid point costs four to five far-field kernel values of the BLTC
+    const int f0 = far_off[b];
+    const int n1 = near_off[b + 1];
+    const ListPart part =
+        list_part<NP, 5 * NP * NP, kBlockCost<KER, true>>(w, log_w, far_off[b + 1] - f0, near_off[b], n1,
+                                            near_count, pc_off ? pc_off[b] : 0,
+                                            pc_off ? pc_off[b + 1] : 0);
+    int f = part.plane0 / NP, pa = part.plane0 - f * NP;
+    for (int pl = part.plane0; pl < part.plane1; ++f) {
+        const int64_t slot = far_slot[f0 + f];
+        const int pb = pa + part.plane1 - pl < NP ? pa + part.plane1 - pl : NP;
+        const float* __restrict__ qg = qh32 + slot * P8;
+        if constexpr (kStageHermite<N>) {
+            // the cluster's 8 (n+1)^3 modified charges staged in LDS per wave, as
+            // in the FP32-mixed BLTC kernel
+            float* const qs = reinterpret_cast<float*>(lds) + w * P8;
+            wave_lds_sync();   // the previous cluster's charges are read
+            for (int k = pa * 8 * NP * NP + lane; k < pb * 8 * NP * NP; k += 64)
                 qs[k] = qg[k];
-            __syncthreads();
-            acc += far_sum_hermite_f32<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP, qs,
+            wave_lds_sync();
+            acc += far_sum_hermite_f32<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP, qs, pa, pb,
+                                               nk, kf);
+        } else {
+            acc += far_sum_hermite_f32<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP, qg, pa, pb,
                                                nk, kf);
         }
-    } else {
-        for (int f = far_off[b]; f < f_end; ++f) {
-            const int64_t slot = far_slot[f];
-            acc += far_sum_hermite_f32<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP,
-                                               qh32 + slot * P8, nk, kf);
-        }
+        pl += pb - pa;
+        pa = 0;
     }
     const double4 bi = batch_info[b];
-    const int n_end = near_off[b + 1];
-    for (int e = near_off[b]; e < n_end; ++e) {
-        const int64_t nb = near_begin[e];
-        acc += near_entry_mixed<KER>(t.x, t.y, t.z, bi, node_info[near_leaf[e]], src32 + nb,
-                                     src + nb, static_cast<int32_t>(near_count[e]), nk, ka);
-    }
+    for_direct_runs(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t e) {
+        acc += near_entry_mixed<KER>(t.x, t.y, t.z, bi, node_info[near_leaf[e]], src32 + j, src + j,
+                                     cnt, nk, ka);
+    });
     if (pc_off) {
         // mutual leaf pairs: this target's row or column sums of each unit
-        const int64_t pos = i - batch_begin[b];
-        const int pc_end = pc_off[b + 1];
-        for (int e = pc_off[b]; e < pc_end; ++e)
-            acc += pair_out[pc_base[e] + pos];
+        acc += pair_results(part, pc_base, pair_out, i - batch_begin[b]);
     }
-    if (valid)
+    acc = sum_waves(acc, w, log_w, lds);
+    if (w == 0 && valid)
         phi[tgt_orig[i]] = acc;
 }
 
@@ -334,9 +360,12 @@ hipError_t run_interact_hermite_mixed(const DevicePlan& d, double* phi, KernelCo
     if (d.ngroups == 0)
         return hipSuccess;
     const NearLists nl = near_lists(d);
-    const size_t lds = kStageHermite<N> ? sizeof(float) * 8 * (N + 1) * (N + 1) * (N + 1) : 0;
-    hipLaunchKernelGGL((interact_hermite_mixed<N, KER>), dim3(static_cast<unsigned>(d.ngroups)),
-                       dim3(d.group_threads), lds, s, d.tgt, d.tgt_orig, d.src, d.src32,
+    const GroupLaunch gl = group_launch(d, kHermiteWaves);
+    const size_t stage = kStageHermite<N> ? sizeof(float) * 8 * (N + 1) * (N + 1) * (N + 1) : 0;
+    const size_t lds = std::max(stage, gl.log_w ? 64 * sizeof(double) : size_t(0)) << gl.log_w;
+    hipLaunchKernelGGL((interact_hermite_mixed<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w), lds,
+                       s, static_cast<int32_t>(d.ngroups), gl.sub_shift, gl.log_w, d.tgt, d.tgt_orig,
+                       d.src, d.src32,
                        d.node_info, d.batch_info, d.group_batch, d.group_first, d.batch_end,
                        d.far_off, d.far_slot, nl.off, nl.begin, nl.count, nl.leaf, d.slot_nodes,
                        d.qhat32, nl.pc_off, nl.pc_base, nl.pair_out, nl.batch_begin, phi, kc);
@@ -349,8 +378,11 @@ hipError_t run_interact_hermite(const DevicePlan& d, double* phi, KernelConst kc
     if (d.ngroups == 0)
         return hipSuccess;
     const NearLists nl = near_lists(d);
-    hipLaunchKernelGGL((interact_hermite_f64<N, KER>), dim3(static_cast<unsigned>(d.ngroups)),
-                       dim3(d.group_threads), 0, s, d.tgt, d.tgt_orig, d.src, d.group_batch,
+    const GroupLaunch gl = group_launch(d, kHermiteWaves);
+    hipLaunchKernelGGL((interact_hermite_f64<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w),
+                       gl.log_w ? sizeof(double) * (64u << gl.log_w) : 0, s,
+                       static_cast<int32_t>(d.ngroups), gl.sub_shift, gl.log_w, d.tgt, d.tgt_orig,
+                       d.src, d.group_batch,
                        d.group_first, d.batch_end, d.far_off, d.far_slot, nl.off, nl.begin,
                        nl.count, d.slot_nodes, d.qhat_h, nl.pc_off, nl.pc_base, nl.pair_out,
                        nl.batch_begin, phi, kc);

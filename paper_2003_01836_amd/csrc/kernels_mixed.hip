@@ -8,8 +8,11 @@
 //    rounded once per target and pair) and FP32 modified charges;
 //  * FP32 partial sums cover at most kMixedFlush sources or (n+1)^2 proxy
 //    points before they are added to the lane's FP64 accumulator.
+#include <algorithm>
+
 #include "device_common.hpp"
 #include "device_mixed.hpp"
+#include "device_split.hpp"
 #include "kernels.hpp"
 
 namespace bltc {
@@ -20,7 +23,7 @@ using namespace dev;
 template <int N, int KER>
 __device__ __forceinline__ double far_sum_mixed(double xt, double yt, double zt,
                                                 const double* __restrict__ nd,
-                                                const float* __restrict__ qh,
+                                                const float* __restrict__ qh, int ka, int kb,
                                                 const KernelArg32& nk)
 {
     constexpr int NP = N + 1;
@@ -34,7 +37,7 @@ __device__ __forceinline__ double far_sum_mixed(double xt, double yt, double zt,
     }
     double acc = 0.0;
 #pragma unroll 1
-    for (int k1 = 0; k1 < NP; ++k1) {
+    for (int k1 = ka; k1 < kb; ++k1) {
         const float dx = static_cast<float>(xt - nd[k1]);
         const float a2 = dx * dx;
         const float* __restrict__ q1 = qh + k1 * NP * NP;
@@ -57,17 +60,18 @@ __device__ __forceinline__ double far_sum_mixed(double xt, double yt, double zt,
     return acc;
 }
 
-// LDS staging of a cluster's modified charges up to n = 10 (5.3 KB per
-// one-wave workgroup, about 30 workgroups per CU); above, the LDS would cut
-// the occupancy and the charges come through the scalar cache
+// LDS staging of a cluster's modified charges up to n = 10 (5.3 KB per wave);
+// above, the LDS would cut the occupancy and the charges come through the
+// scalar cache
 template <int N>
 constexpr bool kStageCharges = N <= 10;
 
 // eight waves per SIMD: the register allocation fits without spills and the
-// far-field loop's scalar loads are better hidden than at the six waves the
-// default allocation allows
+// far-field loop's loads are better hidden than at the six waves the default
+// allocation allows
 template <int N, int KER>
-__global__ __launch_bounds__(kGroupSize) __attribute__((amdgpu_waves_per_eu(8, 8))) void interact_mixed(
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(8, 8))) void interact_mixed(
+    int32_t ngroups, int32_t sub_shift, int32_t log_w,
     const double4* __restrict__ tgt, const int64_t* __restrict__ tgt_orig,
     const double4* __restrict__ src, const float4* __restrict__ src32,
     const double4* __restrict__ node_info, const double4* __restrict__ batch_info,
@@ -83,20 +87,23 @@ __global__ __launch_bounds__(kGroupSize) __attribute__((amdgpu_waves_per_eu(8, 8
 {
     constexpr int NP = N + 1;
     constexpr int P = NP * NP * NP;
+    extern __shared__ double lds[];
     __shared__ double exp_tab[64];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg kappa{kc.kappa, kc.delta2, exp_tab};
-    const int g = blockIdx.x;
-    const int b = group_batch[g];
+    int sub;
+    const int g = group_of_block(blockIdx.x, sub_shift, sub);
+    const int b = g < ngroups ? group_batch[g] : -1;
     if (b < 0)
         return;  // empty slot of the per-die schedule
-    const int64_t first = group_first[g];
+    const int64_t first = group_first[g] + 64 * sub;
     const int64_t end = batch_end[b];
-    // (one-vector plans launch one wave per workgroup, so every wave of a
-    // workgroup reaches the barriers of the far-field loop below; a wave
-    // past the batch end evaluates its clamped targets and stores nothing)
-    int64_t i = first + threadIdx.x;
+    if (first >= end)
+        return;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    int64_t i = first + lane;
     const bool valid = i < end;
     if (!valid)
         i = end - 1;
@@ -104,56 +111,44 @@ __global__ __launch_bounds__(kGroupSize) __attribute__((amdgpu_waves_per_eu(8, 8
     const KernelArg32 nk = kernel_arg32(kc.kappa, kc.delta2);
     double acc = 0.0;
 
-    const int f_end = far_off[b + 1];
-    if constexpr (kStageCharges<N>) {
-        // the cluster's modified charges staged in LDS (coalesced loads, one
-        // copy per workgroup, read back as broadcasts): 5% faster at n = 8
-        // than the wave-uniform scalar loads, whose latency the waves of a
-        // SIMD did not hide
-        extern __shared__ float qs[];
-        for (int f = far_off[b]; f < f_end; ++f) {
-            const int64_t slot = far_slot[f];
-            const float* __restrict__ qg = qhat32 + slot * P;
-            __syncthreads();   // the previous cluster's charges are read
-            for (int k = threadIdx.x; k < P; k += blockDim.x)
+    const int f0 = far_off[b];
+    const int n1 = near_off[b + 1];
+    const ListPart part =
+        list_part<NP, NP * NP, kBlockCost<KER, true>>(w, log_w, far_off[b + 1] - f0, near_off[b], n1, near_count,
+                               pc_off ? pc_off[b] : 0, pc_off ? pc_off[b + 1] : 0);
+    float* const qs = reinterpret_cast<float*>(lds) + w * P;   // this wave's staged charges
+    int f = part.plane0 / NP, ka = part.plane0 - f * NP;
+    for (int pl = part.plane0; pl < part.plane1; ++f) {
+        const int64_t slot = far_slot[f0 + f];
+        const int kb = ka + part.plane1 - pl < NP ? ka + part.plane1 - pl : NP;
+        const float* __restrict__ qg = qhat32 + slot * P;
+        if constexpr (kStageCharges<N>) {
+            // the cluster's modified charges staged in LDS (coalesced loads, one
+            // copy per wave, read back as broadcasts): 5% faster at n = 8 than
+            // the wave-uniform scalar loads, whose latency the waves of a SIMD
+            // did not hide
+            wave_lds_sync();   // the previous cluster's charges are read
+            for (int k = ka * NP * NP + lane; k < kb * NP * NP; k += 64)
                 qs[k] = qg[k];
-            __syncthreads();
-            acc += far_sum_mixed<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP, qs, nk);
+            wave_lds_sync();
+            acc += far_sum_mixed<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP, qs, ka, kb, nk);
+        } else {
+            acc += far_sum_mixed<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP, qg, ka, kb, nk);
         }
-    } else {
-        for (int f = far_off[b]; f < f_end; ++f) {
-            const int64_t slot = far_slot[f];
-            acc += far_sum_mixed<N, KER>(t.x, t.y, t.z, slot_nodes + slot * 3 * NP,
-                                         qhat32 + slot * P, nk);
-        }
+        pl += kb - ka;
+        ka = 0;
     }
     const double4 bi = batch_info[b];
-    const int n_end = near_off[b + 1];
-    for (int e = near_off[b]; e < n_end; ++e) {
-        const double4 li = node_info[near_leaf[e]];
-        const double dx = bi.x - li.x, dy = bi.y - li.y, dz = bi.z - li.z;
-        const double dist = sqrt(dx * dx + dy * dy + dz * dz);
-        const double extent = dist + bi.w + 2.0 * li.w;
-        const double tau = kMixedTauRel * extent;
-        const float tau2 = static_cast<float>(tau * tau);
-        const int64_t nb = near_begin[e];
-        const int32_t nc = static_cast<int32_t>(near_count[e]);
-        // bounding spheres further apart than tau: no pair needs the FP64 branch
-        if (dist - bi.w - li.w > 1.0625 * tau)
-            acc += near_sum_mixed<KER, false>(t.x, t.y, t.z, src32 + nb, src + nb, nc, li, tau2,
-                                              nk, kappa);
-        else
-            acc += near_sum_mixed<KER, true>(t.x, t.y, t.z, src32 + nb, src + nb, nc, li, tau2,
-                                             nk, kappa);
-    }
+    for_direct_runs(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t e) {
+        acc += near_entry_mixed<KER>(t.x, t.y, t.z, bi, node_info[near_leaf[e]], src32 + j, src + j,
+                                     cnt, nk, kappa);
+    });
     if (pc_off) {
         // mutual leaf pairs: this target's row or column sums of each unit
-        const int64_t pos = i - batch_begin[b];
-        const int pc_end = pc_off[b + 1];
-        for (int e = pc_off[b]; e < pc_end; ++e)
-            acc += pair_out[pc_base[e] + pos];
+        acc += pair_results(part, pc_base, pair_out, i - batch_begin[b]);
     }
-    if (valid)
+    acc = sum_waves(acc, w, log_w, lds);
+    if (w == 0 && valid)
         phi[tgt_orig[i]] = acc;
 }
 
@@ -163,9 +158,14 @@ hipError_t run_interact_mixed(const DevicePlan& d, double* phi, KernelConst kc, 
     if (d.ngroups == 0)
         return hipSuccess;
     const NearLists nl = near_lists(d);
-    const size_t lds = kStageCharges<N> ? sizeof(float) * (N + 1) * (N + 1) * (N + 1) : 0;
-    hipLaunchKernelGGL((interact_mixed<N, KER>), dim3(static_cast<unsigned>(d.ngroups)),
-                       dim3(d.group_threads), lds, s, d.tgt, d.tgt_orig, d.src, d.src32, d.node_info,
+    constexpr size_t stage = kStageCharges<N> ? sizeof(float) * (N + 1) * (N + 1) * (N + 1) : 0;
+    // staged charges of a workgroup within 48 KB (three workgroups or more per CU)
+    constexpr int max_waves = stage * kMaxWaves <= 48 * 1024 ? kMaxWaves : kMaxWaves / 2;
+    const GroupLaunch gl = group_launch(d, max_waves);
+    const size_t lds = std::max(stage, gl.log_w ? 64 * sizeof(double) : size_t(0)) << gl.log_w;
+    hipLaunchKernelGGL((interact_mixed<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w), lds, s,
+                       static_cast<int32_t>(d.ngroups), gl.sub_shift, gl.log_w, d.tgt, d.tgt_orig,
+                       d.src, d.src32, d.node_info,
                        d.batch_info, d.group_batch, d.group_first, d.batch_end, d.far_off,
                        d.far_slot, nl.off, nl.begin, nl.count, nl.leaf, d.slot_nodes, d.qhat32,
                        nl.pc_off, nl.pc_base, nl.pair_out, nl.batch_begin, phi, kc);
