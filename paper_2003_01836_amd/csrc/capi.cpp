@@ -132,7 +132,6 @@ int make_device_plan(bltc_plan* plan, const bltc_params* p, int64_t nt, const do
     if (mixed)
         HIP_TRY(plan->alloc(&d.src32, static_cast<size_t>(ns)));
     HIP_TRY(plan->alloc(&d.tgt, static_cast<size_t>(nt)));
-    HIP_TRY(plan->alloc(&d.tgt_orig, static_cast<size_t>(nt)));
     int64_t bad = -1;
     std::string err = bltc::build_tree_device(hp.src, ns, sx, sy, sz, p->leaf_size, src_order,
                                               d.src, mixed ? d.src32 : nullptr, s, &bad);
@@ -144,13 +143,9 @@ int make_device_plan(bltc_plan* plan, const bltc_params* p, int64_t nt, const do
         // same particles, same capacity: identical partition
         hp.tgt = hp.src;
         hp.same_tree = true;
-        if (nt > 0) {
-            HIP_TRY(hipMemcpyAsync(d.tgt, d.src, nt * sizeof(double4), hipMemcpyDeviceToDevice, s));
-            HIP_TRY(hipMemcpyAsync(d.tgt_orig, src_order, nt * sizeof(int64_t),
-                                   hipMemcpyDeviceToDevice, s));
-        }
+        HIP_TRY(bltc::launch_copy_targets(nt, d.src, src_order, d.tgt, s));
     } else {
-        err = bltc::build_tree_device(hp.tgt, nt, tx, ty, tz, p->batch_size, d.tgt_orig, d.tgt,
+        err = bltc::build_tree_device(hp.tgt, nt, tx, ty, tz, p->batch_size, nullptr, d.tgt,
                                       nullptr, s, &bad);
         if (bad >= 0)
             return fail(BLTC_EINVAL, "target coordinate %lld is not finite",
@@ -207,15 +202,13 @@ int upload_symmetric(bltc_plan* plan, hipStream_t s)
     return bltc_internal_upload_symmetric(plan, d, dl, &hp.batch_cost, s);
 }
 
-// Plans with one charge vector: interaction workgroups of kGroupSizeSym
-// targets (one wave; a finer tail than kGroupSize), ordered by the work left
+// Plans with one charge vector: interaction workgroups ordered by the work left
 // to each batch.
 void schedule_single_vector(bltc_plan* plan)
 {
     bltc::HostPlan& hp = plan->hp;
     if (plan->max_q != 1)
         return;
-    hp.prm.group_size = bltc::kGroupSizeSym;
     hp.group_batch.clear();
     hp.group_first.clear();
     // time per target: a direct term costs about 2.2 far-field terms (three
@@ -230,7 +223,6 @@ void schedule_single_vector(bltc_plan* plan)
     bltc::group_schedule(hp.batch_begin, hp.batch_count, cost, hp.prm.group_size,
                          hp.prm.xcds, hp.group_batch, hp.group_first);
     plan->d.ngroups = static_cast<int64_t>(hp.group_batch.size());
-    plan->d.group_threads = bltc::kGroupSizeSym;
 }
 
 }  // namespace
@@ -257,10 +249,10 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
         for (int64_t j = 0; j < d.ns; ++j)
             src[j] = make_double4(hp.src.x[j], hp.src.y[j], hp.src.z[j], 0.0);
         for (int64_t i = 0; i < d.nt; ++i)
-            tgt[i] = make_double4(hp.tgt.x[i], hp.tgt.y[i], hp.tgt.z[i], 0.0);
+            tgt[i] = bltc_detail::target_record(hp.tgt.x[i], hp.tgt.y[i], hp.tgt.z[i],
+                                                hp.tgt.order[i]);
         HIP_TRY(plan->put(&d.src, src, s));
         HIP_TRY(plan->put(&d.tgt, tgt, s));
-        HIP_TRY(plan->put(&d.tgt_orig, hp.tgt.order, s));
         int64_t* src_order = nullptr;
         HIP_TRY(plan->put(&src_order, hp.src.order, s));
         d.src_order = src_order;
@@ -1110,8 +1102,8 @@ int bltc_plan_view_get(const bltc_plan* plan, bltc_plan_view* out)
                 HIP_TRY(hipMemcpy(plan->view_src_order.data(), plan->d.src_order,
                                   hp.src.n * sizeof(int64_t), hipMemcpyDeviceToHost));
             if (hp.tgt.n > 0)
-                HIP_TRY(hipMemcpy(plan->view_tgt_order.data(), plan->d.tgt_orig,
-                                  hp.tgt.n * sizeof(int64_t), hipMemcpyDeviceToHost));
+                HIP_TRY(bltc_detail::copy_target_order(plan->view_tgt_order.data(), plan->d.tgt,
+                                                       hp.tgt.n));
         }
         out->source_order = plan->view_src_order.data();
         out->target_order = plan->view_tgt_order.data();

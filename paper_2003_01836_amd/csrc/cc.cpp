@@ -14,7 +14,6 @@
 //     target's path (kernels_cp.hip), phi +=.
 #include <chrono>
 #include <cstring>
-#include <numeric>
 
 #include "internal.hpp"
 #include "kernels_cp.hpp"
@@ -53,7 +52,6 @@ int create_device(bltc_plan* plan, const bltc::PlanParams& pp, int64_t nt, const
     if (mixed)
         HIP_TRY(plan->alloc(&du.src32, static_cast<size_t>(ns)));
     HIP_TRY(plan->alloc(&dd.tgt, static_cast<size_t>(nt)));
-    HIP_TRY(plan->alloc(&dd.tgt_orig, static_cast<size_t>(nt)));
     int64_t bad = -1;
     std::string err = bltc::build_tree_device(cc.src, ns, sx, sy, sz, pp.leaf_size, src_order,
                                               du.src, mixed ? du.src32 : nullptr, s, &bad);
@@ -64,13 +62,9 @@ int create_device(bltc_plan* plan, const bltc::PlanParams& pp, int64_t nt, const
     if (nt == ns && tx == sx && ty == sy && tz == sz && pp.batch_size == pp.leaf_size) {
         cc.tgt = cc.src;
         cc.same_tree = true;
-        if (nt > 0) {
-            HIP_TRY(hipMemcpyAsync(dd.tgt, du.src, nt * sizeof(double4), hipMemcpyDeviceToDevice, s));
-            HIP_TRY(hipMemcpyAsync(dd.tgt_orig, src_order, nt * sizeof(int64_t),
-                                   hipMemcpyDeviceToDevice, s));
-        }
+        HIP_TRY(bltc::launch_copy_targets(nt, du.src, src_order, dd.tgt, s));
     } else {
-        err = bltc::build_tree_device(cc.tgt, nt, tx, ty, tz, pp.batch_size, dd.tgt_orig, dd.tgt,
+        err = bltc::build_tree_device(cc.tgt, nt, tx, ty, tz, pp.batch_size, nullptr, dd.tgt,
                                       nullptr, s, &bad);
         if (bad >= 0)
             return fail(BLTC_EINVAL, "target coordinate %lld is not finite",
@@ -109,8 +103,12 @@ int upload(bltc_plan* plan, hipStream_t s)
             for (int32_t k1 = 0; k1 < np; ++k1)
                 for (int32_t k2 = 0; k2 < np; ++k2)
                     for (int32_t k3 = 0; k3 < np; ++k3)
-                        g[static_cast<size_t>(sl * P + (k1 * np + k2) * np + k3)] =
-                            make_double4(nd[k1], nd[np + k2], nd[2 * np + k3], 0.0);
+                    {
+                        // grid points are targets: their position is their index
+                        const int64_t k = sl * P + (k1 * np + k2) * np + k3;
+                        g[static_cast<size_t>(k)] = bltc_detail::target_record(
+                            nd[k1], nd[np + k2], nd[2 * np + k3], k);
+                    }
         }
         return g;
     };
@@ -121,10 +119,10 @@ int upload(bltc_plan* plan, hipStream_t s)
         for (int64_t j = 0; j < ns; ++j)
             src[j] = make_double4(cc.src.x[j], cc.src.y[j], cc.src.z[j], 0.0);
         for (int64_t i = 0; i < nt; ++i)
-            tgt[i] = make_double4(cc.tgt.x[i], cc.tgt.y[i], cc.tgt.z[i], 0.0);
+            tgt[i] = bltc_detail::target_record(cc.tgt.x[i], cc.tgt.y[i], cc.tgt.z[i],
+                                                cc.tgt.order[i]);
         HIP_TRY(plan->put(&du.src, src, s));
         HIP_TRY(plan->put(&dd.tgt, tgt, s));
-        HIP_TRY(plan->put(&dd.tgt_orig, cc.tgt.order, s));
         int64_t* src_order = nullptr;
         HIP_TRY(plan->put(&src_order, cc.src.order, s));
         du.src_order = src_order;
@@ -163,8 +161,7 @@ int upload(bltc_plan* plan, hipStream_t s)
 
     // ---- proxy potentials of the target slots
     const std::vector<double4> tgrid = expand(cc.tslot_nodes, nts);
-    std::vector<int64_t> tgrid_orig(tgrid.size()), tgrid_end(nts), leaf_end(ntl);
-    std::iota(tgrid_orig.begin(), tgrid_orig.end(), int64_t(0));
+    std::vector<int64_t> tgrid_end(nts), leaf_end(ntl);
     for (int64_t u = 0; u < nts; ++u)
         tgrid_end[u] = (u + 1) * P;
     for (int64_t r = 0; r < ntl; ++r)
@@ -176,7 +173,6 @@ int upload(bltc_plan* plan, hipStream_t s)
     px.nbatches = nts;
     px.ngroups = static_cast<int64_t>(cc.pg_batch.size());
     HIP_TRY(plan->put(&px.tgt, tgrid, s));
-    HIP_TRY(plan->put(&px.tgt_orig, tgrid_orig, s));
     HIP_TRY(plan->put(&px.group_batch, cc.pg_batch, s));
     HIP_TRY(plan->put(&px.group_first, cc.pg_first, s));
     HIP_TRY(plan->put(&px.batch_end, tgrid_end, s));
@@ -249,12 +245,11 @@ int upload(bltc_plan* plan, hipStream_t s)
         if (dd.sym) {
             cc.dg_batch.clear();
             cc.dg_first.clear();
-            bltc::group_schedule(cc.tl_begin, cc.tl_count, cc.dn_cost, bltc::kGroupSizeSym,
+            bltc::group_schedule(cc.tl_begin, cc.tl_count, cc.dn_cost, bltc::kGroupSize,
                                  cc.prm.xcds, cc.dg_batch, cc.dg_first);
             HIP_TRY(plan->put(&dd.group_batch, cc.dg_batch, s));
             HIP_TRY(plan->put(&dd.group_first, cc.dg_first, s));
             dd.ngroups = static_cast<int64_t>(cc.dg_batch.size());
-            dd.group_threads = bltc::kGroupSizeSym;
         }
     }
     // host staging vectors die at return: finish the copies first
@@ -367,8 +362,8 @@ int view(const bltc_plan* plan, bltc_plan_view* out)
                 HIP_TRY(hipMemcpy(plan->view_src_order.data(), plan->d.src_order,
                                   cc.src.n * sizeof(int64_t), hipMemcpyDeviceToHost));
             if (cc.tgt.n > 0)
-                HIP_TRY(hipMemcpy(plan->view_tgt_order.data(), plan->ddir.tgt_orig,
-                                  cc.tgt.n * sizeof(int64_t), hipMemcpyDeviceToHost));
+                HIP_TRY(bltc_detail::copy_target_order(plan->view_tgt_order.data(), plan->ddir.tgt,
+                                                       cc.tgt.n));
         }
         out->source_order = plan->view_src_order.data();
         out->target_order = plan->view_tgt_order.data();

@@ -104,56 +104,35 @@ int create_device(bltc_plan* plan, const bltc::PlanParams& pp, int64_t nt, const
     if (mixed)
         HIP_TRY(plan->alloc(&px.src32, static_cast<size_t>(ns)));
     HIP_TRY(plan->alloc(&dd.tgt, static_cast<size_t>(nt)));
-    HIP_TRY(plan->alloc(&dd.tgt_orig, static_cast<size_t>(nt)));
     int64_t bad = -1;
-    std::string err = bltc::build_tree_device(cp.tgt, nt, tx, ty, tz, pp.leaf_size, dd.tgt_orig,
-                                              dd.tgt, nullptr, s, &bad);
-    if (bad >= 0)
-        return fail(BLTC_EINVAL, "target coordinate %lld is not finite", static_cast<long long>(bad));
-    if (!err.empty())
-        return fail(BLTC_EHIP, "device tree build: %s", err.c_str());
+    // same particles, same capacity: identical partition
+    cp.same_tree = nt == ns && tx == sx && ty == sy && tz == sz && pp.batch_size == pp.leaf_size;
+    std::string err;
+    if (!cp.same_tree) {
+        err = bltc::build_tree_device(cp.tgt, nt, tx, ty, tz, pp.leaf_size, nullptr, dd.tgt, nullptr,
+                                      s, &bad);
+        if (bad >= 0)
+            return fail(BLTC_EINVAL, "target coordinate %lld is not finite",
+                        static_cast<long long>(bad));
+        if (!err.empty())
+            return fail(BLTC_EHIP, "device tree build: %s", err.c_str());
+    }
     err = bltc::build_tree_device(cp.src, ns, sx, sy, sz, pp.batch_size, src_order, px.src,
                                   mixed ? px.src32 : nullptr, s, &bad);
     if (bad >= 0)
-        return fail(BLTC_EINVAL, "source coordinate %lld is not finite", static_cast<long long>(bad));
+        return fail(BLTC_EINVAL, "%s coordinate %lld is not finite",
+                    cp.same_tree ? "target" : "source", static_cast<long long>(bad));
     if (!err.empty())
         return fail(BLTC_EHIP, "device tree build: %s", err.c_str());
-    cp.same_arrays = nt == ns && tx == sx && ty == sy && tz == sz && pp.batch_size == pp.leaf_size;
+    if (cp.same_tree) {
+        cp.tgt = cp.src;
+        HIP_TRY(bltc::launch_copy_targets(nt, px.src, src_order, dd.tgt, s));
+    }
     bltc::cp_plan_from_trees(cp);
     plan->device_particles = true;
     cp.setup_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     return BLTC_OK;
 }
-
-namespace {
-
-bool same_nodes(const bltc::Tree& a, const bltc::Tree& b)
-{
-    return a.n == b.n && a.begin == b.begin && a.count == b.count && a.nchild == b.nchild &&
-           a.first_child == b.first_child && a.lo == b.lo && a.hi == b.hi;
-}
-
-// Both trees of a device-built plan come from the same arrays with the same
-// capacity: the build is deterministic, and this confirms it (node arrays and
-// particle orders equal) before the one-tree evaluation relies on it.
-int confirm_same_tree(bltc_plan* plan)
-{
-    bltc::CpPlan& cp = plan->cpp;
-    if (!cp.same_arrays || cp.same_tree || !same_nodes(cp.src, cp.tgt))
-        return BLTC_OK;
-    const int64_t n = cp.src.n;
-    std::vector<int64_t> a(n), b(n);
-    if (n > 0) {
-        HIP_TRY(hipMemcpy(a.data(), plan->dprox.src_order, n * sizeof(int64_t),
-                          hipMemcpyDeviceToHost));
-        HIP_TRY(hipMemcpy(b.data(), plan->ddir.tgt_orig, n * sizeof(int64_t),
-                          hipMemcpyDeviceToHost));
-    }
-    cp.same_tree = a == b;
-    return BLTC_OK;
-}
-
-}  // namespace
 
 int upload(bltc_plan* plan, hipStream_t s)
 {
@@ -176,10 +155,10 @@ int upload(bltc_plan* plan, hipStream_t s)
         for (int64_t j = 0; j < ns; ++j)
             src[j] = make_double4(cp.src.x[j], cp.src.y[j], cp.src.z[j], 0.0);
         for (int64_t i = 0; i < nt; ++i)
-            tgt[i] = make_double4(cp.tgt.x[i], cp.tgt.y[i], cp.tgt.z[i], 0.0);
+            tgt[i] = bltc_detail::target_record(cp.tgt.x[i], cp.tgt.y[i], cp.tgt.z[i],
+                                                cp.tgt.order[i]);
         HIP_TRY(plan->put(&px.src, src, s));
         HIP_TRY(plan->put(&dd.tgt, tgt, s));
-        HIP_TRY(plan->put(&dd.tgt_orig, cp.tgt.order, s));
         int64_t* src_order = nullptr;
         HIP_TRY(plan->put(&src_order, cp.src.order, s));
         px.src_order = src_order;
@@ -276,11 +255,6 @@ int upload(bltc_plan* plan, hipStream_t s)
     }
     // targets are the sources: mutual direct leaf pairs once for both directions,
     // and the target-leaf workgroups (one wave each) re-ordered by the work left
-    if (cp.same_arrays && !plan->prm.no_symmetry) {
-        int rc = plan->device_particles ? confirm_same_tree(plan) : BLTC_OK;
-        if (rc != BLTC_OK)
-            return rc;
-    }
     if (cp.same_tree && !plan->prm.no_symmetry) {
         const bltc::DirectLists dl{&cp.src,    &cp.tl_node, &cp.tl_begin, &cp.tl_count,
                                    &cp.dn_off, &cp.dn_leaf, &cp.dn_cost};
@@ -290,12 +264,11 @@ int upload(bltc_plan* plan, hipStream_t s)
         if (dd.sym) {
             cp.dg_batch.clear();
             cp.dg_first.clear();
-            bltc::group_schedule(cp.tl_begin, cp.tl_count, cp.dn_cost, bltc::kGroupSizeSym,
+            bltc::group_schedule(cp.tl_begin, cp.tl_count, cp.dn_cost, bltc::kGroupSize,
                                  cp.prm.xcds, cp.dg_batch, cp.dg_first);
             HIP_TRY(plan->put(&dd.group_batch, cp.dg_batch, s));
             HIP_TRY(plan->put(&dd.group_first, cp.dg_first, s));
             dd.ngroups = static_cast<int64_t>(cp.dg_batch.size());
-            dd.group_threads = bltc::kGroupSizeSym;
         }
     }
     // host staging vectors die at return: finish the copies first
@@ -403,8 +376,8 @@ int view(const bltc_plan* plan, bltc_plan_view* out)
                 HIP_TRY(hipMemcpy(plan->view_src_order.data(), plan->dprox.src_order,
                                   cp.src.n * sizeof(int64_t), hipMemcpyDeviceToHost));
             if (cp.tgt.n > 0)
-                HIP_TRY(hipMemcpy(plan->view_tgt_order.data(), plan->ddir.tgt_orig,
-                                  cp.tgt.n * sizeof(int64_t), hipMemcpyDeviceToHost));
+                HIP_TRY(bltc_detail::copy_target_order(plan->view_tgt_order.data(), plan->ddir.tgt,
+                                                       cp.tgt.n));
         }
         out->source_order = plan->view_src_order.data();
         out->target_order = plan->view_tgt_order.data();

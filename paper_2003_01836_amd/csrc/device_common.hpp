@@ -10,6 +10,12 @@
 namespace bltc {
 namespace dev {
 
+// caller index of a target: the bits of its record's fourth word
+__device__ __forceinline__ int64_t caller_index(const double4& t)
+{
+    return __double_as_longlong(t.w);
+}
+
 // ---------------------------------------------------------------------------
 // FP64 reciprocal square root from the hardware estimate y0 = v_rsq_f64(r2)
 // (relative error below 2^-22 on this device) and one Newton step in the form

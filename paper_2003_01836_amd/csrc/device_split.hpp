@@ -21,16 +21,6 @@ namespace dev {
 
 constexpr int kSplitBlock = 128;   // sources; = the FP32-mixed flush length
 
-// Group and 64-target sub-block of workgroup k: groups of 64 << sub_shift
-// targets, whose sub-blocks all run on the group's die (workgroup k runs on die
-// k % 8 and shares that die's L2).
-__device__ __forceinline__ int group_of_block(int k, int sub_shift, int& sub)
-{
-    const int q = k >> 3;
-    sub = q & ((1 << sub_shift) - 1);
-    return ((q >> sub_shift) << 3) | (k & 7);
-}
-
 struct ListPart {
     int32_t plane0, plane1;   // planes f (n+1) + k1 of the batch's far list
     int32_t entry;            // first direct entry, the block it starts with,

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstdarg>
 #include <cstdio>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -64,6 +65,21 @@ hipError_t upload(T** dst, const std::vector<T>& v, hipStream_t s)
     if (!v.empty())
         e = hipMemcpyAsync(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
     return e;
+}
+
+// device record of a target: position, and its caller index in the fourth word
+inline double4 target_record(double x, double y, double z, int64_t index)
+{
+    double w;
+    std::memcpy(&w, &index, sizeof(w));
+    return make_double4(x, y, z, w);
+}
+
+// the caller indices of n target records on the device
+inline hipError_t copy_target_order(int64_t* out, const double4* tgt, int64_t n)
+{
+    return hipMemcpy2D(out, sizeof(int64_t), &tgt->w, sizeof(double4), sizeof(int64_t),
+                       static_cast<size_t>(n), hipMemcpyDeviceToHost);
 }
 
 }  // namespace bltc_detail

@@ -70,8 +70,7 @@ __device__ __forceinline__ double far_sum_f64(double x, double y, double z,
 // ---------------------------------------------------------------------------
 template <int N, int KER>
 __global__ __launch_bounds__(64 * kMaxWaves) void interact_f64(
-    int32_t ngroups, int32_t sub_shift, int32_t log_w,
-    const double4* __restrict__ tgt, const int64_t* __restrict__ tgt_orig,
+    int32_t log_w, const double4* __restrict__ tgt,
     const double4* __restrict__ src, const int32_t* __restrict__ group_batch,
     const int64_t* __restrict__ group_first, const int64_t* __restrict__ batch_end,
     const int32_t* __restrict__ far_off, const int32_t* __restrict__ far_slot,
@@ -89,15 +88,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void interact_f64(
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg kappa{kc.kappa, kc.delta2, exp_tab};
-    int sub;
-    const int g = group_of_block(blockIdx.x, sub_shift, sub);
-    const int b = g < ngroups ? group_batch[g] : -1;
+    const int g = blockIdx.x;
+    const int b = group_batch[g];
     if (b < 0)
         return;  // empty slot of the per-die schedule
-    const int64_t first = group_first[g] + 64 * sub;
+    const int64_t first = group_first[g];
     const int64_t end = batch_end[b];
-    if (first >= end)
-        return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     int64_t i = first + lane;
@@ -130,7 +126,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void interact_f64(
     }
     acc = sum_waves(acc, w, log_w, lds);
     if (w == 0 && valid)
-        phi[tgt_orig[i]] = acc;
+        phi[caller_index(t)] = acc;
 }
 
 __global__ __launch_bounds__(256) void gather_charges(double4* __restrict__ src,
@@ -266,8 +262,7 @@ hipError_t run_interact(const DevicePlan& d, double* phi, KernelConst kc, hipStr
     const GroupLaunch gl = group_launch(d);
     hipLaunchKernelGGL((interact_f64<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w),
                        gl.log_w ? sizeof(double) * (64u << gl.log_w) : 0, s,
-                       static_cast<int32_t>(d.ngroups), gl.sub_shift, gl.log_w, d.tgt, d.tgt_orig,
-                       d.src, d.group_batch,
+                       gl.log_w, d.tgt, d.src, d.group_batch,
                        d.group_first, d.batch_end, d.far_off, d.far_slot, nl.off, nl.begin,
                        nl.count, d.slot_nodes, d.qhat, nl.pc_off, nl.pc_base, nl.pair_out,
                        nl.batch_begin, phi, kc);

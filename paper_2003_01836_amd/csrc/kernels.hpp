@@ -9,8 +9,12 @@ namespace bltc {
 
 constexpr int kMaxDegree = 16;
 constexpr int kMaxHermiteDegree = 10;   // Hermite treecode: 8 (n+1)^3 charges per cluster
-constexpr int kGroupSize = 256;      // targets of a group of the schedule
-constexpr int kGroupSizeSym = 64;    // the same for one-vector plans (finer tail)
+// Targets of an interaction workgroup, one per lane of each of its waves.  No
+// workgroup of a launch is empty but a few at the end of a die's queue: a
+// schedule of 256-target groups with a workgroup per 64 of them left a regular
+// pattern of empty ones, which put 4 to 64 waves on a CU (even: 36 to 44) and
+// a third of the CUs idle.
+constexpr int kGroupSize = 64;
 constexpr int kMaxWaves = 16;        // waves of an interaction workgroup
 
 // The direct lists the single-vector interaction kernels walk: the plan's own,
@@ -48,9 +52,8 @@ struct DevicePlan {
     int64_t nt = 0, ns = 0, nslots = 0, nchunks = 0, ngroups = 0, nbatches = 0;
     // sources in tree order: x, y, z, charge of the current vector
     double4* src = nullptr;
-    // targets in batch order: x, y, z, unused
+    // targets in batch order: x, y, z, caller index (int64 bits)
     double4* tgt = nullptr;
-    int64_t* tgt_orig = nullptr;      // caller index of each batch position
     const int64_t* src_order = nullptr; // caller index of each tree position
     // FP32-mixed path: sources relative to the center of their leaf
     float4* src32 = nullptr;          // x - c_x, y - c_y, z - c_z, q (tree order)
@@ -90,9 +93,6 @@ struct DevicePlan {
     // lists and add, per target, the unit results listed in sym_pc_*
     int32_t sym = 0;
     int64_t sym_units = 0;            // sub-units
-    // targets per group of the schedule (kGroupSize or kGroupSizeSym); the
-    // single-vector interaction kernels take 64 of them per workgroup
-    int32_t group_threads = 256;
     // lanes per target asked for (waves of an interaction workgroup, at least)
     int32_t threads_per_target = 1;
     SymUnit* sym_unit = nullptr;
@@ -112,8 +112,8 @@ struct DevicePlan {
     double* sym_acc = nullptr;
 };
 
-// Launch of a single-vector interaction kernel: workgroups of 64 targets,
-// 1 << sub_shift per group of the schedule, 1 << log_w waves each.
+// Launch of a single-vector interaction kernel: a workgroup of 1 << log_w waves
+// per group of the schedule.
 //
 // Waves per workgroup: a target's lists are one serial chain per lane, so a
 // problem of few targets leaves the chip (1024 SIMDs, up to 8 waves each) idle,
@@ -127,13 +127,11 @@ constexpr int64_t kWavesWanted = 32768;
 constexpr int64_t kWavesFew = 4096;
 struct GroupLaunch {
     uint32_t blocks;
-    int32_t sub_shift, log_w;
+    int32_t log_w;
 };
 inline GroupLaunch group_launch(const DevicePlan& d, int max_waves = kMaxWaves)
 {
-    GroupLaunch g{0, d.group_threads == kGroupSizeSym ? 0 : 2, 0};
-    const int64_t padded = (d.ngroups + 7) / 8 * 8;
-    g.blocks = static_cast<uint32_t>(padded << g.sub_shift);
+    GroupLaunch g{static_cast<uint32_t>(d.ngroups), 0};
     const int64_t targets = (d.nt + 63) / 64;
     while ((2 << g.log_w) <= max_waves &&
            ((1 << g.log_w) < d.threads_per_target ||
@@ -153,7 +151,6 @@ struct KernelConst {
 // to a kernel, or as an array for the work-queue kernel).
 struct MrhsDesc {
     const double4* tgt;
-    const int64_t* tgt_orig;
     const double4* src;
     const float4* src32;
     const double* qm;

@@ -11,7 +11,7 @@
 //           = (sum_k a_1k1 a_2k2 a_3k3 phihat_k) / (D_1 D_2 D_3),
 // with a_lk = w_k / (x_l - t_lk) and D_l = sum_k a_lk, or a one-hot row and
 // D_l = 1 when x_l is within DBL_MIN of a node (eq. 5; the lowest such k).
-// One target per lane, 256 targets of one target leaf per workgroup; the
+// One target per lane, 64 targets of one target leaf per workgroup; the
 // cluster grids and proxy potentials are wave-uniform (scalar loads).
 #include <cfloat>
 
@@ -50,8 +50,7 @@ __device__ __forceinline__ double interp_factors(double x, const double* __restr
 
 template <int N>
 __global__ __launch_bounds__(kGroupSize) void interpolate_targets(
-    const double4* __restrict__ tgt, const int64_t* __restrict__ tgt_orig,
-    const int32_t* __restrict__ group_batch, const int64_t* __restrict__ group_first,
+    const double4* __restrict__ tgt, const int32_t* __restrict__ group_batch, const int64_t* __restrict__ group_first,
     const int64_t* __restrict__ batch_end, const int32_t* __restrict__ path_off,
     const int32_t* __restrict__ path_slot, const double* __restrict__ slot_nodes,
     const double* __restrict__ phat, double* __restrict__ phi)
@@ -64,8 +63,6 @@ __global__ __launch_bounds__(kGroupSize) void interpolate_targets(
         return;
     const int64_t first = group_first[g];
     const int64_t end = batch_end[b];
-    if (first + (threadIdx.x & ~63) >= end)
-        return;
     int64_t i = first + threadIdx.x;
     const bool valid = i < end;
     if (!valid)
@@ -97,7 +94,7 @@ __global__ __launch_bounds__(kGroupSize) void interpolate_targets(
         acc += s / D;
     }
     if (valid)
-        phi[tgt_orig[i]] += acc;
+        phi[caller_index(t)] += acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -305,8 +302,8 @@ hipError_t launch_interpolate_targets(const DevicePlan& d, const int32_t* path_o
     switch (d.degree) {
 #define X(n)                                                                                  \
     case n:                                                                                   \
-        hipLaunchKernelGGL(interpolate_targets<n>, grid, dim3(d.group_threads), 0, s, d.tgt,  \
-                           d.tgt_orig, d.group_batch, d.group_first, d.batch_end, path_off,   \
+        hipLaunchKernelGGL(interpolate_targets<n>, grid, dim3(kGroupSize), 0, s, d.tgt,       \
+                           d.group_batch, d.group_first, d.batch_end, path_off,   \
                            path_slot, slot_nodes, phat, phi);                                 \
         return hipGetLastError();
         BLTC_DEGREE_CASES(X)

@@ -7,7 +7,7 @@
 
 namespace bltc {
 
-// phi[tgt_orig[i]] += the interpolant of the proxy potentials phat[slot][P] of
+// phi[caller index of i] += the interpolant of the proxy potentials phat[slot][P] of
 // every slot listed for the target's leaf (path_off/path_slot per batch of d),
 // grids slot_nodes[slot][3][n+1] (kernels_cp.hip)
 hipError_t launch_interpolate_targets(const DevicePlan& d, const int32_t* path_off,

@@ -114,8 +114,7 @@ __device__ __forceinline__ double far_sum_hermite(double x, double y, double z,
 
 template <int N, int KER>
 __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_f64(
-    int32_t ngroups, int32_t sub_shift, int32_t log_w,
-    const double4* __restrict__ tgt, const int64_t* __restrict__ tgt_orig,
+    int32_t log_w, const double4* __restrict__ tgt,
     const double4* __restrict__ src, const int32_t* __restrict__ group_batch,
     const int64_t* __restrict__ group_first, const int64_t* __restrict__ batch_end,
     const int32_t* __restrict__ far_off, const int32_t* __restrict__ far_slot,
@@ -133,15 +132,12 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_f64(
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg ka{kc.kappa, kc.delta2, exp_tab};
-    int sub;
-    const int g = group_of_block(blockIdx.x, sub_shift, sub);
-    const int b = g < ngroups ? group_batch[g] : -1;
+    const int g = blockIdx.x;
+    const int b = group_batch[g];
     if (b < 0)
         return;  // empty slot of the per-die schedule
-    const int64_t first = group_first[g] + 64 * sub;
+    const int64_t first = group_first[g];
     const int64_t end = batch_end[b];
-    if (first >= end)
-        return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     int64_t i = first + lane;
@@ -175,7 +171,7 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_f64(
     }
     acc = sum_waves(acc, w, log_w, lds);
     if (w == 0 && valid)
-        phi[tgt_orig[i]] = acc;
+        phi[caller_index(t)] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -270,8 +266,7 @@ constexpr bool kStageHermite = N == 4;
 
 template <int N, int KER>
 __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_mixed(
-    int32_t ngroups, int32_t sub_shift, int32_t log_w,
-    const double4* __restrict__ tgt, const int64_t* __restrict__ tgt_orig,
+    int32_t log_w, const double4* __restrict__ tgt,
     const double4* __restrict__ src, const float4* __restrict__ src32,
     const double4* __restrict__ node_info, const double4* __restrict__ batch_info,
     const int32_t* __restrict__ group_batch, const int64_t* __restrict__ group_first,
@@ -293,15 +288,12 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_mixed(
     const KernelArg ka{kc.kappa, kc.delta2, exp_tab};
     const KernelArg32 nk = kernel_arg32(kc.kappa, kc.delta2);
     const float kf = static_cast<float>(kc.kappa);
-    int sub;
-    const int g = group_of_block(blockIdx.x, sub_shift, sub);
-    const int b = g < ngroups ? group_batch[g] : -1;
+    const int g = blockIdx.x;
+    const int b = group_batch[g];
     if (b < 0)
         return;  // empty slot of the per-die schedule
-    const int64_t first = group_first[g] + 64 * sub;
+    const int64_t first = group_first[g];
     const int64_t end = batch_end[b];
-    if (first >= end)
-        return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     int64_t i = first + lane;
@@ -350,7 +342,7 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_mixed(
     }
     acc = sum_waves(acc, w, log_w, lds);
     if (w == 0 && valid)
-        phi[tgt_orig[i]] = acc;
+        phi[caller_index(t)] = acc;
 }
 
 template <int N, int KER>
@@ -364,8 +356,7 @@ hipError_t run_interact_hermite_mixed(const DevicePlan& d, double* phi, KernelCo
     const size_t stage = kStageHermite<N> ? sizeof(float) * 8 * (N + 1) * (N + 1) * (N + 1) : 0;
     const size_t lds = std::max(stage, gl.log_w ? 64 * sizeof(double) : size_t(0)) << gl.log_w;
     hipLaunchKernelGGL((interact_hermite_mixed<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w), lds,
-                       s, static_cast<int32_t>(d.ngroups), gl.sub_shift, gl.log_w, d.tgt, d.tgt_orig,
-                       d.src, d.src32,
+                       s, gl.log_w, d.tgt, d.src, d.src32,
                        d.node_info, d.batch_info, d.group_batch, d.group_first, d.batch_end,
                        d.far_off, d.far_slot, nl.off, nl.begin, nl.count, nl.leaf, d.slot_nodes,
                        d.qhat32, nl.pc_off, nl.pc_base, nl.pair_out, nl.batch_begin, phi, kc);
@@ -381,8 +372,7 @@ hipError_t run_interact_hermite(const DevicePlan& d, double* phi, KernelConst kc
     const GroupLaunch gl = group_launch(d, kHermiteWaves);
     hipLaunchKernelGGL((interact_hermite_f64<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w),
                        gl.log_w ? sizeof(double) * (64u << gl.log_w) : 0, s,
-                       static_cast<int32_t>(d.ngroups), gl.sub_shift, gl.log_w, d.tgt, d.tgt_orig,
-                       d.src, d.group_batch,
+                       gl.log_w, d.tgt, d.src, d.group_batch,
                        d.group_first, d.batch_end, d.far_off, d.far_slot, nl.off, nl.begin,
                        nl.count, d.slot_nodes, d.qhat_h, nl.pc_off, nl.pc_base, nl.pair_out,
                        nl.batch_begin, phi, kc);

@@ -71,8 +71,7 @@ constexpr bool kStageCharges = N <= 10;
 // allocation allows
 template <int N, int KER>
 __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(8, 8))) void interact_mixed(
-    int32_t ngroups, int32_t sub_shift, int32_t log_w,
-    const double4* __restrict__ tgt, const int64_t* __restrict__ tgt_orig,
+    int32_t log_w, const double4* __restrict__ tgt,
     const double4* __restrict__ src, const float4* __restrict__ src32,
     const double4* __restrict__ node_info, const double4* __restrict__ batch_info,
     const int32_t* __restrict__ group_batch, const int64_t* __restrict__ group_first,
@@ -92,15 +91,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg kappa{kc.kappa, kc.delta2, exp_tab};
-    int sub;
-    const int g = group_of_block(blockIdx.x, sub_shift, sub);
-    const int b = g < ngroups ? group_batch[g] : -1;
+    const int g = blockIdx.x;
+    const int b = group_batch[g];
     if (b < 0)
         return;  // empty slot of the per-die schedule
-    const int64_t first = group_first[g] + 64 * sub;
+    const int64_t first = group_first[g];
     const int64_t end = batch_end[b];
-    if (first >= end)
-        return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     int64_t i = first + lane;
@@ -149,7 +145,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     }
     acc = sum_waves(acc, w, log_w, lds);
     if (w == 0 && valid)
-        phi[tgt_orig[i]] = acc;
+        phi[caller_index(t)] = acc;
 }
 
 template <int N, int KER>
@@ -164,8 +160,7 @@ hipError_t run_interact_mixed(const DevicePlan& d, double* phi, KernelConst kc, 
     const GroupLaunch gl = group_launch(d, max_waves);
     const size_t lds = std::max(stage, gl.log_w ? 64 * sizeof(double) : size_t(0)) << gl.log_w;
     hipLaunchKernelGGL((interact_mixed<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w), lds, s,
-                       static_cast<int32_t>(d.ngroups), gl.sub_shift, gl.log_w, d.tgt, d.tgt_orig,
-                       d.src, d.src32, d.node_info,
+                       gl.log_w, d.tgt, d.src, d.src32, d.node_info,
                        d.batch_info, d.group_batch, d.group_first, d.batch_end, d.far_off,
                        d.far_slot, nl.off, nl.begin, nl.count, nl.leaf, d.slot_nodes, d.qhat32,
                        nl.pc_off, nl.pc_base, nl.pair_out, nl.batch_begin, phi, kc);

@@ -3,8 +3,8 @@
 //
 // The kernel values G(x_i, y_j) do not depend on the charge vector, so a pair
 // is evaluated once and contracted with all right-hand sides on the matrix
-// cores:  Phi[i][m] += sum_j G[i][j] Q[j][m].  A wave owns 64 targets of one
-// batch as four 16-target tiles.  Per step of 4 sources (or proxy points),
+// cores:  Phi[i][m] += sum_j G[i][j] Q[j][m].  A wave (a workgroup) owns 64 targets
+// of one batch as four 16-target tiles.  Per step of 4 sources (or proxy points),
 // lane l evaluates G for target row (l % 16) of each tile and source column
 // (l / 16) on the VALU -- exactly the MFMA A-operand layout -- and loads
 // Q[source l/16][rhs l%16] -- the B-operand layout -- so the G tile goes
@@ -121,7 +121,6 @@ template <int KER>
 __device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, const double* exp_tab)
 {
     const double4* __restrict__ tgt = d.tgt;
-    const int64_t* __restrict__ tgt_orig = d.tgt_orig;
     const double4* __restrict__ src = d.src;
     const double* __restrict__ qm = d.qm;
     const int32_t* __restrict__ far_off = d.far_off;
@@ -141,17 +140,14 @@ __device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, const d
         return;
     const int64_t first = gload<int64_t>(d.group_first + g);
     const int64_t end = gload<int64_t>(d.batch_end + b);
-    const int64_t wave_first = first + (threadIdx.x & ~63);
-    if (wave_first >= end)
-        return;
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x;
     const int row = lane & 15;
     const int col = lane >> 4;
 
     double tx[4], ty[4], tz[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        int64_t i = wave_first + 16 * t + row;
+        int64_t i = first + 16 * t + row;
         i = i < end ? i : end - 1;
         const d3v v = gload<d3v>(tgt + i);
         tx[t] = v.x;
@@ -257,9 +253,9 @@ __device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, const d
         for (int t = 0; t < 4; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t i = wave_first + 16 * t + 4 * r + col;
+                const int64_t i = first + 16 * t + 4 * r + col;
                 if (i < end)   // the kernel values were doubled (green_*2_f64)
-                    gstore(phi + row * phi_ld + gload<int64_t>(tgt_orig + i), 0.5 * acc[t][r]);
+                    gstore(phi + row * phi_ld + gload<int64_t>(&tgt[i].w), 0.5 * acc[t][r]);
             }
     }
 }
@@ -285,7 +281,6 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
                                                  double* __restrict__ tl)
 {
     const double4* __restrict__ tgt = d.tgt;
-    const int64_t* __restrict__ tgt_orig = d.tgt_orig;
     const double4* __restrict__ src = d.src;
     const float4* __restrict__ src32 = d.src32;
     const float* __restrict__ qm32 = d.qm32;
@@ -310,10 +305,7 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
         return;
     const int64_t first = gload<int64_t>(d.group_first + g);
     const int64_t end = gload<int64_t>(d.batch_end + b);
-    const int64_t wave_first = first + (threadIdx.x & ~63);
-    if (wave_first >= end)
-        return;
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x;
     const int row = lane & 15;
     const int col = lane >> 4;
     const KernelArg32 nk = kernel_arg32(d.kc.kappa, d.kc.delta2);
@@ -329,7 +321,7 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
     };
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        int64_t i = wave_first + 16 * t + row;
+        int64_t i = first + 16 * t + row;
         i = i < end ? i : end - 1;
         const d3v v = gload<d3v>(tgt + i);
         tc(t, 0) = v.x;
@@ -487,9 +479,9 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
         for (int t = 0; t < 4; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t i = wave_first + 16 * t + 4 * col + r;
+                const int64_t i = first + 16 * t + 4 * col + r;
                 if (i < end)
-                    gstore(phi + row * phi_ld + gload<int64_t>(tgt_orig + i), acc[t][r]);
+                    gstore(phi + row * phi_ld + gload<int64_t>(&tgt[i].w), acc[t][r]);
             }
     }
 }
@@ -586,7 +578,6 @@ MrhsDesc make_mrhs_desc(const DevicePlan& d, const KernelParams& kp, double* phi
 {
     MrhsDesc m;
     m.tgt = d.tgt;
-    m.tgt_orig = d.tgt_orig;
     m.src = d.src;
     m.src32 = d.src32;
     m.qm = d.qm;

@@ -868,7 +868,7 @@ void make_cp_plan(CpPlan& cp, const PlanParams& prm,
     build_tree(cp.tgt, nt, tx, ty, tz, prm.leaf_size);
     if (nt == ns && tx == sx && ty == sy && tz == sz && prm.batch_size == prm.leaf_size) {
         cp.src = cp.tgt;
-        cp.same_arrays = cp.same_tree = true;
+        cp.same_tree = true;
     } else
         build_tree(cp.src, ns, sx, sy, sz, prm.batch_size);
     cp_plan_from_trees(cp);

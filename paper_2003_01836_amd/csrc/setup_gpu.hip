@@ -340,12 +340,26 @@ finish_points(const FinalChunk* __restrict__ chunks, Sets sets, int64_t* __restr
     for (int i = threadIdx.x; i < c.count; i += kThreads) {
         const int64_t p = c.begin + i;
         const double vx = x[p], vy = y[p], vz = z[p];
-        order[p] = o[p];
-        pos[p] = make_double4(vx, vy, vz, 0.0);
+        if (order)
+            order[p] = o[p];
+        // targets (no order array): the caller index in the fourth word
+        pos[p] = make_double4(vx, vy, vz,
+                              order ? 0.0 : __longlong_as_double(static_cast<int64_t>(o[p])));
         if (rel)
             rel[p] = make_float4(static_cast<float>(vx - c.ctr[0]), static_cast<float>(vy - c.ctr[1]),
                                  static_cast<float>(vz - c.ctr[2]), 0.0f);
     }
+}
+
+__global__ void __launch_bounds__(kThreads)
+copy_targets(int64_t n, const double4* __restrict__ src, const int64_t* __restrict__ order,
+             double4* __restrict__ tgt)
+{
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+    if (i >= n)
+        return;
+    const double4 p = src[i];
+    tgt[i] = make_double4(p.x, p.y, p.z, __longlong_as_double(order[i]));
 }
 
 // device buffer that grows on demand (the stream is idle whenever it grows)
@@ -389,6 +403,16 @@ struct Buf {
     } while (0)
 
 }  // namespace
+
+hipError_t launch_copy_targets(int64_t n, const double4* src, const int64_t* order, double4* tgt,
+                               hipStream_t s)
+{
+    if (n == 0)
+        return hipSuccess;
+    copy_targets<<<static_cast<uint32_t>((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(n, src,
+                                                                                          order, tgt);
+    return hipGetLastError();
+}
 
 std::string build_tree_device(Tree& t, int64_t n, const double* x, const double* y,
                               const double* z, int64_t cap, int64_t* order, double4* pos,

@@ -16,13 +16,19 @@ namespace bltc {
 // leaf capacity cap.  The node arrays of t are filled on the host and equal
 // those of build_tree(); t.order, t.x, t.y, t.z stay empty.  Device outputs
 // (n entries each, tree order): order[p] = caller index of tree position p,
-// pos[p] = (x, y, z, 0), and when rel is not NULL the FP32 coordinates
+// pos[p] = (x, y, z, 0) -- with order NULL (targets) the caller index is the
+// fourth word of pos[p] -- and when rel is not NULL the FP32 coordinates
 // relative to the center of the leaf holding p.  The stream is synchronised
 // before return.  Returns an empty string on success; a non-finite coordinate
 // sets *bad_index to the lowest such caller index.
 std::string build_tree_device(Tree& t, int64_t n, const double* x, const double* y,
                               const double* z, int64_t cap, int64_t* order, double4* pos,
                               float4* rel, hipStream_t s, int64_t* bad_index);
+
+// Target records of the sources' own tree: the position of every source record
+// with its caller index order[p] in the fourth word.
+hipError_t launch_copy_targets(int64_t n, const double4* src, const int64_t* order, double4* tgt,
+                               hipStream_t s);
 
 // Interaction lists on the device, in the host planner's layout and order.
 struct DeviceLists {
