@@ -74,6 +74,7 @@ def build(verbose: bool = False, defines=(), lib_path: str = LIB, build_dir: str
         "kernels_cp": os.path.join(build_dir, "kernels_cp.o"),
         "kernels_hermite": os.path.join(build_dir, "kernels_hermite.o"),
         "kernels_sym": os.path.join(build_dir, "kernels_sym.o"),
+        "kernels_multi": os.path.join(build_dir, "kernels_multi.o"),
         "noalloc": os.path.join(build_dir, "noalloc.o"),
     }
     cmds = [
@@ -97,6 +98,8 @@ def build(verbose: bool = False, defines=(), lib_path: str = LIB, build_dir: str
                                objs["kernels_hermite"]],
         [hipcc] + hip_flags + ["-c", os.path.join(CSRC, "kernels_sym.hip"), "-o",
                                objs["kernels_sym"]],
+        [hipcc] + hip_flags + ["-c", os.path.join(CSRC, "kernels_multi.hip"), "-o",
+                               objs["kernels_multi"]],
         [hipcc] + hip_flags + ["-c", os.path.join(CSRC, "noalloc.hip"), "-o", objs["noalloc"]],
     ]
     if verbose:

@@ -65,7 +65,7 @@ int enqueue(bltc_batch* b, const double* const* q, const int32_t* num_q, const i
     const int32_t count = static_cast<int32_t>(b->plans.size());
     for (int32_t i = 0; i < count; ++i) {
         const bltc::DevicePlan& d = b->plans[i]->d;
-        HIP_TRY(bltc::launch_gather_charges16(d, q[i], q_ld[i], num_q[i], s));
+        HIP_TRY(bltc::launch_gather_charges_multi(d, q[i], q_ld[i], num_q[i], 16, s));
     }
     if (b->multi_np > 0)
         HIP_TRY(bltc::launch_upward_many_multi(b->d_updescs, b->d_upunits, b->nupunits,
@@ -236,8 +236,10 @@ int batch_execute(bltc_batch* b, const double* const* q, const int32_t* num_q,
             b->exec = nullptr;
         }
         b->key = key;
-        for (int32_t i = 0; i < count; ++i)
-            b->plans[i]->last_q = num_q[i];
+    }
+    for (int32_t i = 0; i < count; ++i) {
+        b->plans[i]->last_q = num_q[i];
+        b->plans[i]->last_ld = 16;
     }
     if (!b->use_graph) {
         ++b->launches;

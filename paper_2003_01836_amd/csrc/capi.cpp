@@ -285,7 +285,8 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
     // modified charges (first nslots rows) and the partial rows of multi-chunk
     // clusters; [row][P] for one charge vector, [row][P][16] for several
     const size_t mw_max = plan->max_q > 1 ? 16 : 1;
-    HIP_TRY(plan->alloc(&d.qhat, static_cast<size_t>(d.nslots + hp.npartial) * hp.P * mw_max));
+    d.qhat_rows = d.nslots + hp.npartial;
+    HIP_TRY(plan->alloc(&d.qhat, static_cast<size_t>(d.qhat_rows) * hp.P * mw_max));
     if (d.hermite)
         HIP_TRY(plan->alloc(&d.qhat_h, static_cast<size_t>(d.nslots) * hp.P));
     const bool mixed = plan->prm.precision == BLTC_FP32_MIXED;
@@ -522,12 +523,17 @@ int execute(bltc_plan* plan, const double* q, int32_t num_q, int64_t q_ld, doubl
             const int32_t m0 = 16 * u;
             const int32_t mc = std::min<int32_t>(16, num_q - m0);
             HIP_TRY(mark(u, 0));
-            HIP_TRY(bltc::launch_gather_charges16(d, q + static_cast<int64_t>(m0) * q_ld, q_ld, mc, s));
+            const int32_t ld = bltc::multi_ld(kp.precision, d.degree, mc);
+            HIP_TRY(bltc::launch_gather_charges_multi(d, q + static_cast<int64_t>(m0) * q_ld, q_ld,
+                                                      mc, ld, s));
             HIP_TRY(mark(u, 1));
-            HIP_TRY(bltc::launch_upward_mfma(d, 16, d.qhat16, d.qhat16f, s));
+            HIP_TRY(bltc::launch_upward_mfma(d, ld, d.qhat16, d.qhat16f, s));
             HIP_TRY(mark(u, 2));
-            HIP_TRY(bltc::launch_interact_mrhs(d, kp, phi + static_cast<int64_t>(m0) * phi_ld, phi_ld,
-                                               mc, s));
+            double* const phi0 = phi + static_cast<int64_t>(m0) * phi_ld;
+            plan->last_ld = ld;
+            HIP_TRY(kp.precision == BLTC_FP64 && d.degree <= bltc::kMultiMaxDegree
+                        ? bltc::launch_interact_multi(d, kp, phi0, phi_ld, mc, s)
+                        : bltc::launch_interact_mrhs(d, kp, phi0, phi_ld, mc, s));
             HIP_TRY(mark(u, 3));
         }
     }
@@ -1009,19 +1015,20 @@ int bltc_plan_modified_charges(bltc_plan* plan, int64_t cluster, int32_t qi, dou
                     static_cast<long long>(cluster));
     if (!plan->uploaded || plan->last_q == 0)
         return fail(BLTC_EINVAL, "plan has not been executed");
-    // one vector: qhat[slot][k]; several: the last pass of 16, qhat16[slot][k][m]
+    // one vector: qhat[slot][k]; several: the last pass of up to 16, qhat16[slot][k][ld]
     const int32_t m0 = plan->last_q == 1 ? 0 : 16 * ((plan->last_q - 1) / 16);
     if (qi < m0 || qi >= plan->last_q)
         return fail(BLTC_EINVAL, "charge vector %d is not in the last execution's last pass", qi);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    std::vector<double> buf(plan->last_q == 1 ? hp.P : hp.P * 16);
+    const int32_t ld = plan->last_q == 1 ? 1 : plan->last_ld;
+    std::vector<double> buf(hp.P * ld);
     // Hermite: the charges regrouped per grid point, [slot][k][a]
     const double* src = (plan->d.hermite ? plan->d.qhat_h : plan->d.qhat) +
                         static_cast<int64_t>(slot) * static_cast<int64_t>(buf.size());
     HIP_TRY(hipMemcpyAsync(buf.data(), src, buf.size() * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     for (int64_t k = 0; k < hp.P; ++k)
-        out[k] = plan->last_q == 1 ? buf[k] : buf[k * 16 + (qi - m0)];
+        out[k] = buf[k * ld + (plan->last_q == 1 ? 0 : qi - m0)];
     return BLTC_OK;
 }
 

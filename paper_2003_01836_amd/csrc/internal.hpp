@@ -134,6 +134,7 @@ struct bltc_plan {
     std::vector<void*> allocations;
     bool timing = false;
     int32_t last_q = 0;                  // charge vectors of the last execution
+    int32_t last_ld = 16;                // and the row length of its last pass's charges
     int32_t timed_q = 0;                 // charge vectors covered by the recorded events
     int64_t sym_pair_evals = 0;          // kernel values of the mutual leaf pairs (each serving
                                          // two direct terms), once uploaded

@@ -77,6 +77,7 @@ struct DevicePlan {
     int32_t* slot_chunk_off = nullptr;
     int64_t* chunk_dst = nullptr;     // output row of each chunk (slot, or nslots + partial)
     double* qhat = nullptr;           // [slot][P] or [slot][P][16], then partial rows
+    int64_t qhat_rows = 0;            // nslots + partial rows
     float* qhat32 = nullptr;          // [slot][P] (mixed precision; Hermite [slot][(n+1)^3][8])
     // several charge vectors at once (16 per pass)
     int32_t* slot_cluster = nullptr;  // cluster id of each slot
@@ -189,7 +190,8 @@ struct KernelParams {
 // src[j].w = q[order[j]] (and src32[j].w when present), j < ns: charges into tree order
 hipError_t launch_gather_charges(const DevicePlan& d, const double* q, hipStream_t s);
 // upward pass, eqs. 14-15, on the matrix cores (kernels_upward.hip): mw = 1 (charges in
-// src[j].w, result buf[slot][k]) or 16 (charges in qm, result buf[slot][k][16]);
+// src[j].w, result buf[slot][k]) or 2, 4, 8 (FP64), 16 (charges in qm[ns][mw], result
+// buf[slot][k][mw]);
 // buf holds nslots final rows followed by the partial rows of multi-chunk slots
 hipError_t launch_upward_mfma(const DevicePlan& d, int32_t mw, double* buf, float* qhat32,
                               hipStream_t s);
@@ -218,7 +220,7 @@ bool upward_many_multi(int32_t np, int32_t mw);
 hipError_t launch_upward_many_multi(const UpwardDesc* descs, const int2* units, int32_t nunits,
                                     int32_t np, bool f32, hipStream_t s);
 hipError_t launch_upward_reduce(const DevicePlan& d, int32_t mw, double* buf, float* qhat32,
-                                hipStream_t s);
+                                hipStream_t s, int32_t ranges = 1);
 // (with d.hermite the upward pass forms 8 (n+1)^3 charges per slot and the
 // reduction writes them to d.qhat_h, [slot][k][a], and their FP32 copy to
 // qhat32 when given; mw must be 1)
@@ -263,13 +265,27 @@ hipError_t launch_interact(const DevicePlan& d, const KernelParams& kp, double* 
 // the same in FP32-mixed arithmetic (kernels_mixed.hip)
 hipError_t launch_interact_mixed(const DevicePlan& d, const KernelParams& kp, double* phi,
                                  hipStream_t s);
-// several charge vectors (kernels_mrhs.hip): charges of vectors m0..m0+mc-1
-// into qm/qm32 (tree order, zero padded to 16), and the interactions of all
-// mc vectors: phi[m * phi_ld + i], m < mc
-hipError_t launch_gather_charges16(const DevicePlan& d, const double* q, int64_t q_ld, int32_t mc,
-                                   hipStream_t s);
+// several charge vectors: mc of them at a time, mc <= 16, in tree order in
+// d.qm/d.qm32 ([ns][ld], zero padded), their modified charges in d.qhat16
+// ([slot][P][ld]); ld = multi_ld(precision, mc).  phi[m * phi_ld + i], m < mc.
+//
+// FP64 passes with n <= 15 run on the vector units, a grid line of n + 1 <= 16
+// points per row of lanes, their charges packed to the next of 2, 4, 8, 16 a
+// source (2 vectors take 4.8 ms where 16 take 11.4, kernels_multi.hip); FP32-mixed
+// passes and n = 16 run on the matrix cores, whose tiles have 16 columns.
+constexpr int32_t kMultiMaxDegree = 15;
+inline int32_t multi_ld(int32_t precision, int32_t degree, int32_t mc)
+{
+    return precision == 0 && degree <= kMultiMaxDegree && mc <= 8 ? (mc <= 2 ? 2 : mc <= 4 ? 4 : 8) : 16;
+}
+hipError_t launch_gather_charges_multi(const DevicePlan& d, const double* q, int64_t q_ld,
+                                       int32_t mc, int32_t ld, hipStream_t s);
+// on the matrix cores, ld = 16 (kernels_mrhs.hip)
 hipError_t launch_interact_mrhs(const DevicePlan& d, const KernelParams& kp, double* phi,
                                 int64_t phi_ld, int32_t mc, hipStream_t s);
+// in FP64 on the vector units, n <= kMultiMaxDegree (kernels_multi.hip)
+hipError_t launch_interact_multi(const DevicePlan& d, const KernelParams& kp, double* phi,
+                                 int64_t phi_ld, int32_t mc, hipStream_t s);
 MrhsDesc make_mrhs_desc(const DevicePlan& d, const KernelParams& kp, double* phi, int64_t phi_ld,
                         int32_t mc);
 // work queue over (system, group) units of many systems; counter reset first

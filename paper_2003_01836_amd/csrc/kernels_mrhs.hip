@@ -541,19 +541,20 @@ __global__ void reset_counter(int32_t* counter)
         counter[0] = 0;
 }
 
-// charges of up to 16 vectors into tree order, padded with zeros:
-// qm[j][m] = q[(m0 + m) * q_ld + order[j]] for m < mc
-__global__ __launch_bounds__(256) void gather_charges16(double* __restrict__ qm,
-                                                        float* __restrict__ qm32,
-                                                        const int64_t* __restrict__ order,
-                                                        const double* __restrict__ q, int64_t q_ld,
-                                                        int32_t mc, int64_t ns)
+// charges of mc <= 1 << log_ld vectors into tree order, padded with zeros:
+// qm[j][m] = q[m * q_ld + order[j]] for m < mc
+__global__ __launch_bounds__(256) void gather_charges_multi(double* __restrict__ qm,
+                                                            float* __restrict__ qm32,
+                                                            const int64_t* __restrict__ order,
+                                                            const double* __restrict__ q,
+                                                            int64_t q_ld, int32_t mc, int log_ld,
+                                                            int64_t ns)
 {
     const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= ns * kRhs)
+    if (idx >= ns << log_ld)
         return;
-    const int64_t j = idx / kRhs;
-    const int m = static_cast<int>(idx - j * kRhs);
+    const int64_t j = idx >> log_ld;
+    const int m = static_cast<int>(idx - (j << log_ld));
     const double v = m < mc ? q[m * q_ld + order[j]] : 0.0;
     qm[idx] = v;
     if (qm32)
@@ -562,14 +563,17 @@ __global__ __launch_bounds__(256) void gather_charges16(double* __restrict__ qm,
 
 }  // namespace
 
-hipError_t launch_gather_charges16(const DevicePlan& d, const double* q, int64_t q_ld, int32_t mc,
-                                   hipStream_t s)
+hipError_t launch_gather_charges_multi(const DevicePlan& d, const double* q, int64_t q_ld,
+                                       int32_t mc, int32_t ld, hipStream_t s)
 {
     if (d.ns == 0)
         return hipSuccess;
-    const int64_t total = d.ns * kRhs;
-    hipLaunchKernelGGL(gather_charges16, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256),
-                       0, s, d.qm, d.qm32, d.src_order, q, q_ld, mc, d.ns);
+    const int log_ld = ld == 2 ? 1 : ld == 4 ? 2 : ld == 8 ? 3 : 4;
+    if (ld != 1 << log_ld || mc > ld)
+        return hipErrorInvalidValue;
+    const int64_t total = d.ns << log_ld;
+    hipLaunchKernelGGL(gather_charges_multi, dim3(static_cast<unsigned>((total + 255) / 256)),
+                       dim3(256), 0, s, d.qm, d.qm32, d.src_order, q, q_ld, mc, log_ld, d.ns);
     return hipGetLastError();
 }
 

@@ -16,6 +16,7 @@
 // The Hermite variant has 2(n+1) factors per dimension -- A_k then B_k, the
 // Hermite basis on the same nodes -- and hence 8 (n+1)^3 outputs per cluster
 // in the layout ((a1 (n+1) + k1) 2(n+1) + a2 (n+1) + k2) 2(n+1) + a3 (n+1) + k3.
+#include <algorithm>
 #include <cfloat>
 
 #include "kernels.hpp"
@@ -95,7 +96,7 @@ __device__ __forceinline__ double factors_hermite(double yv, const double* __res
 }
 
 // grid: x = chunk, y = tile pass.  mw = 1 (one charge vector, taken from
-// src[j].w) or 16 (charges from qm[j][16]).  Output of a chunk: dst[k * mw + m]
+// src[j].w) or 2, 4, 8, 16 (charges from qm[j][mw]).  Output of a chunk: dst[k * mw + m]
 // with dst = out + chunk_dst[c] * P * mw (rows below nslots are the final
 // modified charges of single-chunk clusters, the others partial sums).
 // Tiles are dealt round-robin to the 4 waves: wave w of tile pass p owns
@@ -185,7 +186,7 @@ __device__ __forceinline__ void upward_chunk(
                     SQ[tid] = p.w * inv;
                 } else {
                     for (int m = 0; m < mw; ++m)
-                        SQ[tid * mw + m] = qm[j * 16 + m] * inv;
+                        SQ[tid * mw + m] = qm[j * mw + m] * inv;
                 }
             } else {
                 // zero rows: the partial last step of the tile contributes nothing
@@ -626,16 +627,17 @@ bool launch_single(const DevicePlan& d, double* buf, hipStream_t s, hipError_t* 
 }
 
 // ---------------------------------------------------------------------------
-// 16 charge vectors, Lagrange factors, n + 1 = NP <= 9 nodes per dimension.
-// Output tile (k1, ct) is Qhat[k1][m][(k2, k3)] for the 16 vectors m (rows)
-// and the 16 columns ct*16 .. ct*16 + 15 of (k2, k3): A[m][j] = L1[j][k1]
-// q[j][m] and B[j][(k2, k3)] = L2[j][k2] L3[j][k3], with the factors
-// normalized per dimension (L_l = a_l / D_l, eq. 4, so q~ of eq. 14 is the
-// charge itself).  The NP * ceil(NP^2 / 16) tiles of a chunk are dealt
+// S charge vectors (16, or FP64 2, 4, 8), Lagrange factors, n + 1 = NP <= 9 nodes
+// per dimension.  The products are a matrix of NP S rows (k1, m) and NP^2
+// columns (k2, k3): A[(k1, m)][j] = L1[j][k1] q[j][m] and B[j][(k2, k3)] =
+// L2[j][k2] L3[j][k3], with the factors normalized per dimension (L_l =
+// a_l / D_l, eq. 4, so q~ of eq. 14 is the charge itself), in tiles of 16 x 16:
+// 16 / S values of k1 share a row tile (three row tiles at n = 8 for four
+// vectors, nine for sixteen).  The tiles of a chunk are dealt
 // round-robin to the 8 waves of a workgroup and each wave runs over all of
 // the chunk's sources, so the factors are formed once per chunk, 128 sources
 // at a time: the four quarters of the workgroup take the x, y and z factors
-// and the charges (16 per source) of the same 128 sources into LDS, with the
+// and the charges of the same 128 sources into LDS, with the
 // degree known at compile time.  F32: the rows and charges are rounded to
 // FP32 after their FP64 formation, the products run on v_mfma_f32_16x16x4f32,
 // and every wave adds its FP32 tiles -- 128 sources -- to FP64 tiles after
@@ -647,13 +649,24 @@ constexpr int kMultiMaxNP = 9;
 // LDS of one round: three factor rows of kMultiMaxNP + 1 and 16 charges per source
 constexpr int kMultiLds = kMultiTile * (3 * (kMultiMaxNP + 1) + 16);
 
-template <int NP>
-constexpr int multi_tiles_per_wave()
+// The share of a chunk that a workgroup takes: tiles tile, tile + tiles, ... of
+// every wave's (each share forms the factors again) over range `range` of
+// `ranges` of the chunk's rounds (each range has its own rows of results, summed
+// by the reduction).  Few chunks -- a cluster of the upper levels is one of 64
+// serial rounds -- leave most CUs idle otherwise: on 150,001 points (88 chunks,
+// n = 8, FP64) four vectors took 0.55 ms with one workgroup a chunk, 0.20 ms so,
+// sixteen 1.27 and 0.58 ms.
+struct MultiPart {
+    int32_t tile, tiles, range, ranges;
+};
+
+template <int NP, int S>
+constexpr int multi_tiles()
 {
-    return (NP * ((NP * NP + 15) / 16) + kMultiWaves - 1) / kMultiWaves;
+    return ((NP * S + 15) / 16) * ((NP * NP + 15) / 16);
 }
 
-template <int NP, bool F32>
+template <int NP, int S, bool F32>
 __device__ __forceinline__ void multi_chunk(const double4* __restrict__ src,
                                             const double* __restrict__ qm,
                                             const float* __restrict__ qm32,
@@ -662,18 +675,20 @@ __device__ __forceinline__ void multi_chunk(const double4* __restrict__ src,
                                             const int64_t* __restrict__ chunk_count,
                                             const int64_t* __restrict__ chunk_dst,
                                             const double* __restrict__ slot_nodes,
-                                            double* __restrict__ out, int c, double* lds)
+                                            double* __restrict__ out, int64_t rows, int c,
+                                            MultiPart part, double* lds)
 {
     constexpr int NP2 = NP * NP;
     constexpr int CT = (NP2 + 15) / 16;
-    constexpr int T = NP * CT;
-    constexpr int TW = multi_tiles_per_wave<NP>();
+    constexpr int T = multi_tiles<NP, S>();
+    constexpr int TW = (T + kMultiWaves - 1) / kMultiWaves;
+    static_assert(16 % S == 0, "the vectors of a lane's row are the same in every tile");
     constexpr int SP = NP + 1;                      // row stride: NP factors and a zero
     using R = typename std::conditional<F32, float, double>::type;
     R* __restrict__ L1 = reinterpret_cast<R*>(lds);
     R* __restrict__ L2 = L1 + kMultiTile * SP;
     R* __restrict__ L3 = L2 + kMultiTile * SP;
-    R* __restrict__ SQ = L3 + kMultiTile * SP;      // [kMultiTile][16] charges
+    R* __restrict__ SQ = L3 + kMultiTile * SP;      // [kMultiTile][S] charges
 
     const int64_t slot = chunk_slot[c];
     const int64_t begin = chunk_begin[c];
@@ -683,29 +698,32 @@ __device__ __forceinline__ void multi_chunk(const double4* __restrict__ src,
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double* __restrict__ sn = slot_nodes + slot * 3 * NP;   // wave-uniform
 
-    // this wave's tiles t = wave + 8u: row tile k1 = t / CT, column tile t % CT;
-    // columns past NP^2 read the zero entry of the rows
+    // this wave's tiles: row tile t / CT, column tile t % CT; rows past NP S and
+    // columns past NP^2 read the zero entry of the factor rows
+    auto tile = [&](int u) { return wave + kMultiWaves * (part.tile + part.tiles * u); };
     int ok1[TW], ok2[TW], ok3[TW];
     d4v acc[TW];
     f4v acc32[TW];
 #pragma unroll
     for (int u = 0; u < TW; ++u) {
-        const int t = wave + kMultiWaves * u;
+        const int t = tile(u);
         const bool live = t < T;
-        const int k1 = live ? t / CT : 0;
+        const int k1 = ((live ? t / CT : 0) * 16 + (lane & 15)) / S;
         const int cc = (live ? t - (t / CT) * CT : 0) * 16 + (lane & 15);
-        ok1[u] = k1;
+        ok1[u] = k1 < NP ? k1 : NP;
         ok2[u] = cc < NP2 ? cc / NP : NP;
         ok3[u] = cc < NP2 ? cc - (cc / NP) * NP : NP;
         acc[u] = d4v{0.0, 0.0, 0.0, 0.0};
         acc32[u] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    const int m = lane & 15;
+    const int m = lane & (S - 1);
     const int jl = lane >> 4;
     const int js = tid & (kMultiTile - 1);          // this thread's source of a round
     const int role = tid / kMultiTile;              // 0, 1, 2: x, y, z factors; 3: charges
 
-    for (int64_t t0 = 0; t0 < count; t0 += kMultiTile) {
+    const int64_t rounds = (count + kMultiTile - 1) / kMultiTile;
+    const int64_t t1 = rounds * (part.range + 1) / part.ranges * kMultiTile;
+    for (int64_t t0 = rounds * part.range / part.ranges * kMultiTile; t0 < t1; t0 += kMultiTile) {
         const int tn = static_cast<int>(count - t0 < kMultiTile ? count - t0 : kMultiTile);
         {
             // rows and charges past the chunk's end are zero
@@ -733,13 +751,13 @@ __device__ __forceinline__ void multi_chunk(const double4* __restrict__ src,
                 row[NP] = R(0);
             } else {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
+                for (int v = 0; v < S; ++v) {
                     R qv;
                     if constexpr (F32)
-                        qv = on ? qm32[j * 16 + v] : 0.0f;
+                        qv = on ? qm32[j * S + v] : 0.0f;
                     else
-                        qv = on ? qm[j * 16 + v] : 0.0;
-                    SQ[js * 16 + v] = qv;
+                        qv = on ? qm[j * S + v] : 0.0;
+                    SQ[js * S + v] = qv;
                 }
             }
         }
@@ -747,11 +765,11 @@ __device__ __forceinline__ void multi_chunk(const double4* __restrict__ src,
         const int steps = (tn + 3) / 4;
         for (int st = 0; st < steps; ++st) {
             const int j = 4 * st + jl;
-            const R qv = SQ[j * 16 + m];
+            const R qv = SQ[j * S + m];
             const int jb = j * SP;
 #pragma unroll
             for (int u = 0; u < TW; ++u) {
-                if (wave + kMultiWaves * u >= T)   // uniform: past this wave's last tile
+                if (tile(u) >= T)   // uniform: past this wave's last tile
                     continue;
                 const R av = L1[jb + ok1[u]] * qv;
                 const R bv = L2[jb + ok2[u]] * L3[jb + ok3[u]];
@@ -773,31 +791,37 @@ __device__ __forceinline__ void multi_chunk(const double4* __restrict__ src,
         __syncthreads();
     }
 
-    // lane l, register r: row m = 4r + l/16 (f64) or 4 (l/16) + r (f32), column l % 16
-    double* __restrict__ dst = out + chunk_dst[c] * static_cast<int64_t>(NP2) * NP * 16;
+    // lane l, register r: tile row 4r + l/16 (f64) or 4 (l/16) + r (f32), column l % 16
+    double* __restrict__ dst =
+        out + (part.range * rows + chunk_dst[c]) * static_cast<int64_t>(NP2) * NP * S;
 #pragma unroll
     for (int u = 0; u < TW; ++u) {
-        if (wave + kMultiWaves * u >= T || ok2[u] == NP)
+        if (tile(u) >= T || ok2[u] == NP)
             continue;
-        const int64_t kb = static_cast<int64_t>((ok1[u] * NP + ok2[u]) * NP + ok3[u]) * 16;
+        const int row0 = tile(u) / CT * 16;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int mo = F32 ? 4 * (lane >> 4) + r : 4 * r + (lane >> 4);
-            dst[kb + mo] = acc[u][r];
+            const int row = row0 + (F32 ? 4 * (lane >> 4) + r : 4 * r + (lane >> 4));
+            if (row < NP * S)
+                dst[static_cast<int64_t>(((row / S) * NP + ok2[u]) * NP + ok3[u]) * S + row % S] =
+                    acc[u][r];
         }
     }
 }
 
-template <int NP, bool F32>
+template <int NP, int S, bool F32>
 __global__ __launch_bounds__(64 * kMultiWaves) void upward_multi(
     const double4* __restrict__ src, const double* __restrict__ qm, const float* __restrict__ qm32,
     const int32_t* __restrict__ chunk_slot, const int64_t* __restrict__ chunk_begin,
     const int64_t* __restrict__ chunk_count, const int64_t* __restrict__ chunk_dst,
-    const double* __restrict__ slot_nodes, double* __restrict__ out)
+    const double* __restrict__ slot_nodes, double* __restrict__ out, int64_t rows, int32_t tiles,
+    int32_t ranges)
 {
     __shared__ double lds[kMultiLds];
-    multi_chunk<NP, F32>(src, qm, qm32, chunk_slot, chunk_begin, chunk_count, chunk_dst,
-                         slot_nodes, out, blockIdx.x, lds);
+    const MultiPart part{static_cast<int32_t>(blockIdx.y) % tiles, tiles,
+                         static_cast<int32_t>(blockIdx.y) / tiles, ranges};
+    multi_chunk<NP, S, F32>(src, qm, qm32, chunk_slot, chunk_begin, chunk_count, chunk_dst,
+                            slot_nodes, out, rows, blockIdx.x, part, lds);
 }
 
 // the chunks of many systems (all of degree NP - 1) in one launch
@@ -808,28 +832,49 @@ __global__ __launch_bounds__(64 * kMultiWaves) void upward_multi_many(
     __shared__ double lds[kMultiLds];
     const int2 w = units[blockIdx.x];
     const UpwardDesc& d = descs[__builtin_amdgcn_readfirstlane(w.x)];
-    multi_chunk<NP, F32>(d.src, d.qm, d.qm32, d.chunk_slot, d.chunk_begin, d.chunk_count,
-                         d.chunk_dst, d.slot_nodes, d.buf, __builtin_amdgcn_readfirstlane(w.y),
+    multi_chunk<NP, 16, F32>(d.src, d.qm, d.qm32, d.chunk_slot, d.chunk_begin, d.chunk_count,
+                         d.chunk_dst, d.slot_nodes, d.buf, 0, __builtin_amdgcn_readfirstlane(w.y),
+                         MultiPart{static_cast<int32_t>(blockIdx.y),
+                                   static_cast<int32_t>(gridDim.y), 0, 1},
                          lds);
+}
+
+// workgroups of an upward launch that fill the chip (three per CU)
+constexpr int64_t kMultiWanted = 768;
+
+// shares of the tiles per chunk (at most four: each forms the factors again)
+int32_t multi_tile_shares(int64_t groups)
+{
+    return static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(4, kMultiWanted / std::max<int64_t>(1, groups))));
 }
 
 #define BLTC_MULTI_NP(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9)
 
-// 16-vector Lagrange upward pass of one plan (n + 1 <= 9); false for other degrees
-bool launch_multi(const DevicePlan& d, double* buf, bool f32, hipStream_t s, hipError_t* err)
+template <int NP, int S, bool F32>
+hipError_t run_multi(const DevicePlan& d, double* buf, int32_t ranges, hipStream_t s)
+{
+    const int32_t tiles = multi_tile_shares(d.nchunks * ranges);
+    hipLaunchKernelGGL((upward_multi<NP, S, F32>),
+                       dim3(static_cast<unsigned>(d.nchunks), static_cast<unsigned>(ranges * tiles)),
+                       dim3(64 * kMultiWaves), 0, s, d.src, d.qm, d.qm32, d.chunk_slot,
+                       d.chunk_begin, d.chunk_count, d.chunk_dst, d.slot_nodes, buf, d.qhat_rows,
+                       tiles, ranges);
+    return hipGetLastError();
+}
+
+// Lagrange upward pass of one plan for mw vectors (n + 1 <= 9); false for other
+// degrees
+bool launch_multi(const DevicePlan& d, int32_t mw, double* buf, bool f32, int32_t ranges,
+                  hipStream_t s, hipError_t* err)
 {
     switch (d.degree + 1) {
-#define X(np)                                                                                  \
-    case np:                                                                                   \
-        if (f32)                                                                               \
-            hipLaunchKernelGGL((upward_multi<np, true>), dim3(static_cast<unsigned>(d.nchunks)), \
-                               dim3(64 * kMultiWaves), 0, s, d.src, d.qm, d.qm32, d.chunk_slot, d.chunk_begin, \
-                               d.chunk_count, d.chunk_dst, d.slot_nodes, buf);                 \
-        else                                                                                   \
-            hipLaunchKernelGGL((upward_multi<np, false>), dim3(static_cast<unsigned>(d.nchunks)), \
-                               dim3(64 * kMultiWaves), 0, s, d.src, d.qm, d.qm32, d.chunk_slot, d.chunk_begin, \
-                               d.chunk_count, d.chunk_dst, d.slot_nodes, buf);                 \
-        *err = hipGetLastError();                                                              \
+#define X(np)                                            \
+    case np:                                             \
+        *err = f32       ? run_multi<np, 16, true>(d, buf, ranges, s)   \
+             : mw == 2 ? run_multi<np, 2, false>(d, buf, ranges, s)   \
+             : mw == 4 ? run_multi<np, 4, false>(d, buf, ranges, s)   \
+             : mw == 8 ? run_multi<np, 8, false>(d, buf, ranges, s)   \
+                         : run_multi<np, 16, false>(d, buf, ranges, s); \
         return true;
         BLTC_MULTI_NP(X)
 #undef X
@@ -867,10 +912,12 @@ __global__ __launch_bounds__(256) void upward_mfma_f64_many(const UpwardDesc* __
 }
 
 // qhat (and its FP32 copy) of every slot: the chunk result already in place
-// for single-chunk clusters, else the sum of the partials in chunk order
+// for single-chunk clusters, else the sum of the partials in chunk order (and
+// within a chunk over its ranges, range_stride values apart)
 __global__ __launch_bounds__(256) void upward_mfma_reduce(
     const int32_t* __restrict__ slot_chunk_off, const int64_t* __restrict__ chunk_dst,
-    double* __restrict__ buf, float* __restrict__ qhat32, int64_t nslots, int64_t per_slot)
+    double* __restrict__ buf, float* __restrict__ qhat32, int64_t nslots, int64_t per_slot,
+    int64_t range_stride, int32_t ranges)
 {
     const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (idx >= nslots * per_slot)
@@ -879,12 +926,13 @@ __global__ __launch_bounds__(256) void upward_mfma_reduce(
     const int64_t k = idx - slot * per_slot;
     const int32_t c0 = slot_chunk_off[slot], c1 = slot_chunk_off[slot + 1];
     double s;
-    if (c1 - c0 == 1) {
+    if (c1 - c0 == 1 && ranges == 1) {
         s = buf[idx];
     } else {
         s = 0.0;
         for (int32_t c = c0; c < c1; ++c)
-            s += buf[chunk_dst[c] * per_slot + k];
+            for (int32_t r = 0; r < ranges; ++r)
+                s += buf[r * range_stride + chunk_dst[c] * per_slot + k];
         buf[idx] = s;
     }
     if (qhat32)
@@ -951,7 +999,7 @@ hipError_t upward_prepare(size_t lds)
 }
 
 hipError_t launch_upward_reduce(const DevicePlan& d, int32_t mw, double* buf, float* qhat32,
-                                hipStream_t s)
+                                hipStream_t s, int32_t ranges)
 {
     const int32_t nf = d.hermite ? 2 * (d.degree + 1) : d.degree + 1;
     const int64_t per_slot = static_cast<int64_t>(nf) * nf * nf * mw;
@@ -968,7 +1016,7 @@ hipError_t launch_upward_reduce(const DevicePlan& d, int32_t mw, double* buf, fl
     }
     hipLaunchKernelGGL(upward_mfma_reduce, dim3(static_cast<unsigned>((total + 255) / 256)),
                        dim3(256), 0, s, d.slot_chunk_off, d.chunk_dst, buf, qhat32, d.nslots,
-                       per_slot);
+                       per_slot, d.qhat_rows * per_slot, ranges);
     return hipGetLastError();
 }
 
@@ -983,10 +1031,14 @@ hipError_t launch_upward_mfma(const DevicePlan& d, int32_t mw, double* buf, floa
             return e;
         return launch_upward_reduce(d, mw, buf, qhat32, s);
     }
-    if (mw == 16 && !d.hermite && launch_multi(d, buf, d.src32 != nullptr, s, &e)) {
+    // the result rows are sized for 16 vectors: fewer leave room for 16 / mw
+    // ranges of every chunk
+    const int32_t ranges = static_cast<int32_t>(std::max<int64_t>(
+        1, std::min<int64_t>(16 / std::max(1, mw), kMultiWanted / d.nchunks)));
+    if (mw > 1 && !d.hermite && launch_multi(d, mw, buf, d.src32 != nullptr, ranges, s, &e)) {
         if (e != hipSuccess)
             return e;
-        return launch_upward_reduce(d, mw, buf, qhat32, s);
+        return launch_upward_reduce(d, mw, buf, qhat32, s, ranges);
     }
     const int32_t np = d.degree + 1;
     const int32_t nf = d.hermite ? 2 * np : np;
@@ -1013,15 +1065,17 @@ hipError_t launch_upward_many_multi(const UpwardDesc* descs, const int2* units, 
 {
     if (nunits == 0)
         return hipSuccess;
+    const dim3 grid(static_cast<unsigned>(nunits),
+                    static_cast<unsigned>(multi_tile_shares(nunits)));
     switch (np) {
 #define X(n)                                                                                   \
     case n:                                                                                    \
         if (f32)                                                                               \
-            hipLaunchKernelGGL((upward_multi_many<n, true>), dim3(static_cast<unsigned>(nunits)), \
-                               dim3(64 * kMultiWaves), 0, s, descs, units);                                 \
+            hipLaunchKernelGGL((upward_multi_many<n, true>), grid, dim3(64 * kMultiWaves), 0, s,  \
+                               descs, units);                                                      \
         else                                                                                   \
-            hipLaunchKernelGGL((upward_multi_many<n, false>), dim3(static_cast<unsigned>(nunits)), \
-                               dim3(64 * kMultiWaves), 0, s, descs, units);                                 \
+            hipLaunchKernelGGL((upward_multi_many<n, false>), grid, dim3(64 * kMultiWaves), 0, s, \
+                               descs, units);                                                      \
         return hipGetLastError();
         BLTC_MULTI_NP(X)
 #undef X
