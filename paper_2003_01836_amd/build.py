@@ -69,6 +69,7 @@ def build(verbose: bool = False, defines=(), lib_path: str = LIB, build_dir: str
         "batch": os.path.join(build_dir, "batch.o"),
         "autotune": os.path.join(build_dir, "autotune.o"),
         "setup": os.path.join(build_dir, "setup_gpu.o"),
+        "setup_sym": os.path.join(build_dir, "setup_sym.o"),
         "cp": os.path.join(build_dir, "cp.o"),
         "cc": os.path.join(build_dir, "cc.o"),
         "kernels_cp": os.path.join(build_dir, "kernels_cp.o"),
@@ -91,6 +92,8 @@ def build(verbose: bool = False, defines=(), lib_path: str = LIB, build_dir: str
         [hipcc] + hip_flags + ["-x", "hip", "-c", os.path.join(CSRC, "autotune.cpp"), "-o", objs["autotune"]],
         # geometric decisions (MAC) follow their formulas operation by operation
         [hipcc] + hip_flags + ["-ffp-contract=off", "-c", os.path.join(CSRC, "setup_gpu.hip"), "-o", objs["setup"]],
+        [hipcc] + hip_flags + ["-ffp-contract=off", "-c", os.path.join(CSRC, "setup_sym.hip"), "-o",
+                               objs["setup_sym"]],
         [hipcc] + hip_flags + ["-x", "hip", "-c", os.path.join(CSRC, "cp.cpp"), "-o", objs["cp"]],
         [hipcc] + hip_flags + ["-x", "hip", "-c", os.path.join(CSRC, "cc.cpp"), "-o", objs["cc"]],
         [hipcc] + hip_flags + ["-c", os.path.join(CSRC, "kernels_cp.hip"), "-o", objs["kernels_cp"]],

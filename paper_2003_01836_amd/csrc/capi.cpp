@@ -186,19 +186,8 @@ int upload_symmetric(bltc_plan* plan, hipStream_t s)
     if (plan->prm.no_symmetry || plan->max_q != 1 || !hp.same_tree ||
         (plan->prm.method != BLTC_PARTICLE_CLUSTER && plan->prm.method != BLTC_HERMITE))
         return BLTC_OK;
-    const int64_t nb = static_cast<int64_t>(hp.batch_node.size());
-    const int64_t nnear = nb > 0 ? hp.near_off[nb] : 0;
-    std::vector<int32_t> near_leaf;
-    if (plan->device_lists) {
-        near_leaf.resize(nnear);
-        if (nnear > 0)
-            HIP_TRY(hipMemcpy(near_leaf.data(), d.near_leaf, nnear * sizeof(int32_t),
-                              hipMemcpyDeviceToHost));
-    } else {
-        near_leaf = hp.near_leaf;
-    }
     const bltc::DirectLists dl{&hp.src,      &hp.batch_node, &hp.batch_begin, &hp.batch_count,
-                               &hp.near_off, &near_leaf,     &hp.batch_cost};
+                               &hp.near_off, &hp.near_leaf,  &hp.batch_cost};
     return bltc_internal_upload_symmetric(plan, d, dl, &hp.batch_cost, s);
 }
 
@@ -258,6 +247,14 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
         d.src_order = src_order;
         HIP_TRY(hipStreamSynchronize(s));
     }
+    HIP_TRY(plan->put(&d.far_off, hp.far_off, s));
+    HIP_TRY(plan->put(&d.near_off, hp.near_off, s));
+    if (!plan->device_lists) {
+        HIP_TRY(plan->put(&d.far_slot, hp.far_slot, s));
+        HIP_TRY(plan->put(&d.near_begin, hp.near_begin, s));
+        HIP_TRY(plan->put(&d.near_count, hp.near_count, s));
+        HIP_TRY(plan->put(&d.near_leaf, hp.near_leaf, s));
+    }
     int rc = upload_symmetric(plan, s);
     if (rc != BLTC_OK)
         return rc;
@@ -268,14 +265,6 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
     HIP_TRY(plan->put(&d.group_batch, hp.group_batch, s));
     HIP_TRY(plan->put(&d.group_first, hp.group_first, s));
     HIP_TRY(plan->put(&d.batch_end, batch_end, s));
-    HIP_TRY(plan->put(&d.far_off, hp.far_off, s));
-    HIP_TRY(plan->put(&d.near_off, hp.near_off, s));
-    if (!plan->device_lists) {
-        HIP_TRY(plan->put(&d.far_slot, hp.far_slot, s));
-        HIP_TRY(plan->put(&d.near_begin, hp.near_begin, s));
-        HIP_TRY(plan->put(&d.near_count, hp.near_count, s));
-        HIP_TRY(plan->put(&d.near_leaf, hp.near_leaf, s));
-    }
     HIP_TRY(plan->put(&d.slot_nodes, hp.slot_nodes, s));
     HIP_TRY(plan->put(&d.chunk_slot, hp.chunk_slot, s));
     HIP_TRY(plan->put(&d.chunk_begin, hp.chunk_begin, s));
@@ -617,9 +606,53 @@ int bltc_internal_upload_symmetric(bltc_plan* plan, bltc::DevicePlan& d,
 {
     const int64_t sub = plan->prm.precision == BLTC_FP32_MIXED ? bltc::kSymTargetsMixed
                                                                : bltc::kSymTargetsF64;
+    const int64_t max_unit = kPairWorkspaceBytes / 4 / static_cast<int64_t>(sizeof(double));
+    bltc_plan::Pairs& pr = plan->pairs;
+    if (plan->limit == 0) {
+        // all results in one round: planned on the device
+        bltc::SymDevice sd;
+        auto alloc = [plan](void** ptr, size_t bytes) -> hipError_t {
+            return plan->alloc_bytes(ptr, bytes);
+        };
+        HIP_TRY(bltc::plan_symmetric_device(dl, d, sub, kPairWorkspaceBytes, max_unit, alloc, sd, s));
+        if (sd.planned) {
+            if (sd.units == 0)
+                return BLTC_OK;
+            d.sym_near_off = sd.near_off;
+            d.sym_near_begin = sd.near_begin;
+            d.sym_near_count = sd.near_count;
+            d.sym_near_leaf = sd.near_leaf;
+            d.sym_pc_off = sd.pc_off;
+            d.sym_pc_base = sd.pc_base;
+            d.batch_begin = sd.batch_begin;
+            d.sym_unit = sd.unit;
+            d.sym_out = sd.out;
+            d.sym_units = sd.sub_units;
+            d.sym = 1;
+            d.sym_rounds = 1;
+            for (size_t b = 0; b < cost->size(); ++b)
+                (*cost)[b] -= sd.cut[b];
+            plan->sym_pair_evals = sd.pair_evals;
+            pr.d = &d;
+            pr.count = sd.units;
+            pr.rounds = 1;
+            pr.workspace_bytes = sd.workspace_bytes;
+            return BLTC_OK;
+        }
+    }
     // every mutual pair whose results fit in a quarter of the round workspace
+    bltc::DirectLists hl = dl;
+    std::vector<int32_t> near_leaf;
+    const int64_t nnear = dl.batch_node->empty() ? 0 : dl.near_off->back();
+    if (static_cast<int64_t>(dl.near_leaf->size()) != nnear) {
+        near_leaf.resize(nnear);   // lists built on the device
+        HIP_TRY(hipMemcpyAsync(near_leaf.data(), d.near_leaf, nnear * sizeof(int32_t),
+                               hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        hl.near_leaf = &near_leaf;
+    }
     bltc::SymPlan sp;
-    if (!bltc::plan_symmetric(dl, sub, INT64_MAX, kPairWorkspaceBytes / 4 / sizeof(double), sp))
+    if (!bltc::plan_symmetric(hl, sub, INT64_MAX, max_unit, sp))
         return BLTC_OK;
     HIP_TRY(plan->put(&d.sym_near_off, sp.near_off, s));
     HIP_TRY(plan->put(&d.sym_near_begin, sp.near_begin, s));
@@ -633,7 +666,6 @@ int bltc_internal_upload_symmetric(bltc_plan* plan, bltc::DevicePlan& d,
     d.sym_rounds = 1;
     plan->sym_pair_evals = sp.pair_evals;
     *cost = sp.batch_cost;
-    bltc_plan::Pairs& pr = plan->pairs;
     pr.d = &d;
     pr.batch_begin = *dl.batch_begin;
     pr.batch_count = *dl.batch_count;

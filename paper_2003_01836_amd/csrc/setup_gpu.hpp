@@ -53,4 +53,27 @@ using DeviceAlloc = std::function<hipError_t(void** p, size_t bytes)>;
 std::string build_lists_device(HostPlan& hp, DeviceLists& out, const DeviceAlloc& alloc,
                                hipStream_t s);
 
+// Mutual leaf pairs planned on the device (setup_sym.hip): the reduced direct
+// lists, the result offsets and the sub-units of a DevicePlan, all results in one
+// round.
+struct SymDevice {
+    bool planned = false;   // false: left to the host's plan_symmetric
+    int64_t units = 0;      // pairs (0: the lists stay as they are)
+    int64_t sub_units = 0, pair_evals = 0, workspace_bytes = 0;
+    std::vector<int64_t> cut;   // per batch: direct evaluations per target taken out
+    int32_t *near_off = nullptr, *near_leaf = nullptr, *pc_off = nullptr;
+    int64_t *near_begin = nullptr, *near_count = nullptr, *pc_base = nullptr,
+            *batch_begin = nullptr;
+    SymUnit* unit = nullptr;
+    double* out = nullptr;
+};
+
+// dl: the host side of the lists whose device copies are lists.near_*.  Pairs
+// with results of more than max_unit values, or results and sub-units of more than
+// max_bytes together, are not planned here.  Arrays come from alloc.  Synchronises
+// the stream.
+hipError_t plan_symmetric_device(const DirectLists& dl, const DevicePlan& lists, int64_t sub,
+                                 int64_t max_bytes, int64_t max_unit, const DeviceAlloc& alloc,
+                                 SymDevice& out, hipStream_t s);
+
 }  // namespace bltc
