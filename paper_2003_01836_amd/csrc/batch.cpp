@@ -34,7 +34,7 @@ struct bltc_batch {
     // (FP32 products for FP32-mixed batches) instead of the general one
     int32_t multi_np = 0;
     int32_t* d_counter = nullptr;
-    int32_t workgroups = 0;
+    bltc::QueueLaunch queue;
     // graph of the last set of caller buffers
     bool use_graph = true;
     std::vector<uintptr_t> key;
@@ -79,7 +79,7 @@ int enqueue(bltc_batch* b, const double* const* q, const int32_t* num_q, const i
     }
     HIP_TRY(bltc::launch_reset_counter(b->d_counter, s));
     HIP_TRY(bltc::launch_interact_queue(b->d_descs, b->d_units, b->nunits, b->d_counter, b->kp,
-                                        b->workgroups, s));
+                                        b->queue, s));
     return BLTC_OK;
 }
 
@@ -172,14 +172,7 @@ int batch_create(bltc_batch** out, bltc_plan* const* plans, int32_t count, void*
     if (e == hipSuccess)
         e = bltc::upward_prepare(b->lds);
     if (e == hipSuccess) {
-        int dev = 0, cus = 0, per_cu = 0;
-        e = hipGetDevice(&dev);
-        if (e == hipSuccess)
-            e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, bltc::interact_queue_symbol(b->kp), bltc::kGroupSize, 0);
-        b->workgroups = std::max(1, std::min(b->nunits, cus * std::max(1, per_cu)));
+        e = bltc::plan_interact_queue(b->kp, b->nunits, &b->queue);
     }
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
@@ -316,7 +309,7 @@ int bltc_batch_info_get(const bltc_batch* b, bltc_batch_info* out)
     out->systems = static_cast<int32_t>(b->plans.size());
     out->units = b->nunits;
     out->upward_units = b->nupunits;
-    out->workgroups = b->workgroups;
+    out->workgroups = b->queue.workgroups;
     out->graph_captures = b->captures;
     out->launches = b->launches;
     return BLTC_OK;

@@ -290,10 +290,14 @@ MrhsDesc make_mrhs_desc(const DevicePlan& d, const KernelParams& kp, double* phi
                         int32_t mc);
 // work queue over (system, group) units of many systems; counter reset first
 hipError_t launch_reset_counter(int32_t* counter, hipStream_t s);
+// (persistent workgroups of 1 << log_w waves: as many as the chip holds)
+struct QueueLaunch {
+    int32_t workgroups = 0, log_w = 0;
+};
+hipError_t plan_interact_queue(const KernelParams& kp, int32_t nunits, QueueLaunch* q);
 hipError_t launch_interact_queue(const MrhsDesc* descs, const int2* units, int32_t nunits,
-                                 int32_t* counter, const KernelParams& kp, int32_t workgroups,
+                                 int32_t* counter, const KernelParams& kp, QueueLaunch q,
                                  hipStream_t s);
-const void* interact_queue_symbol(const KernelParams& kp);
 // GPU direct sum (eq. 1) of all targets against all sources, m <= kDirectVectors
 // charge vectors at once.  split = direct_split(nt, ns); `part` holds the
 // pieces' partial sums (pieces * m * nt values; NULL: one piece, phi written

@@ -17,6 +17,8 @@
 //   f64: lane l, register r holds D[4r + l/16][l % 16]
 //   f32: lane l, register r holds D[4(l/16) + r][l % 16]
 // Rows are targets, columns are right-hand sides.
+#include <algorithm>
+
 #include "device_common.hpp"
 #include "kernels.hpp"
 
@@ -114,11 +116,103 @@ struct GridWalk {
     __device__ __forceinline__ int steps() const { return ((lines + 3) / 4) * np; }
 };
 
+// The waves of a workgroup share the lists of its 64 targets, each a part of
+// about equal cost, whole clusters and whole direct entries (the FP32 sums end
+// with them); their sums meet in LDS in wave order (store_sums).
+struct EntryPart {
+    int32_t f0, f1, n0, n1;
+};
+
+__device__ __forceinline__ EntryPart entry_part(int w, int log_w, int32_t f0, int32_t f1, int32_t P,
+                                                int32_t n0, int32_t n1,
+                                                const int64_t* __restrict__ near_count)
+{
+    if (log_w == 0)
+        return EntryPart{f0, f1, n0, n1};
+    // cost in far-field kernel values; a direct value costs about 1.2 of them
+    // (the contraction is the same), in sixths
+    const int lane = threadIdx.x & 63;
+    auto cost_of = [&](int32_t e) {
+        return e < n1 ? 6 * static_cast<long long>(gload<int64_t>(near_count + e)) / 5 : 0ll;
+    };
+    long long near_cost = 0;
+    for (int32_t e = n0 + lane; e < n1; e += 64)
+        near_cost += cost_of(e);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1)
+        near_cost += __shfl_xor(near_cost, m);
+    const int64_t far_cost = static_cast<int64_t>(f1 - f0) * P;
+    const int64_t total = far_cost + uniform64(near_cost);
+    int32_t f[2], n[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int64_t a = (total * (w + k)) >> log_w;
+        f[k] = a < far_cost ? f0 + static_cast<int32_t>((a + P / 2) / P) : f1;
+        // the first entry that starts at or behind the cut
+        const int64_t cut = a - far_cost;
+        n[k] = cut <= 0 ? n0 : n1;
+        long long base = 0;
+        if (cut > 0 && w + k < (1 << log_w))
+            for (int32_t e0 = n0; e0 < n1; e0 += 64) {
+                const long long own = cost_of(e0 + lane);
+                long long upto = own;
+#pragma unroll
+                for (int m = 1; m < 64; m <<= 1) {
+                    const long long v = __shfl_up(upto, m);
+                    upto += lane >= m ? v : 0;
+                }
+                const uint64_t past = __ballot(e0 + lane >= n1 || base + upto - own >= cut);
+                if (past) {
+                    const int32_t e = uniform32(e0 + __builtin_ctzll(past));
+                    n[k] = e < n1 ? e : n1;
+                    break;
+                }
+                base += __shfl(upto, 63);
+            }
+    }
+    return EntryPart{uniform32(f[0]), uniform32(f[1]), uniform32(n[0]), uniform32(n[1])};
+}
+
+// The waves' 4 NT sums per lane (tile t, register r: acc[4 t + r]) added in wave
+// order and stored: rows of a tile are targets, `row` of the lane its vector.
+// `red`: 4 NT * 64 doubles of LDS per wave that nobody reads any more.
+template <bool F32, int NT>
+__device__ __forceinline__ void store_sums(const MrhsDesc& d, const double (&acc)[4 * NT], int64_t first,
+                                           int64_t end, int w, int log_w, double scale,
+                                           double* __restrict__ red)
+{
+    const int lane = threadIdx.x & 63;
+    const int row = lane & 15, col = lane >> 4;
+    auto store = [&](int v, double sum) {
+        const int64_t i = first + 16 * (v >> 2) + (F32 ? 4 * col + (v & 3) : 4 * (v & 3) + col);
+        if (row < d.mc && i < end)
+            gstore(d.phi + row * d.phi_ld + gload<int64_t>(&d.tgt[i].w), scale * sum);
+    };
+    if (log_w == 0) {
+#pragma unroll
+        for (int v = 0; v < 4 * NT; ++v)
+            store(v, acc[v]);
+        return;
+    }
+    __syncthreads();   // the LDS held the waves' targets
+#pragma unroll
+    for (int v = 0; v < 4 * NT; ++v)
+        red[(w * 4 * NT + v) * 64 + lane] = acc[v];
+    __syncthreads();
+    for (int v = w; v < 4 * NT; v += 1 << log_w) {
+        double sum = 0.0;
+        for (int u = 0; u < (1 << log_w); ++u)
+            sum += red[(u * 4 * NT + v) * 64 + lane];
+        store(v, sum);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // FP64: G in FP64 on the VALU, contraction on v_mfma_f64_16x16x4f64.
 // ---------------------------------------------------------------------------
 template <int KER>
-__device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, const double* exp_tab)
+__device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, int log_w,
+                                               const double* exp_tab, double* __restrict__ lds)
 {
     const double4* __restrict__ tgt = d.tgt;
     const double4* __restrict__ src = d.src;
@@ -130,17 +224,15 @@ __device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, const d
     const int64_t* __restrict__ near_count = d.near_count;
     const double4* __restrict__ proxies = d.proxies;
     const double* __restrict__ qhat16 = d.qhat16;
-    double* __restrict__ phi = d.phi;
     const int32_t np = d.np;
-    const int64_t phi_ld = d.phi_ld;
-    const int32_t m_count = d.mc;
     const KernelArg kappa{d.kc.kappa, d.kc.delta2, exp_tab};
     const int b = gload<int32_t>(d.group_batch + g);
     if (b < 0)
         return;
     const int64_t first = gload<int64_t>(d.group_first + g);
     const int64_t end = gload<int64_t>(d.batch_end + b);
-    const int lane = threadIdx.x;
+    const int w = uniform32(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     const int row = lane & 15;
     const int col = lane >> 4;
 
@@ -160,8 +252,11 @@ __device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, const d
         acc[t] = d4v{0.0, 0.0, 0.0, 0.0};
 
     const int P = np * np * np;
-    const int f_end = gload<int32_t>(far_off + b + 1);
-    for (int f = gload<int32_t>(far_off + b); f < f_end; ++f) {
+    const EntryPart part = entry_part(w, log_w, gload<int32_t>(far_off + b),
+                                      gload<int32_t>(far_off + b + 1), P,
+                                      gload<int32_t>(near_off + b),
+                                      gload<int32_t>(near_off + b + 1), near_count);
+    for (int f = part.f0; f < part.f1; ++f) {
         const int64_t slot = gload<int32_t>(far_slot + f);
         const double4* __restrict__ px = proxies + slot * P;
         const double* __restrict__ qh = qhat16 + slot * static_cast<int64_t>(P) * kRhs;
@@ -211,8 +306,7 @@ __device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, const d
             }
         }
     }
-    const int n_end = gload<int32_t>(near_off + b + 1);
-    for (int e = gload<int32_t>(near_off + b); e < n_end; ++e) {
+    for (int e = part.n0; e < part.n1; ++e) {
         const int64_t nb = uniform64(gload<int64_t>(near_begin + e));
         const int32_t cnt = uniform32(static_cast<int32_t>(gload<int64_t>(near_count + e)));
         const double4* sp = src + nb;
@@ -248,16 +342,11 @@ __device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, const d
             }
         }
     }
-    if (row < m_count) {
+    double sums[16];
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t i = first + 16 * t + 4 * r + col;
-                if (i < end)   // the kernel values were doubled (green_*2_f64)
-                    gstore(phi + row * phi_ld + gload<int64_t>(&tgt[i].w), 0.5 * acc[t][r]);
-            }
-    }
+    for (int v = 0; v < 16; ++v)
+        sums[v] = acc[v >> 2][v & 3];
+    store_sums<false, 4>(d, sums, first, end, w, log_w, 0.5, lds);   // the values were doubled
 }
 
 // ---------------------------------------------------------------------------
@@ -265,20 +354,22 @@ __device__ __forceinline__ void group_mrhs_f64(const MrhsDesc& d, int g, const d
 // coordinates), contraction on v_mfma_f32_16x16x4f32, FP32 partial sums over
 // <= kMixedFlushSteps steps, accumulated per target and right-hand side in FP64.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void flush_f32(f4v (&part)[4], double (&acc)[4][4])
+template <int NT>
+__device__ __forceinline__ void flush_f32(f4v (&psum)[NT], double (&acc)[NT][4])
 {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < NT; ++t) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            acc[t][r] += static_cast<double>(part[t][r]);
-        part[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+            acc[t][r] += static_cast<double>(psum[t][r]);
+        psum[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
     }
 }
 
-template <int KER>
-__device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const double* exp_tab,
-                                                 double* __restrict__ tl)
+template <int KER, int NT>
+__device__ __forceinline__ void tiles_mrhs_mixed(const MrhsDesc& d, int b, int64_t first,
+                                                 int64_t end, int log_w, const double* exp_tab,
+                                                 double* __restrict__ lds)
 {
     const double4* __restrict__ tgt = d.tgt;
     const double4* __restrict__ src = d.src;
@@ -295,17 +386,10 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
     const int32_t* __restrict__ slot_cluster = d.slot_cluster;
     const float4* __restrict__ proxies32 = d.proxies32;
     const float* __restrict__ qhat16 = d.qhat16f;
-    double* __restrict__ phi = d.phi;
     const int32_t np = d.np;
-    const int64_t phi_ld = d.phi_ld;
-    const int32_t m_count = d.mc;
     const KernelArg kappa{d.kc.kappa, d.kc.delta2, exp_tab};
-    const int b = gload<int32_t>(d.group_batch + g);
-    if (b < 0)
-        return;
-    const int64_t first = gload<int64_t>(d.group_first + g);
-    const int64_t end = gload<int64_t>(d.batch_end + b);
-    const int lane = threadIdx.x;
+    const int w = uniform32(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     const int row = lane & 15;
     const int col = lane >> 4;
     const KernelArg32 nk = kernel_arg32(d.kc.kappa, d.kc.delta2);
@@ -315,12 +399,12 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
     // group and keep the kernel from four waves per SIMD.  The accesses are
     // volatile, or the compiler forwards the stored values and keeps them in
     // registers after all.
-    volatile double* tl_lane = tl + threadIdx.x;
+    volatile double* tl_lane = lds + w * (16 * 64) + lane;
     auto tc = [tl_lane](int t, int l) -> volatile double& {
-        return tl_lane[(3 * t + l) * kGroupSize];
+        return tl_lane[(3 * t + l) * 64];
     };
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < NT; ++t) {
         int64_t i = first + 16 * t + row;
         i = i < end ? i : end - 1;
         const d3v v = gload<d3v>(tgt + i);
@@ -328,25 +412,28 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
         tc(t, 1) = v.y;
         tc(t, 2) = v.z;
     }
-    double acc[4][4];
-    f4v part[4];
+    double acc[NT][4];
+    f4v psum[NT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        part[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int t = 0; t < NT; ++t) {
+        psum[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             acc[t][r] = 0.0;
     }
 
     const int P = np * np * np;
-    const int f_end = gload<int32_t>(far_off + b + 1);
-    for (int f = gload<int32_t>(far_off + b); f < f_end; ++f) {
+    const EntryPart part = entry_part(w, log_w, gload<int32_t>(far_off + b),
+                                      gload<int32_t>(far_off + b + 1), P,
+                                      gload<int32_t>(near_off + b),
+                                      gload<int32_t>(near_off + b + 1), near_count);
+    for (int f = part.f0; f < part.f1; ++f) {
         const int64_t slot = gload<int32_t>(far_slot + f);
         const d4v ci = gload<d4v>(node_info + gload<int32_t>(slot_cluster + slot));
         // targets relative to the cluster center (proxy points are stored so)
-        float ux[4], uy[4], uz[4];
+        float ux[NT], uy[NT], uz[NT];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < NT; ++t) {
             ux[t] = static_cast<float>(tc(t, 0) - ci.x);
             uy[t] = static_cast<float>(tc(t, 1) - ci.y);
             uz[t] = static_cast<float>(tc(t, 2) - ci.z);
@@ -365,7 +452,7 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
             // slot 0 first: the loop's first wait then leaves the other slots in flight
             __builtin_amdgcn_sched_barrier(0);
         }
-        float ab[4];   // (x - x_k1)^2 + (y - y_k2)^2 of the lane's line
+        float ab[NT];   // (x - x_k1)^2 + (y - y_k2)^2 of the lane's line
         int rounds = 0;
         const int steps = ev.steps();
         for (int s1 = 0; s1 < steps; s1 += kAheadMixed) {
@@ -374,17 +461,17 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
                 const float bq = ev.live(col) ? qn[u] : 0.0f;
                 if (ev.k3 == 0) {
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) {
+                    for (int t = 0; t < NT; ++t) {
                         const float dx = ux[t] - pn[u].x, dy = uy[t] - pn[u].y;
                         ab[t] = __fmaf_rn(dy, dy, dx * dx);
                     }
                 }
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
+                for (int t = 0; t < NT; ++t) {
                     const float dz = uz[t] - pn[u].z;
                     const float r2 = __fmaf_rn(dz, dz, ab[t]);
                     const float gv = green_f32<KER>(r2, nk);
-                    part[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(gv, bq, part[t], 0, 0, 0);
+                    psum[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(gv, bq, psum[t], 0, 0, 0);
                 }
                 ev.advance();
                 const uint32_t kk = ld.point(col);
@@ -395,24 +482,23 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (++rounds == kFlushRounds) {
-                flush_f32(part, acc);
+                flush_f32(psum, acc);
                 rounds = 0;
             }
         }
-        flush_f32(part, acc);
+        flush_f32(psum, acc);
     }
 
     const d4v bi = gload<d4v>(batch_info + b);
-    const int n_end = gload<int32_t>(near_off + b + 1);
-    for (int e = gload<int32_t>(near_off + b); e < n_end; ++e) {
+    for (int e = part.n0; e < part.n1; ++e) {
         const d4v li = gload<d4v>(node_info + gload<int32_t>(near_leaf + e));
         const double ddx = bi.x - li.x, ddy = bi.y - li.y, ddz = bi.z - li.z;
         const double extent = sqrt(ddx * ddx + ddy * ddy + ddz * ddz) + bi.w + 2.0 * li.w;
         const double tau = kTauRel * extent;
         const float tau2 = static_cast<float>(tau * tau);
-        float ux[4], uy[4], uz[4];
+        float ux[NT], uy[NT], uz[NT];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < NT; ++t) {
             ux[t] = static_cast<float>(tc(t, 0) - li.x);
             uy[t] = static_cast<float>(tc(t, 1) - li.y);
             uz[t] = static_cast<float>(tc(t, 2) - li.z);
@@ -437,18 +523,22 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
             for (int u = 0; u < kAheadMixed; ++u) {
                 const int32_t j0 = j1 + 4 * u;
                 const float bq = (j0 + col < cnt) ? qn[u] : 0.0f;
-                float gv[4], r2v[4];
+                float gv[NT], r2v[NT];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
+                for (int t = 0; t < NT; ++t) {
                     const float dx = ux[t] - pn[u].x, dy = uy[t] - pn[u].y, dz = uz[t] - pn[u].z;
                     r2v[t] = __fmaf_rn(dz, dz, __fmaf_rn(dy, dy, dx * dx));
                     gv[t] = green_f32<KER>(r2v[t], nk);
                 }
-                if (fminf(fminf(r2v[0], r2v[1]), fminf(r2v[2], r2v[3])) <= tau2) {
+                float least = r2v[0];
+#pragma unroll
+                for (int t = 1; t < NT; ++t)
+                    least = fminf(least, r2v[t]);
+                if (least <= tau2) {
                     // close pairs: the kernel value from the exact coordinates, in FP64
                     const d3v p64 = gload<d3v>(src + nb + (j0 + col < cnt ? j0 + col : cnt - 1));
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
+                    for (int t = 0; t < NT; ++t)
                         if (r2v[t] <= tau2) {
                             const double dx = tc(t, 0) - p64.x;
                             const double dy = tc(t, 1) - p64.y;
@@ -458,8 +548,8 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
                         }
                 }
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    part[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(gv[t], bq, part[t], 0, 0, 0);
+                for (int t = 0; t < NT; ++t)
+                    psum[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(gv[t], bq, psum[t], 0, 0, 0);
                 const int32_t jn = j0 + 4 * kAheadMixed + col;
                 const uint32_t jj = jn < cnt ? jn : cnt - 1;
                 pn[u] = gload_at<f3v>(sp, jj * 16u);
@@ -468,53 +558,78 @@ __device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, const
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (++rounds == kFlushRounds) {
-                flush_f32(part, acc);
+                flush_f32(psum, acc);
                 rounds = 0;
             }
         }
-        flush_f32(part, acc);
+        flush_f32(psum, acc);
     }
-    if (row < m_count) {
+    double sums[4 * NT];
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t i = first + 16 * t + 4 * col + r;
-                if (i < end)
-                    gstore(phi + row * phi_ld + gload<int64_t>(&tgt[i].w), acc[t][r]);
-            }
-    }
+    for (int v = 0; v < 4 * NT; ++v)
+        sums[v] = acc[v >> 2][v & 3];
+    store_sums<true, NT>(d, sums, first, end, w, log_w, 1.0, lds);
 }
+
+// Tiles the group's targets need: a leaf of 195 targets is three groups of four
+// tiles and one of one, whose steps cost a quarter (leaves of 156 to 195, 16
+// vectors: queue kernel 6.3 ms with four tiles throughout, 5.9 so).
+template <int KER>
+__device__ __forceinline__ void group_mrhs_mixed(const MrhsDesc& d, int g, int log_w,
+                                                 const double* exp_tab, double* __restrict__ lds)
+{
+    const int b = gload<int32_t>(d.group_batch + g);
+    if (b < 0)
+        return;
+    const int64_t first = uniform64(gload<int64_t>(d.group_first + g));
+    const int64_t end = uniform64(gload<int64_t>(d.batch_end + b));
+    const int tiles = uniform32(static_cast<int32_t>(min(int64_t(4), (end - first + 15) / 16)));
+    if (tiles >= 4)
+        tiles_mrhs_mixed<KER, 4>(d, b, first, end, log_w, exp_tab, lds);
+    else if (tiles == 3)
+        tiles_mrhs_mixed<KER, 3>(d, b, first, end, log_w, exp_tab, lds);
+    else if (tiles == 2)
+        tiles_mrhs_mixed<KER, 2>(d, b, first, end, log_w, exp_tab, lds);
+    else
+        tiles_mrhs_mixed<KER, 1>(d, b, first, end, log_w, exp_tab, lds);
+}
+
+// Waves of a workgroup, at most: 8 KB of LDS each (the FP32-mixed targets' FP64
+// coordinates, then the sums).
+constexpr int kMrhsWaves = 8;
 
 // four waves per SIMD on the FP32-mixed form, as for the work queue below
 template <int KER, int PREC>
-__global__ __launch_bounds__(kGroupSize) __attribute__((amdgpu_waves_per_eu(PREC == 1 ? 4 : 1)))
-void interact_mrhs(MrhsDesc d)
+__global__ __launch_bounds__(64 * kMrhsWaves) __attribute__((amdgpu_waves_per_eu(PREC == 1 ? 4 : 2)))
+void interact_mrhs(MrhsDesc d, int32_t log_w)
 {
     __shared__ double exp_tab[64];
-    __shared__ double tlds[PREC == 0 ? 1 : 12 * kGroupSize];
+    extern __shared__ double lds[];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     if constexpr (PREC == 0)
-        group_mrhs_f64<KER>(d, blockIdx.x, exp_tab);
+        group_mrhs_f64<KER>(d, blockIdx.x, log_w, exp_tab, lds);
     else
-        group_mrhs_mixed<KER>(d, blockIdx.x, exp_tab, tlds);
+        group_mrhs_mixed<KER>(d, blockIdx.x, log_w, exp_tab, lds);
 }
 
 // Persistent work queue over the groups of many systems: every workgroup
 // repeatedly takes the next unit (system, group) -- heaviest first -- until
 // the queue is empty.  The counter is reset by reset_counter before a launch.
-template <int KER, int PREC>
+// The waves of a workgroup share a unit: 8 systems of 12,501 to 100,001 points are
+// 4600 units, about one for each of the 4096 waves that are resident, and the
+// second ones of some left the rest idle (kernel 6.9 ms; 6.3 with four waves a unit).
 // The FP32-mixed form is held to four waves per SIMD (the compiler then keeps
 // 128 VGPRs and spills a few to scratch; measured faster than three waves
 // without spills).
-__global__ __launch_bounds__(kGroupSize) __attribute__((amdgpu_waves_per_eu(PREC == 1 ? 4 : 1)))
+template <int KER, int PREC>
+__global__ __launch_bounds__(64 * kMrhsWaves) __attribute__((amdgpu_waves_per_eu(PREC == 1 ? 4 : 2)))
 void interact_queue(const MrhsDesc* __restrict__ descs, const int2* __restrict__ units,
-                    int32_t nunits, int32_t* __restrict__ counter)
+                    int32_t nunits, int32_t log_w, int32_t* __restrict__ counter)
 {
     __shared__ int32_t next;
     __shared__ double exp_tab[64];
-    __shared__ double tlds[PREC == 0 ? 1 : 12 * kGroupSize];
+    extern __shared__ double lds[];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     for (;;) {
@@ -529,9 +644,9 @@ void interact_queue(const MrhsDesc* __restrict__ descs, const int2* __restrict__
         const int32_t sys = __builtin_amdgcn_readfirstlane(w.x);
         const int32_t g = __builtin_amdgcn_readfirstlane(w.y);
         if constexpr (PREC == 0)
-            group_mrhs_f64<KER>(descs[sys], g, exp_tab);
+            group_mrhs_f64<KER>(descs[sys], g, log_w, exp_tab, lds);
         else
-            group_mrhs_mixed<KER>(descs[sys], g, exp_tab, tlds);
+            group_mrhs_mixed<KER>(descs[sys], g, log_w, exp_tab, lds);
     }
 }
 
@@ -610,6 +725,11 @@ MrhsDesc make_mrhs_desc(const DevicePlan& d, const KernelParams& kp, double* phi
     return m;
 }
 
+static size_t mrhs_lds(int32_t log_w)
+{
+    return sizeof(double) * 16 * (64u << log_w);
+}
+
 static bool mrhs_tables_ok(const DevicePlan& d, int32_t precision)
 {
     if (precision == 1)
@@ -625,19 +745,19 @@ hipError_t launch_interact_mrhs(const DevicePlan& d, const KernelParams& kp, dou
     if (!mrhs_tables_ok(d, kp.precision))
         return hipErrorInvalidValue;
     const MrhsDesc m = make_mrhs_desc(d, kp, phi, phi_ld, mc);
-    const dim3 grid(static_cast<unsigned>(d.ngroups)), block(kGroupSize);
-    void (*fn)(MrhsDesc) = nullptr;
+    const GroupLaunch gl = group_launch(d, kMrhsWaves);
+    void (*fn)(MrhsDesc, int32_t) = nullptr;
     if (kp.precision == 1)
         fn = kp.kernel == 1 ? interact_mrhs<1, 1> : kp.kernel == 2 ? interact_mrhs<2, 1>
                                                                    : interact_mrhs<0, 1>;
     else
         fn = kp.kernel == 1 ? interact_mrhs<1, 0> : kp.kernel == 2 ? interact_mrhs<2, 0>
                                                                    : interact_mrhs<0, 0>;
-    hipLaunchKernelGGL(fn, grid, block, 0, s, m);
+    hipLaunchKernelGGL(fn, dim3(gl.blocks), dim3(64u << gl.log_w), mrhs_lds(gl.log_w), s, m, gl.log_w);
     return hipGetLastError();
 }
 
-using QueueKernel = void (*)(const MrhsDesc*, const int2*, int32_t, int32_t*);
+using QueueKernel = void (*)(const MrhsDesc*, const int2*, int32_t, int32_t, int32_t*);
 
 static QueueKernel queue_kernel(const KernelParams& kp)
 {
@@ -655,19 +775,31 @@ hipError_t launch_reset_counter(int32_t* counter, hipStream_t s)
 }
 
 hipError_t launch_interact_queue(const MrhsDesc* descs, const int2* units, int32_t nunits,
-                                 int32_t* counter, const KernelParams& kp, int32_t workgroups,
+                                 int32_t* counter, const KernelParams& kp, QueueLaunch q,
                                  hipStream_t s)
 {
     if (nunits == 0)
         return hipSuccess;
-    const dim3 grid(static_cast<unsigned>(workgroups)), block(kGroupSize);
-    hipLaunchKernelGGL(queue_kernel(kp), grid, block, 0, s, descs, units, nunits, counter);
+    hipLaunchKernelGGL(queue_kernel(kp), dim3(static_cast<unsigned>(q.workgroups)),
+                       dim3(64u << q.log_w), mrhs_lds(q.log_w), s, descs, units, nunits, q.log_w,
+                       counter);
     return hipGetLastError();
 }
 
-const void* interact_queue_symbol(const KernelParams& kp)
+hipError_t plan_interact_queue(const KernelParams& kp, int32_t nunits, QueueLaunch* q)
 {
-    return reinterpret_cast<const void*>(queue_kernel(kp));
+    // four waves a unit; eight where four would leave waves without one
+    q->log_w = nunits < 2048 ? 3 : 2;
+    int dev = 0, cus = 0, per_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, reinterpret_cast<const void*>(queue_kernel(kp)), 64 << q->log_w,
+            mrhs_lds(q->log_w));
+    q->workgroups = std::max(1, std::min(nunits, cus * std::max(1, per_cu)));
+    return e;
 }
 
 }  // namespace bltc

@@ -839,8 +839,9 @@ __global__ __launch_bounds__(64 * kMultiWaves) void upward_multi_many(
                          lds);
 }
 
-// workgroups of an upward launch that fill the chip (three per CU)
-constexpr int64_t kMultiWanted = 768;
+// workgroups of an upward launch: twice what is resident (three per CU; at once
+// that many took 0.61 ms on 8 systems of FP32-mixed chunks, twice 0.56)
+constexpr int64_t kMultiWanted = 1536;
 
 // shares of the tiles per chunk (at most four: each forms the factors again)
 int32_t multi_tile_shares(int64_t groups)
