@@ -19,7 +19,11 @@
 namespace bltc {
 namespace dev {
 
-constexpr int kSplitBlock = 128;   // sources; = the FP32-mixed flush length
+// sources of a block of the direct entries: FP32-mixed the flush length of its
+// sums, FP64 a length that divides the few hundred sources of a small problem's
+// leaves evenly among 16 waves
+template <bool MIXED>
+constexpr int kSplitBlock = MIXED ? 128 : 32;
 
 struct ListPart {
     int32_t plane0, plane1;   // planes f (n+1) + k1 of the batch's far list
@@ -29,16 +33,15 @@ struct ListPart {
     int32_t pc0, pc1;         // mutual-pair results
 };
 
-// Cost of a direct block in far-field kernel values of the same kernel and
+// Cost of a direct value in far-field kernel values of the same kernel and
 // precision: three differences and squares, against one addition, beside the
 // reciprocal square root (and, Yukawa, the exponential) that both form.
 template <int KER, bool MIXED>
-constexpr int kBlockCost = (MIXED ? (KER == 1 ? 180 : 220) : (KER == 1 ? 130 : 180)) * kSplitBlock / 100;
+constexpr int kDirectCost = MIXED ? (KER == 1 ? 180 : 220) : (KER == 1 ? 130 : 180);   // percent
 
 // Part w of 2^log_w of far entries [0, nf) with NP planes of PLANE far-field
-// kernel values, direct entries [n0, n1) of BLOCK per block and pair results
-// [p0, p1).
-template <int NP, int PLANE, int BLOCK>
+// kernel values, direct entries [n0, n1) in blocks and pair results [p0, p1).
+template <int NP, int PLANE, int KER, bool MIXED>
 __device__ __forceinline__ ListPart list_part(int w, int log_w, int32_t nf, int32_t n0, int32_t n1,
                                               const int64_t* __restrict__ near_count, int32_t p0,
                                               int32_t p1)
@@ -55,10 +58,12 @@ __device__ __forceinline__ ListPart list_part(int w, int log_w, int32_t nf, int3
         return r;
     }
     constexpr int kPairCost = 4;   // a load and an addition
+    constexpr int kBlock = kSplitBlock<MIXED>;
+    constexpr int BLOCK = kDirectCost<KER, MIXED> * kBlock / 100;
     const int lane = threadIdx.x & 63;
     int32_t mine = 0;
     for (int32_t e = n0 + lane; e < n1; e += 64)
-        mine += static_cast<int32_t>((near_count[e] + (kSplitBlock - 1)) / kSplitBlock);
+        mine += static_cast<int32_t>((near_count[e] + (kBlock - 1)) / kBlock);
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1)
         mine += __shfl_xor(mine, m);
@@ -94,7 +99,7 @@ __device__ __forceinline__ ListPart list_part(int w, int log_w, int32_t nf, int3
         for (int32_t e0 = n0; e0 < n1; e0 += 64) {
             const int32_t e = e0 + lane;
             const int32_t own =
-                e < n1 ? static_cast<int32_t>((near_count[e] + (kSplitBlock - 1)) / kSplitBlock) : 0;
+                e < n1 ? static_cast<int32_t>((near_count[e] + (kBlock - 1)) / kBlock) : 0;
             int32_t upto = own;
 #pragma unroll
             for (int m = 1; m < 64; m <<= 1) {
@@ -116,17 +121,18 @@ __device__ __forceinline__ ListPart list_part(int w, int log_w, int32_t nf, int3
 }
 
 // Direct entries of a part: sum(first source of the run, its length, entry).
-template <class F>
+template <bool MIXED, class F>
 __device__ __forceinline__ void for_direct_runs(const ListPart& part, int32_t n1,
                                                 const int64_t* __restrict__ near_begin,
                                                 const int64_t* __restrict__ near_count, F&& sum)
 {
     int32_t left = part.blocks, skip = part.skip;
     for (int32_t e = part.entry; left > 0 && e < n1; ++e) {
-        const int32_t j0 = skip * kSplitBlock;
+        constexpr int kBlock = kSplitBlock<MIXED>;
+        const int32_t j0 = skip * kBlock;
         const int32_t avail = static_cast<int32_t>(near_count[e]) - j0;
-        const int32_t have = (avail + (kSplitBlock - 1)) / kSplitBlock;
-        const int32_t cnt = left < have ? left * kSplitBlock : avail;
+        const int32_t have = (avail + (kBlock - 1)) / kBlock;
+        const int32_t cnt = left < have ? left * kBlock : avail;
         sum(near_begin[e] + j0, cnt, e);
         left -= have;
         skip = 0;

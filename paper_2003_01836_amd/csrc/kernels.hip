@@ -106,7 +106,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void interact_f64(
     const int f0 = far_off[b];
     const int n1 = near_off[b + 1];
     const ListPart part =
-        list_part<NP, NP * NP, kBlockCost<KER, false>>(w, log_w, far_off[b + 1] - f0, near_off[b], n1, near_count,
+        list_part<NP, NP * NP, KER, false>(w, log_w, far_off[b + 1] - f0, near_off[b], n1, near_count,
                                pc_off ? pc_off[b] : 0, pc_off ? pc_off[b + 1] : 0);
     int f = part.plane0 / NP, ka = part.plane0 - f * NP;
     for (int pl = part.plane0; pl < part.plane1; ++f) {
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void interact_f64(
         pl += kb - ka;
         ka = 0;
     }
-    for_direct_runs(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t) {
+    for_direct_runs<false>(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t) {
         acc += near_sum_f64<KER>(t.x, t.y, t.z, src + j, cnt, kappa);
     });
     if (pc_off) {

@@ -150,7 +150,7 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_f64(
     const int f0 = far_off[b];
     const int n1 = near_off[b + 1];
     const ListPart part =
-        list_part<NP, 4 * NP * NP, kBlockCost<KER, false>>(w, log_w, far_off[b + 1] - f0, near_off[b], n1,
+        list_part<NP, 4 * NP * NP, KER, false>(w, log_w, far_off[b + 1] - f0, near_off[b], n1,
                                             near_count, pc_off ? pc_off[b] : 0,
                                             pc_off ? pc_off[b + 1] : 0);
     int f = part.plane0 / NP, pa = part.plane0 - f * NP;
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_f64(
         pl += pb - pa;
         pa = 0;
     }
-    for_direct_runs(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t) {
+    for_direct_runs<false>(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t) {
         acc += near_sum_f64<KER>(t.x, t.y, t.z, src + j, cnt, ka);
     });
     if (pc_off) {
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_mixed(
     const int f0 = far_off[b];
     const int n1 = near_off[b + 1];
     const ListPart part =
-        list_part<NP, 5 * NP * NP, kBlockCost<KER, true>>(w, log_w, far_off[b + 1] - f0, near_off[b], n1,
+        list_part<NP, 5 * NP * NP, KER, true>(w, log_w, far_off[b + 1] - f0, near_off[b], n1,
                                             near_count, pc_off ? pc_off[b] : 0,
                                             pc_off ? pc_off[b + 1] : 0);
     int f = part.plane0 / NP, pa = part.plane0 - f * NP;
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_mixed(
         pa = 0;
     }
     const double4 bi = batch_info[b];
-    for_direct_runs(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t e) {
+    for_direct_runs<true>(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t e) {
         acc += near_entry_mixed<KER>(t.x, t.y, t.z, bi, node_info[near_leaf[e]], src32 + j, src + j,
                                      cnt, nk, ka);
     });

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     const int f0 = far_off[b];
     const int n1 = near_off[b + 1];
     const ListPart part =
-        list_part<NP, NP * NP, kBlockCost<KER, true>>(w, log_w, far_off[b + 1] - f0, near_off[b], n1, near_count,
+        list_part<NP, NP * NP, KER, true>(w, log_w, far_off[b + 1] - f0, near_off[b], n1, near_count,
                                pc_off ? pc_off[b] : 0, pc_off ? pc_off[b + 1] : 0);
     float* const qs = reinterpret_cast<float*>(lds) + w * P;   // this wave's staged charges
     int f = part.plane0 / NP, ka = part.plane0 - f * NP;
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         ka = 0;
     }
     const double4 bi = batch_info[b];
-    for_direct_runs(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t e) {
+    for_direct_runs<true>(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t e) {
         acc += near_entry_mixed<KER>(t.x, t.y, t.z, bi, node_info[near_leaf[e]], src32 + j, src + j,
                                      cnt, nk, kappa);
     });

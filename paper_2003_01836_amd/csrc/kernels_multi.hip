@@ -307,7 +307,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void interact_multi(
 
     const int f0 = a.far_off[b];
     const int n1 = a.near_off[b + 1];
-    const ListPart part = list_part<NP, NP * NP, kBlockCost<KER, false>>(
+    const ListPart part = list_part<NP, NP * NP, KER, false>(
         w, a.log_w, a.far_off[b + 1] - f0, a.near_off[b], n1, near_count, 0, 0);
     int f = part.plane0 / NP, ka = part.plane0 - f * NP;
     for (int pl = part.plane0; pl < part.plane1; ++f) {
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void interact_multi(
         pl += kb - ka;
         ka = 0;
     }
-    for_direct_runs(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t) {
+    for_direct_runs<false>(part, n1, near_begin, near_count, [&](int64_t j, int32_t cnt, int32_t) {
         for (int32_t k = 0; k < cnt; k += 4 * kBlockTerms) {
             const int32_t c = cnt - k < 4 * kBlockTerms ? cnt - k : 4 * kBlockTerms;
             near_run<KER, M>(t.x, t.y, t.z, src + j + k, qm + (j + k) * M, c, kappa, acc);

@@ -40,6 +40,7 @@ static_assert(kSymTargetsMixed == 64 * kChunks && kSymTargetsF64 == 64 * kChunks
 
 constexpr double kTauRel = kMixedTauRel;   // the mixed interaction kernel's cut-off
 constexpr int kFlushEvery = 128;           // FP32 row sums span at most this many sources
+constexpr int kPairWaves = 8;              // waves that share a unit, at most
 
 // lane l returns the sum over the wave's 64 lanes of v[l % kBlk] (v is consumed)
 template <typename T>
@@ -84,11 +85,57 @@ __device__ __forceinline__ void pair_term_f64(double tx, double ty, double tz, d
     col = __fma_rn(g, tq, col);
 }
 
+// The part of a unit's sources that wave w of W takes: runs of whole `grain`s of
+// sources (a butterfly block, or the length of an FP32 row sum).
+struct SourceRange {
+    int begin, end;
+};
+
+__device__ __forceinline__ SourceRange source_range(int nc, int grain, int w, int waves)
+{
+    const int grains = (nc + grain - 1) / grain;
+    const int b = grains * w / waves * grain, e = grains * (w + 1) / waves * grain;
+    return SourceRange{b < nc ? b : nc, e < nc ? e : nc};
+}
+
+// Row sums of the unit's waves (row[k]: target 64 k + lane) added in wave order and
+// stored; `red`: 64 kChunks doubles per wave.
+template <int CHUNKS>
+__device__ __forceinline__ void store_rows(const SymUnit& u, const double (&row)[CHUNKS], int nch,
+                                           int lane, int w, int waves, double* __restrict__ out,
+                                           double* __restrict__ red)
+{
+    if (waves == 1) {
+#pragma unroll
+        for (int k = 0; k < CHUNKS; ++k) {
+            const int i = 64 * k + lane;
+            if (k < nch && i < u.nb)
+                out[u.roff + i] = row[k];
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < CHUNKS; ++k)
+        if (k < nch)
+            red[(w * CHUNKS + k) * 64 + lane] = row[k];
+    __syncthreads();
+    for (int k = w; k < nch; k += waves) {
+        double v = red[k * 64 + lane];
+        for (int x = 1; x < waves; ++x)
+            v += red[(x * CHUNKS + k) * 64 + lane];
+        const int i = 64 * k + lane;
+        if (i < u.nb)
+            out[u.roff + i] = v;
+    }
+}
+
 template <int KER, bool CHECK>
 __device__ __forceinline__ void pairs_unit_f64(const SymUnit& u, const double4* __restrict__ src,
-                                               double* __restrict__ out, const KernelArg& ka)
+                                               double* __restrict__ out, const KernelArg& ka, int w,
+                                               int waves, double* __restrict__ red)
 {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const SourceRange part = source_range(u.nc, kBlk, w, waves);
     const double4* __restrict__ S = src + u.sb;
     const int nch = (u.nb + 63) / 64;   // uniform, <= kChunks64 by construction
     double tx[kChunks64], ty[kChunks64], tz[kChunks64], tq[kChunks64], a0[kChunks64],
@@ -106,8 +153,8 @@ __device__ __forceinline__ void pairs_unit_f64(const SymUnit& u, const double4* 
     }
     // full blocks: the kBlk sources are loaded once (wave-uniform, into SGPRs)
     // and serve every chunk of targets
-    int s0 = 0;
-    for (; s0 + kBlk <= u.nc; s0 += kBlk) {
+    int s0 = part.begin;
+    for (; s0 + kBlk <= part.end; s0 += kBlk) {
         double4 p[kBlk];
 #pragma unroll
         for (int m = 0; m < kBlk; ++m)
@@ -128,9 +175,9 @@ __device__ __forceinline__ void pairs_unit_f64(const SymUnit& u, const double4* 
         const double cs = column_sums(v, lane);
         out[u.coff + s0 + (lane & (kBlk - 1))] = 0.5 * cs;   // lanes l, l + kBlk, ... agree
     }
-    if (s0 < u.nc) {
+    if (s0 < part.end) {
         // the last, partial block
-        const int cnt = u.nc - s0;   // uniform, < kBlk
+        const int cnt = part.end - s0;   // uniform, < kBlk
         double v[kBlk];
 #pragma unroll
         for (int m = 0; m < kBlk; ++m)
@@ -152,31 +199,33 @@ __device__ __forceinline__ void pairs_unit_f64(const SymUnit& u, const double4* 
             out[u.coff + s0 + lane] = 0.5 * cs;
     }
 #pragma unroll
-    for (int k = 0; k < kChunks64; ++k) {
-        const int i = 64 * k + lane;
-        if (k < nch && i < u.nb)
-            out[u.roff + i] = 0.5 * (a0[k] + a1[k]);
-    }
+    for (int k = 0; k < kChunks64; ++k)
+        a0[k] = 0.5 * (a0[k] + a1[k]);
+    store_rows<kChunks64>(u, a0, nch, lane, w, waves, out, red);
 }
 
 // Two waves per SIMD: 8 chunks of targets and a source block in flight take
 // about 250 VGPRs (one wave per SIMD when left to the compiler, or spills at
 // three); measured on 10^6 particles, 19.2 ms against 24.9 ms (one wave) and
 // 20.5 ms (4 chunks, three waves).
-template <int KER>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void near_pairs_f64(
+// A launch of few units shares each among 2, 4 or 8 waves (pair_waves).
+template <int KER, bool SHARED>
+__global__ __launch_bounds__(SHARED ? 64 * kPairWaves : 64) __attribute__((amdgpu_waves_per_eu(2))) void near_pairs_f64(
     const SymUnit* __restrict__ units, const double4* __restrict__ src, double* __restrict__ out,
     KernelConst kc)
 {
     __shared__ double exp_tab[64];
+    extern __shared__ double red[];
+    const int w = SHARED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int waves = SHARED ? blockDim.x >> 6 : 1;
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg ka{kc.kappa, kc.delta2, exp_tab};
     const SymUnit u = units[blockIdx.x];
     if (u.apart)
-        pairs_unit_f64<KER, false>(u, src, out, ka);
+        pairs_unit_f64<KER, false>(u, src, out, ka, w, waves, red);
     else
-        pairs_unit_f64<KER, true>(u, src, out, ka);
+        pairs_unit_f64<KER, true>(u, src, out, ka, w, waves, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -258,19 +307,23 @@ __device__ __forceinline__ void block_mixed(const float (&tx)[kChunks], const fl
 
 // four waves per SIMD (128 VGPRs, no spills): 8% faster than the three the
 // default allocation allows
-template <int KER>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void near_pairs_mixed(
+template <int KER, bool SHARED>
+__global__ __launch_bounds__(SHARED ? 64 * kPairWaves : 64) __attribute__((amdgpu_waves_per_eu(4))) void near_pairs_mixed(
     const SymUnit* __restrict__ units, const double4* __restrict__ src,
     const float4* __restrict__ src32, const double4* __restrict__ node_info,
     const double4* __restrict__ batch_info, double* __restrict__ out, KernelConst kc)
 {
     __shared__ double exp_tab[64];
+    extern __shared__ double red[];
+    const int w = SHARED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int waves = SHARED ? blockDim.x >> 6 : 1;
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg ka{kc.kappa, kc.delta2, exp_tab};
     const KernelArg32 nk = kernel_arg32(kc.kappa, kc.delta2);
     const SymUnit u = units[blockIdx.x];
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const SourceRange part = source_range(u.nc, kFlushEvery, w, waves);
     // tau of the pair: the larger of the two directions' values
     const double4 bi = batch_info[u.batch];
     const double4 li = node_info[u.leaf];
@@ -297,8 +350,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void ne
         ra[k] = 0.0f;
         acc[k] = 0.0;
     }
-    int s0 = 0;
-    for (; s0 + kBlk <= u.nc; s0 += kBlk) {
+    int s0 = part.begin;
+    for (; s0 + kBlk <= part.end; s0 += kBlk) {
         float v[kBlk];
 #pragma unroll
         for (int m = 0; m < kBlk; ++m)
@@ -316,8 +369,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void ne
             }
         }
     }
-    if (s0 < u.nc) {
-        const int cnt = u.nc - s0;
+    if (s0 < part.end) {
+        const int cnt = part.end - s0;
         float v[kBlk];
 #pragma unroll
         for (int m = 0; m < kBlk; ++m)
@@ -329,11 +382,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void ne
             out[u.coff + s0 + lane] = static_cast<double>(cs);
     }
 #pragma unroll
-    for (int k = 0; k < kChunks; ++k) {
-        const int i = 64 * k + lane;
-        if (k < nch && i < u.nb)
-            out[u.roff + i] = acc[k] + static_cast<double>(ra[k]);
-    }
+    for (int k = 0; k < kChunks; ++k)
+        acc[k] += static_cast<double>(ra[k]);
+    store_rows<kChunks>(u, acc, nch, lane, w, waves, out, red);
 }
 
 // One round of mutual-pair results into the per-target sums: one workgroup
@@ -372,6 +423,21 @@ hipError_t launch_fold_pairs(int64_t nbatches, const int64_t* begin, const int64
     return hipGetLastError();
 }
 
+// Waves per unit: a unit is one chain of source blocks, so few units leave the chip
+// (2048 resident waves of the FP64 kernel, 4096 FP32-mixed) idle for its length.
+// Shared among 2, 4 or 8 waves as long as all stay resident together (more of them
+// only repeat the loads of the unit's targets); FP32-mixed units in pieces of
+// kFlushEvery sources, of which a leaf has few: at most two.  FP64, one wave each
+// -> shared: 99 units of 1500 points 34 -> 12.5 us; 885 units of 10^4 points 37 -> 27.4 us.
+static int pair_waves(int64_t count, bool mixed)
+{
+    const int64_t resident = mixed ? 4096 : 2048;
+    int w = 1;
+    while (w < (mixed ? 2 : kPairWaves) && 2 * w * count <= resident)
+        w *= 2;
+    return w;
+}
+
 hipError_t launch_near_pairs(const DevicePlan& d, int64_t first, int64_t count,
                              const KernelParams& kp, hipStream_t s)
 {
@@ -380,32 +446,29 @@ hipError_t launch_near_pairs(const DevicePlan& d, int64_t first, int64_t count,
     if (!d.sym_unit || !d.sym_out || first < 0 || first + count > d.sym_units)
         return hipErrorInvalidValue;
     const KernelConst kc = kp.kconst();
+    const bool mixed = kp.precision == 1;
+    if (mixed && (!d.src32 || !d.node_info || !d.batch_info))
+        return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(count));
     const SymUnit* units = d.sym_unit + first;
-    const size_t lds = 0;
-    if (kp.precision == 1) {
-        if (!d.src32 || !d.node_info || !d.batch_info)
-            return hipErrorInvalidValue;
-        if (kp.kernel == 1)
-            hipLaunchKernelGGL(near_pairs_mixed<1>, grid, dim3(64), lds, s, units, d.src,
-                               d.src32, d.node_info, d.batch_info, d.sym_out, kc);
-        else if (kp.kernel == 2)
-            hipLaunchKernelGGL(near_pairs_mixed<2>, grid, dim3(64), lds, s, units, d.src,
-                               d.src32, d.node_info, d.batch_info, d.sym_out, kc);
-        else
-            hipLaunchKernelGGL(near_pairs_mixed<0>, grid, dim3(64), lds, s, units, d.src,
-                               d.src32, d.node_info, d.batch_info, d.sym_out, kc);
+    const int waves = pair_waves(count, mixed);
+    const dim3 block(64 * waves);
+    const size_t lds = waves > 1 ? sizeof(double) * 64 * kChunks * waves : 0;
+#define X(KER, SHARED)                                                                            \
+    if (mixed)                                                                                    \
+        hipLaunchKernelGGL((near_pairs_mixed<KER, SHARED>), grid, block, lds, s, units, d.src,    \
+                           d.src32, d.node_info, d.batch_info, d.sym_out, kc);                    \
+    else                                                                                          \
+        hipLaunchKernelGGL((near_pairs_f64<KER, SHARED>), grid, block, lds, s, units, d.src,      \
+                           d.sym_out, kc);
+    if (kp.kernel == 1) {
+        if (waves > 1) { X(1, true) } else { X(1, false) }
+    } else if (kp.kernel == 2) {
+        if (waves > 1) { X(2, true) } else { X(2, false) }
     } else {
-        if (kp.kernel == 1)
-            hipLaunchKernelGGL(near_pairs_f64<1>, grid, dim3(64), lds, s, units, d.src,
-                               d.sym_out, kc);
-        else if (kp.kernel == 2)
-            hipLaunchKernelGGL(near_pairs_f64<2>, grid, dim3(64), lds, s, units, d.src,
-                               d.sym_out, kc);
-        else
-            hipLaunchKernelGGL(near_pairs_f64<0>, grid, dim3(64), lds, s, units, d.src,
-                               d.sym_out, kc);
+        if (waves > 1) { X(0, true) } else { X(0, false) }
     }
+#undef X
     return hipGetLastError();
 }
 
