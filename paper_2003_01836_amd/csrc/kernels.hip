@@ -84,7 +84,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void interact_f64(
     constexpr int NP = N + 1;
     constexpr int P = NP * NP * NP;
     extern __shared__ double lds[];
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg kappa{kc.kappa, kc.delta2, exp_tab};
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(64 * kDirectWaves) void direct_f64(
     int64_t q_ld, int64_t per, double* __restrict__ out, int64_t out_ld, int64_t out_piece,
     KernelConst kc)
 {
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     __shared__ double part[kDirectWaves][M][64];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);

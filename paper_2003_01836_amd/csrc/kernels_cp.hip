@@ -143,7 +143,7 @@ __global__ __launch_bounds__(64) void proxy_potentials(
     constexpr int P = NP2 * NP;
     constexpr int G = (NP + kProxyK1 - 1) / kProxyK1;
     constexpr int parts = proxy_parts<N>();
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg ka{kc.kappa, kc.delta2, exp_tab};

@@ -128,7 +128,7 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_f64(
     constexpr int NP = N + 1;
     constexpr int P8 = 8 * NP * NP * NP;
     extern __shared__ double lds[];
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg ka{kc.kappa, kc.delta2, exp_tab};
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_mixed(
     constexpr int NP = N + 1;
     constexpr int P8 = 8 * NP * NP * NP;
     extern __shared__ double lds[];
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg ka{kc.kappa, kc.delta2, exp_tab};

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     constexpr int NP = N + 1;
     constexpr int P = NP * NP * NP;
     extern __shared__ double lds[];
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg kappa{kc.kappa, kc.delta2, exp_tab};

@@ -603,7 +603,7 @@ template <int KER, int PREC>
 __global__ __launch_bounds__(64 * kMrhsWaves) __attribute__((amdgpu_waves_per_eu(PREC == 1 ? 4 : 2)))
 void interact_mrhs(MrhsDesc d, int32_t log_w)
 {
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     extern __shared__ double lds[];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
@@ -628,7 +628,7 @@ void interact_queue(const MrhsDesc* __restrict__ descs, const int2* __restrict__
                     int32_t nunits, int32_t log_w, int32_t* __restrict__ counter)
 {
     __shared__ int32_t next;
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     extern __shared__ double lds[];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);

@@ -266,7 +266,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void interact_multi(
     constexpr int NP = N + 1;
     constexpr int P = NP * NP * NP;
     extern __shared__ double lds[];
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     if constexpr (KER == 1)
         fill_exp2_table(exp_tab);
     const KernelArg kappa{a.kc.kappa, a.kc.delta2, exp_tab};

@@ -214,7 +214,7 @@ __global__ __launch_bounds__(SHARED ? 64 * kPairWaves : 64) __attribute__((amdgp
     const SymUnit* __restrict__ units, const double4* __restrict__ src, double* __restrict__ out,
     KernelConst kc)
 {
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     extern __shared__ double red[];
     const int w = SHARED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     const int waves = SHARED ? blockDim.x >> 6 : 1;
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(SHARED ? 64 * kPairWaves : 64) __attribute__((amdgp
     const float4* __restrict__ src32, const double4* __restrict__ node_info,
     const double4* __restrict__ batch_info, double* __restrict__ out, KernelConst kc)
 {
-    __shared__ double exp_tab[64];
+    __shared__ double exp_tab[kExpTable];
     extern __shared__ double red[];
     const int w = SHARED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     const int waves = SHARED ? blockDim.x >> 6 : 1;

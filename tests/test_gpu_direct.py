@@ -58,3 +58,23 @@ def test_direct_potentials_over_the_charges(dev, noalloc):
     got = bltc.direct(t, t, qd, out=qd, noalloc=noalloc)
     assert got.data_ptr() == qd.data_ptr()
     _check(oracle.direct(pos, pos, q[0]), got.cpu().numpy())
+
+
+@pytest.mark.parametrize("kappa", [1e-3, 0.5, 2.0, 30.0, 1e4])
+def test_yukawa_over_its_exponents(dev, kappa):
+    # one source: each value against exp(-kappa r^2 g) g with g the Coulomb value 1/r of
+    # the same pair (so the reciprocal square root's own error, one Newton step from the
+    # hardware's 2^-24, is left out), from exponents near 0 through every table entry
+    # to underflow; 16 half ulps of the value and of the exponent allowed
+    import paper_2003_01836_amd as bltc
+    x = np.concatenate([np.geomspace(1e-6, 800.0, 20011), [1e5, 1e12, 1e60]])   # kappa r
+    pos = np.zeros((x.size, 3))
+    pos[:, 0] = x / kappa
+    src = _soa(np.zeros((1, 3)), dev)
+    one = torch.ones(1, dtype=torch.float64, device=dev)
+    got = bltc.direct(_soa(pos, dev), src, one, kernel="yukawa", kappa=kappa).cpu().numpy().ravel()
+    g = bltc.direct(_soa(pos, dev), src, one).cpu().numpy().ravel().astype(np.longdouble)
+    r2 = pos[:, 0].astype(np.longdouble) ** 2
+    ref = (np.exp(-np.longdouble(kappa) * r2 * g) * g).astype(np.float64)
+    tol = 16.0 * (1.0 + x) * 2.0 ** -53
+    assert np.all(np.abs(got - ref) <= tol * ref + 1e-307)
