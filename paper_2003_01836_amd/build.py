@@ -66,6 +66,7 @@ def build(verbose: bool = False, defines=(), lib_path: str = LIB, build_dir: str
         "mrhs": os.path.join(build_dir, "kernels_mrhs.o"),
         "upward": os.path.join(build_dir, "kernels_upward.o"),
         "capi": os.path.join(build_dir, "capi.o"),
+        "pool": os.path.join(build_dir, "device_pool.o"),
         "batch": os.path.join(build_dir, "batch.o"),
         "autotune": os.path.join(build_dir, "autotune.o"),
         "setup": os.path.join(build_dir, "setup_gpu.o"),
@@ -88,6 +89,7 @@ def build(verbose: bool = False, defines=(), lib_path: str = LIB, build_dir: str
         [hipcc] + hip_flags + ["-mllvm", "-amdgpu-mfma-vgpr-form",
                                "-c", os.path.join(CSRC, "kernels_upward.hip"), "-o", objs["upward"]],
         [hipcc] + hip_flags + ["-x", "hip", "-c", os.path.join(CSRC, "capi.cpp"), "-o", objs["capi"]],
+        [hipcc] + hip_flags + ["-x", "hip", "-c", os.path.join(CSRC, "device_pool.cpp"), "-o", objs["pool"]],
         [hipcc] + hip_flags + ["-x", "hip", "-c", os.path.join(CSRC, "batch.cpp"), "-o", objs["batch"]],
         [hipcc] + hip_flags + ["-x", "hip", "-c", os.path.join(CSRC, "autotune.cpp"), "-o", objs["autotune"]],
         # geometric decisions (MAC) follow their formulas operation by operation

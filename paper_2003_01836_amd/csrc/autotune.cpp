@@ -132,9 +132,9 @@ int autotune_impl(const bltc_params* p, int64_t nt, const double* tx, const doub
     double best_t = 0.0;
     std::vector<double> ones(static_cast<size_t>(ns) * num_q, 1.0);
     do {
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(&q), ones.size() * sizeof(double));
+        hipError_t e = bltc::device_malloc(reinterpret_cast<void**>(&q), ones.size() * sizeof(double));
         if (e == hipSuccess)
-            e = hipMalloc(reinterpret_cast<void**>(&phi), static_cast<size_t>(nt) * num_q * sizeof(double));
+            e = bltc::device_malloc(reinterpret_cast<void**>(&phi), static_cast<size_t>(nt) * num_q * sizeof(double));
         if (e == hipSuccess)
             e = hipMemcpyAsync(q, ones.data(), ones.size() * sizeof(double), hipMemcpyHostToDevice, s);
         if (e == hipSuccess)

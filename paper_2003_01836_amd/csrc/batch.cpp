@@ -166,9 +166,9 @@ int batch_create(bltc_batch** out, bltc_plan* const* plans, int32_t count, void*
     if (e == hipSuccess)
         e = put(&b->d_updescs, ud);
     if (e == hipSuccess)
-        e = hipMalloc(reinterpret_cast<void**>(&b->d_descs), sizeof(bltc::MrhsDesc) * count);
+        e = bltc::device_malloc(reinterpret_cast<void**>(&b->d_descs), sizeof(bltc::MrhsDesc) * count);
     if (e == hipSuccess)
-        e = hipMalloc(reinterpret_cast<void**>(&b->d_counter), sizeof(int32_t));
+        e = bltc::device_malloc(reinterpret_cast<void**>(&b->d_counter), sizeof(int32_t));
     if (e == hipSuccess)
         e = bltc::upward_prepare(b->lds);
     if (e == hipSuccess) {

@@ -262,15 +262,16 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
     std::vector<int64_t> batch_end(d.nbatches);
     for (int64_t b = 0; b < d.nbatches; ++b)
         batch_end[b] = hp.batch_begin[b] + hp.batch_count[b];
-    HIP_TRY(plan->put(&d.group_batch, hp.group_batch, s));
-    HIP_TRY(plan->put(&d.group_first, hp.group_first, s));
-    HIP_TRY(plan->put(&d.batch_end, batch_end, s));
-    HIP_TRY(plan->put(&d.slot_nodes, hp.slot_nodes, s));
-    HIP_TRY(plan->put(&d.chunk_slot, hp.chunk_slot, s));
-    HIP_TRY(plan->put(&d.chunk_begin, hp.chunk_begin, s));
-    HIP_TRY(plan->put(&d.chunk_count, hp.chunk_count, s));
-    HIP_TRY(plan->put(&d.slot_chunk_off, hp.slot_chunk_off, s));
-    HIP_TRY(plan->put(&d.chunk_dst, hp.chunk_dst, s));
+    bltc::Pack pack;
+    HIP_TRY(plan->put(&d.group_batch, hp.group_batch, pack, s));
+    HIP_TRY(plan->put(&d.group_first, hp.group_first, pack, s));
+    HIP_TRY(plan->put(&d.batch_end, batch_end, pack, s));
+    HIP_TRY(plan->put(&d.slot_nodes, hp.slot_nodes, pack, s));
+    HIP_TRY(plan->put(&d.chunk_slot, hp.chunk_slot, pack, s));
+    HIP_TRY(plan->put(&d.chunk_begin, hp.chunk_begin, pack, s));
+    HIP_TRY(plan->put(&d.chunk_count, hp.chunk_count, pack, s));
+    HIP_TRY(plan->put(&d.slot_chunk_off, hp.slot_chunk_off, pack, s));
+    HIP_TRY(plan->put(&d.chunk_dst, hp.chunk_dst, pack, s));
     // modified charges (first nslots rows) and the partial rows of multi-chunk
     // clusters; [row][P] for one charge vector, [row][P][16] for several
     const size_t mw_max = plan->max_q > 1 ? 16 : 1;
@@ -279,6 +280,7 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
     if (d.hermite)
         HIP_TRY(plan->alloc(&d.qhat_h, static_cast<size_t>(d.nslots) * hp.P));
     const bool mixed = plan->prm.precision == BLTC_FP32_MIXED;
+    std::vector<double4> node_info, batch_info;
     if (plan->max_q > 1) {
         // expanded proxy grids for the multi-vector kernels
         const int32_t np = hp.np;
@@ -315,7 +317,7 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
     if (mixed) {
         // sources relative to the center of their leaf, per-node and per-batch boxes
         const int64_t nn = hp.src.nodes();
-        std::vector<double4> node_info(nn);
+        node_info.resize(nn);
         for (int64_t c = 0; c < nn; ++c)
             node_info[c] = make_double4(hp.src.center[3 * c], hp.src.center[3 * c + 1],
                                         hp.src.center[3 * c + 2], hp.src.radius[c]);
@@ -330,17 +332,17 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
             HIP_TRY(plan->put(&d.src32, src32, s));
             HIP_TRY(hipStreamSynchronize(s));
         }
-        std::vector<double4> batch_info(d.nbatches);
+        batch_info.resize(d.nbatches);
         for (int64_t b = 0; b < d.nbatches; ++b) {
             const int32_t bn = hp.batch_node[b];
             batch_info[b] = make_double4(hp.tgt.center[3 * bn], hp.tgt.center[3 * bn + 1],
                                          hp.tgt.center[3 * bn + 2], hp.tgt.radius[bn]);
         }
-        HIP_TRY(plan->put(&d.node_info, node_info, s));
-        HIP_TRY(plan->put(&d.batch_info, batch_info, s));
+        HIP_TRY(plan->put(&d.node_info, node_info, pack, s));
+        HIP_TRY(plan->put(&d.batch_info, batch_info, pack, s));
         HIP_TRY(plan->alloc(&d.qhat32, static_cast<size_t>(d.nslots) * hp.P));
-        HIP_TRY(hipStreamSynchronize(s));
     }
+    HIP_TRY(plan->send(pack, s));
     // host staging vectors die at return: finish the copies first
     HIP_TRY(hipStreamSynchronize(s));
     plan->uploaded = true;

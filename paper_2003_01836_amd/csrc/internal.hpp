@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "bltc.h"
+#include "device_pool.hpp"
 #include "kernels.hpp"
 #include "planner.hpp"
 
@@ -59,7 +60,7 @@ template <class T>
 hipError_t upload(T** dst, const std::vector<T>& v, hipStream_t s)
 {
     const size_t bytes = std::max<size_t>(1, v.size()) * sizeof(T);
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(dst), bytes);
+    hipError_t e = bltc::device_malloc(reinterpret_cast<void**>(dst), bytes);
     if (e != hipSuccess)
         return e;
     if (!v.empty())
@@ -131,7 +132,7 @@ struct bltc_plan {
     bool uploaded = false;
     int device = -1;
     bltc::DevicePlan d;
-    std::vector<void*> allocations;
+    bltc::DeviceBlocks memory;           // released with the plan
     bool timing = false;
     int32_t last_q = 0;                  // charge vectors of the last execution
     int32_t last_ld = 16;                // and the row length of its last pass's charges
@@ -169,12 +170,11 @@ struct bltc_plan {
             (void)hipEventDestroy(e);
         if (ev_pairs)
             (void)hipEventDestroy(ev_pairs);
-        for (void* p : allocations)
-            (void)hipFree(p);
     }
 
     // every device allocation of the plan: counted against its limit
-    hipError_t alloc_bytes(void** dst, size_t bytes_wanted)
+    // (padding, which the plan's own layout adds, is not)
+    hipError_t alloc_bytes(void** dst, size_t bytes_wanted, size_t padding = 0)
     {
         const size_t n = std::max<size_t>(1, bytes_wanted);
         if (limit > 0 && bytes + static_cast<int64_t>(n) > limit) {
@@ -186,11 +186,9 @@ struct bltc_plan {
             bltc_detail::limit_note() = buf;
             return hipErrorOutOfMemory;
         }
-        hipError_t e = hipMalloc(dst, n);
-        if (e == hipSuccess) {
-            allocations.push_back(*dst);
+        hipError_t e = memory.get(dst, n + padding);
+        if (e == hipSuccess)
             bytes += static_cast<int64_t>(n);
-        }
         return e;
     }
 
@@ -201,6 +199,22 @@ struct bltc_plan {
         if (e == hipSuccess && !v.empty())
             e = hipMemcpyAsync(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
         return e;
+    }
+
+    // as put, a small table with the others of the pack when that is sent
+    template <class T>
+    hipError_t put(T** dst, const std::vector<T>& v, bltc::Pack& pack, hipStream_t s)
+    {
+        return pack.add(dst, v) ? hipSuccess : put(dst, v, s);
+    }
+
+    hipError_t send(const bltc::Pack& pack, hipStream_t s)
+    {
+        if (pack.bytes() == 0)
+            return hipSuccess;
+        void* block = nullptr;
+        hipError_t e = alloc_bytes(&block, pack.wanted(), pack.bytes() - pack.wanted());
+        return e == hipSuccess ? pack.send(block, s) : e;
     }
 
     template <class T>

@@ -365,28 +365,22 @@ copy_targets(int64_t n, const double4* __restrict__ src, const int64_t* __restri
     tgt[i] = make_double4(p.x, p.y, p.z, __longlong_as_double(order[i]));
 }
 
-// device buffer that grows on demand (the stream is idle whenever it grows)
+// device buffer that grows on demand; its memory is the call's (mem)
 template <class T>
 struct Buf {
+    DeviceBlocks& mem;
     T* p = nullptr;
     size_t cap = 0;
-    ~Buf()
-    {
-        if (p)
-            (void)hipFree(p);
-    }
+    explicit Buf(DeviceBlocks& m) : mem(m) {}
     hipError_t reserve(size_t n)
     {
         n = std::max<size_t>(n, 1);
         if (n <= cap)
             return hipSuccess;
-        if (p)
-            (void)hipFree(p);
-        p = nullptr;
-        cap = 0;
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(&p), n * sizeof(T));
-        if (e == hipSuccess)
-            cap = n;
+        // at least doubled: the blocks outgrown stay held until the call returns
+        n = std::max(n, 2 * cap);
+        hipError_t e = mem.get(reinterpret_cast<void**>(&p), n * sizeof(T));
+        cap = e == hipSuccess ? n : 0;
         return e;
     }
     hipError_t put(const std::vector<T>& v, hipStream_t s)
@@ -396,7 +390,24 @@ struct Buf {
             e = hipMemcpyAsync(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
         return e;
     }
+    // a small table goes with the others of the pack when that is sent
+    hipError_t put(const std::vector<T>& v, Pack& pack, hipStream_t s)
+    {
+        if (!pack.add(&p, v))
+            return put(v, s);
+        cap = 0;   // the memory is the pack's
+        return hipSuccess;
+    }
 };
+
+hipError_t send(const Pack& pack, DeviceBlocks& mem, hipStream_t s)
+{
+    if (pack.bytes() == 0)
+        return hipSuccess;
+    void* block = nullptr;
+    hipError_t e = mem.get(&block, pack.bytes());
+    return e == hipSuccess ? pack.send(block, s) : e;
+}
 
 #define TB_TRY(call)                                                               \
     do {                                                                           \
@@ -428,19 +439,21 @@ std::string build_tree_device(Tree& t, int64_t n, const double* x, const double*
         return std::string();
     if (n > INT32_MAX)
         return "the device tree build takes at most 2^31 - 1 points";
-    Buf<double> bx[2], by[2], bz[2];
-    Buf<int32_t> bo[2];
+    DeviceBlocks mem;
+    Buf<double> bx[2]{Buf<double>(mem), Buf<double>(mem)}, by[2]{Buf<double>(mem), Buf<double>(mem)},
+        bz[2]{Buf<double>(mem), Buf<double>(mem)};
+    Buf<int32_t> bo[2]{Buf<int32_t>(mem), Buf<int32_t>(mem)};
     for (int k = 0; k < 2; ++k) {
         TB_TRY(bx[k].reserve(n));
         TB_TRY(by[k].reserve(n));
         TB_TRY(bz[k].reserve(n));
         TB_TRY(bo[k].reserve(n));
     }
-    Buf<unsigned long long> bad, box, cnt;
-    Buf<Chunk> chunks_d, split_chunks_d;
-    Buf<SplitNode> split_d;
-    Buf<int64_t> hist, offs;
-    Buf<FinalChunk> final_d;
+    Buf<unsigned long long> bad(mem), box(mem), cnt(mem);
+    Buf<Chunk> chunks_d(mem), split_chunks_d(mem);
+    Buf<SplitNode> split_d(mem);
+    Buf<int64_t> hist(mem), offs(mem);
+    Buf<FinalChunk> final_d(mem);
     const std::vector<unsigned long long> no_bad(1, ~0ull);
     TB_TRY(bad.put(no_bad, s));
     {
@@ -457,6 +470,7 @@ std::string build_tree_device(Tree& t, int64_t n, const double* x, const double*
     std::vector<SplitNode> split;
     std::vector<int32_t> split_node;        // tree id of each splitting node
     std::vector<unsigned long long> box_h, cnt_h;
+    Pack tables;                            // one level's; the level waits for its copy
     int cur = 0;
     bool first_level = true;
     while (!open.empty()) {
@@ -475,8 +489,10 @@ std::string build_tree_device(Tree& t, int64_t n, const double* x, const double*
         for (int64_t i = 0; i < nopen; ++i)
             for (int l = 0; l < 3; ++l)
                 box_h[6 * i + l] = ~0ull;
-        TB_TRY(chunks_d.put(chunks, s));
-        TB_TRY(box.put(box_h, s));
+        tables.clear();
+        TB_TRY(chunks_d.put(chunks, tables, s));
+        TB_TRY(box.put(box_h, tables, s));
+        TB_TRY(send(tables, mem, s));
         node_boxes<<<static_cast<uint32_t>(chunks.size()), kThreads, 0, s>>>(
             chunks_d.p, bx[cur].p, by[cur].p, bz[cur].p, box.p);
         TB_TRY(hipGetLastError());
@@ -537,9 +553,11 @@ std::string build_tree_device(Tree& t, int64_t n, const double* x, const double*
         // ---- counts, offsets, scatter into the other buffer set
         const int64_t nsplit = static_cast<int64_t>(split.size());
         cnt_h.assign(8 * nsplit, 0ull);
-        TB_TRY(split_d.put(split, s));
-        TB_TRY(split_chunks_d.put(split_chunks, s));
-        TB_TRY(cnt.put(cnt_h, s));
+        tables.clear();
+        TB_TRY(split_d.put(split, tables, s));
+        TB_TRY(split_chunks_d.put(split_chunks, tables, s));
+        TB_TRY(cnt.put(cnt_h, tables, s));
+        TB_TRY(send(tables, mem, s));
         TB_TRY(hist.reserve(hist_total));
         TB_TRY(offs.reserve(hist_total));
         const uint32_t nsc = static_cast<uint32_t>(split_chunks.size());
@@ -615,7 +633,7 @@ std::string build_tree_device(Tree& t, int64_t n, const double* x, const double*
     finish_points<<<static_cast<uint32_t>(fin.size()), kThreads, 0, s>>>(final_d.p, sets, order,
                                                                            pos, rel);
     TB_TRY(hipGetLastError());
-    // the scratch buffers are freed on return: finish first
+    // the scratch buffers are released on return: finish first
     TB_TRY(hipStreamSynchronize(s));
     return std::string();
 }
@@ -861,18 +879,22 @@ std::string build_lists_device(HostPlan& hp, DeviceLists& out, const DeviceAlloc
         leaf_count[i] = S.count[leaf_list[i]];
     }
 
-    Buf<TravNode> nodes_d;
-    Buf<TravBatch> batches_d;
-    Buf<int64_t> run_len_d, run_lo_d, run_hi_d, leaf_begin_d, leaf_count_d, item_off_d;
-    Buf<int32_t> leaf_list_d, far_off_d, near_off_d, slot_d;
-    Buf<ListCounts> counts_d;
-    Buf<uint8_t> used_d;
-    TB_TRY(nodes_d.put(nodes, s));
-    TB_TRY(batches_d.put(batches, s));
-    TB_TRY(run_len_d.put(run_len, s));
+    DeviceBlocks mem;
+    Buf<TravNode> nodes_d(mem);
+    Buf<TravBatch> batches_d(mem);
+    Buf<int64_t> run_len_d(mem), run_lo_d(mem), run_hi_d(mem), leaf_begin_d(mem),
+        leaf_count_d(mem), item_off_d(mem);
+    Buf<int32_t> leaf_list_d(mem), far_off_d(mem), near_off_d(mem), slot_d(mem);
+    Buf<ListCounts> counts_d(mem);
+    Buf<uint8_t> used_d(mem);
+    Pack walk;
+    TB_TRY(nodes_d.put(nodes, walk, s));
+    TB_TRY(batches_d.put(batches, walk, s));
+    TB_TRY(run_len_d.put(run_len, walk, s));
     TB_TRY(counts_d.reserve(nb));
     std::vector<uint8_t> zeros(nn, 0);
-    TB_TRY(used_d.put(zeros, s));
+    TB_TRY(used_d.put(zeros, walk, s));
+    TB_TRY(send(walk, mem, s));
     const uint32_t grid = static_cast<uint32_t>((nb + kListWaves - 1) / kListWaves);
     count_lists<<<grid, 64 * kListWaves, 0, s>>>(nb, batches_d.p, nodes_d.p,
                                                  static_cast<int32_t>(nn), hp.prm.theta, hp.P,
@@ -915,15 +937,17 @@ std::string build_lists_device(HostPlan& hp, DeviceLists& out, const DeviceAlloc
     TB_TRY(alloc(reinterpret_cast<void**>(&out.item_batch), out.n_items * sizeof(int32_t)));
     TB_TRY(alloc(reinterpret_cast<void**>(&out.item_cluster), out.n_items * sizeof(int32_t)));
     TB_TRY(alloc(reinterpret_cast<void**>(&out.item_kind), out.n_items * sizeof(int32_t)));
-    TB_TRY(item_off_d.put(item_off, s));
-    TB_TRY(far_off_d.put(hp.far_off, s));
-    TB_TRY(near_off_d.put(hp.near_off, s));
-    TB_TRY(slot_d.put(hp.cluster_slot, s));
-    TB_TRY(run_lo_d.put(run_lo, s));
-    TB_TRY(run_hi_d.put(run_hi, s));
-    TB_TRY(leaf_list_d.put(leaf_list, s));
-    TB_TRY(leaf_begin_d.put(leaf_begin, s));
-    TB_TRY(leaf_count_d.put(leaf_count, s));
+    Pack tables;
+    TB_TRY(item_off_d.put(item_off, tables, s));
+    TB_TRY(far_off_d.put(hp.far_off, tables, s));
+    TB_TRY(near_off_d.put(hp.near_off, tables, s));
+    TB_TRY(slot_d.put(hp.cluster_slot, tables, s));
+    TB_TRY(run_lo_d.put(run_lo, tables, s));
+    TB_TRY(run_hi_d.put(run_hi, tables, s));
+    TB_TRY(leaf_list_d.put(leaf_list, tables, s));
+    TB_TRY(leaf_begin_d.put(leaf_begin, tables, s));
+    TB_TRY(leaf_count_d.put(leaf_count, tables, s));
+    TB_TRY(send(tables, mem, s));
     ListOut o;
     o.item_off = item_off_d.p;
     o.far_off = far_off_d.p;

@@ -8,6 +8,7 @@
 #include <functional>
 #include <string>
 
+#include "device_pool.hpp"
 #include "planner.hpp"
 
 namespace bltc {

@@ -263,19 +263,11 @@ pair_results(int32_t nb, const SymBatch* __restrict__ batches, const SymOffsets*
 
 // device scratch of one call
 struct Scratch {
-    std::vector<void*> held;
-    ~Scratch()
-    {
-        for (void* p : held)
-            (void)hipFree(p);
-    }
+    DeviceBlocks mem;
     template <class T>
     hipError_t get(T** p, size_t n)
     {
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(p), std::max<size_t>(1, n) * sizeof(T));
-        if (e == hipSuccess)
-            held.push_back(*p);
-        return e;
+        return mem.get(reinterpret_cast<void**>(p), n * sizeof(T));
     }
     template <class T>
     hipError_t put(T** p, const std::vector<T>& v, hipStream_t s)
@@ -284,6 +276,20 @@ struct Scratch {
         if (e == hipSuccess && !v.empty())
             e = hipMemcpyAsync(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
         return e;
+    }
+    // a small table goes with the others of the pack when that is sent
+    template <class T>
+    hipError_t put(T** p, const std::vector<T>& v, Pack& pack, hipStream_t s)
+    {
+        return pack.add(p, v) ? hipSuccess : put(p, v, s);
+    }
+    hipError_t send(const Pack& pack, hipStream_t s)
+    {
+        if (pack.bytes() == 0)
+            return hipSuccess;
+        void* block = nullptr;
+        hipError_t e = mem.get(&block, pack.bytes());
+        return e == hipSuccess ? pack.send(block, s) : e;
     }
 };
 
@@ -323,8 +329,10 @@ hipError_t plan_symmetric_device(const DirectLists& dl, const DevicePlan& lists,
     int32_t *batch_of_d, *match;
     SymBatch* batches_d;
     SymCount* counts_d;
-    SYM_TRY(mem.put(&batch_of_d, batch_of, s));
-    SYM_TRY(mem.put(&batches_d, batches, s));
+    Pack tables;
+    SYM_TRY(mem.put(&batch_of_d, batch_of, tables, s));
+    SYM_TRY(mem.put(&batches_d, batches, tables, s));
+    SYM_TRY(mem.send(tables, s));
     SYM_TRY(mem.get(&match, ne));
     // the counts of the batches and the sub-units of each weight, one copy back
     std::vector<SymCount> counts(static_cast<size_t>(nb) +
@@ -403,8 +411,10 @@ hipError_t plan_symmetric_device(const DirectLists& dl, const DevicePlan& lists,
     SymOffsets* offs_d;
     int64_t* rows;
     int32_t* next_d;
-    SYM_TRY(mem.put(&offs_d, offs, s));
-    SYM_TRY(mem.put(&next_d, first, s));
+    Pack offsets;
+    SYM_TRY(mem.put(&offs_d, offs, offsets, s));
+    SYM_TRY(mem.put(&next_d, first, offsets, s));
+    SYM_TRY(mem.send(offsets, s));
     SYM_TRY(mem.get(&rows, ne));
     fill_pairs<<<grid, 64 * kSymWaves, 0, s>>>(n, batches_d, offs_d, lists.near_leaf, batch_of_d, match,
                                                sub, scale, next_d, out.near_leaf, out.near_begin,
