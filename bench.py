@@ -43,8 +43,9 @@ FLOPS_MUTUAL_PAIR = FLOPS_COULOMB + FLOPS_PAIR_EXTRA
 MFMA_F64_PEAK_TFLOPS = 78.6        # MI355X dense FP64 matrix peak
 KERNEL_SOURCES = {
     "upward_single": ["kernels_upward.hip", "kernels.hpp"],
-    "interact_mixed": ["kernels_mixed.hip", "device_mixed.hpp", "device_common.hpp", "kernels.hpp"],
-    "interact_f64": ["kernels.hip", "device_common.hpp", "kernels.hpp"],
+    "interact_mixed": ["kernels_mixed.hip", "device_mixed.hpp", "device_split.hpp",
+                       "device_common.hpp", "kernels.hpp"],
+    "interact_f64": ["kernels.hip", "device_split.hpp", "device_common.hpp", "kernels.hpp"],
     "near_pairs_mixed": ["kernels_sym.hip", "device_common.hpp", "kernels.hpp"],
     "near_pairs_f64": ["kernels_sym.hip", "device_common.hpp", "kernels.hpp"],
 }
