@@ -522,8 +522,7 @@ int execute(bltc_plan* plan, const double* q, int32_t num_q, int64_t q_ld, doubl
             HIP_TRY(mark(u, 2));
             double* const phi0 = phi + static_cast<int64_t>(m0) * phi_ld;
             plan->last_ld = ld;
-            HIP_TRY(kp.precision == BLTC_FP64 && d.degree <= bltc::kMultiMaxDegree
-                        ? bltc::launch_interact_multi(d, kp, phi0, phi_ld, mc, s)
+            HIP_TRY(ld < 16 ? bltc::launch_interact_multi(d, kp, phi0, phi_ld, mc, s)
                         : bltc::launch_interact_mrhs(d, kp, phi0, phi_ld, mc, s));
             HIP_TRY(mark(u, 3));
         }

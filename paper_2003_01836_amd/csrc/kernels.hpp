@@ -269,10 +269,12 @@ hipError_t launch_interact_mixed(const DevicePlan& d, const KernelParams& kp, do
 // d.qm/d.qm32 ([ns][ld], zero padded), their modified charges in d.qhat16
 // ([slot][P][ld]); ld = multi_ld(precision, mc).  phi[m * phi_ld + i], m < mc.
 //
-// FP64 passes with n <= 15 run on the vector units, a grid line of n + 1 <= 16
-// points per row of lanes, their charges packed to the next of 2, 4, 8, 16 a
-// source (2 vectors take 4.8 ms where 16 take 11.4, kernels_multi.hip); FP32-mixed
-// passes and n = 16 run on the matrix cores, whose tiles have 16 columns.
+// FP64 passes of at most 8 vectors with n <= 15 run on the vector units, a grid line
+// of n + 1 <= 16 points per row of lanes, their charges packed to the next of 2, 4, 8
+// a source; the others run on the matrix cores, whose tiles have 16 columns.  One
+// evaluation of 10^6 points, n = 8, 2000 a leaf, FP64 (10^4 points, n = 4, 500 a
+// leaf): 8 vectors 104 ms (0.13) on the vector units, 9 to 16 vectors 147 (0.17) on
+// the matrix cores against 163-167 (0.22) on the vector units.
 constexpr int32_t kMultiMaxDegree = 15;
 inline int32_t multi_ld(int32_t precision, int32_t degree, int32_t mc)
 {
@@ -283,7 +285,7 @@ hipError_t launch_gather_charges_multi(const DevicePlan& d, const double* q, int
 // on the matrix cores, ld = 16 (kernels_mrhs.hip)
 hipError_t launch_interact_mrhs(const DevicePlan& d, const KernelParams& kp, double* phi,
                                 int64_t phi_ld, int32_t mc, hipStream_t s);
-// in FP64 on the vector units, n <= kMultiMaxDegree (kernels_multi.hip)
+// in FP64 on the vector units, n <= kMultiMaxDegree, ld <= 8 (kernels_multi.hip)
 hipError_t launch_interact_multi(const DevicePlan& d, const KernelParams& kp, double* phi,
                                  int64_t phi_ld, int32_t mc, hipStream_t s);
 MrhsDesc make_mrhs_desc(const DevicePlan& d, const KernelParams& kp, double* phi, int64_t phi_ld,

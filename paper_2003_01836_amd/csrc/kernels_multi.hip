@@ -1,4 +1,4 @@
-// kernels_multi.hip -- FP64 batch/cluster interactions for 2 to 16 charge vectors
+// kernels_multi.hip -- FP64 batch/cluster interactions for up to 8 charge vectors
 // (eqs. 9 and 11 with a matrix of charges), on the vector units.
 //
 // The kernel values do not depend on the charge vector: each is formed once and
@@ -8,18 +8,21 @@
 // one-vector kernel.
 //
 // Why not the matrix cores: v_mfma_f64_16x16x4 contracts 64 kernel values with 16
-// vectors in 70 SIMD cycles, the 16 fused multiply-adds of a lane take the same
-// (4.4 cycles each), and the two units do not issue at the same time.  The vector
-// form pays for the vectors there are instead of for 16, and its far field forms
-// r^2 with one addition per value (separable grid in registers).
+// vectors in 70 SIMD cycles, the M fused multiply-adds of a lane take 4.4 cycles
+// each, and the two units do not issue at the same time.  The vector form pays for
+// the vectors there are, and its far field forms r^2 with one addition per value
+// (separable grid in registers).  At 16 vectors the contraction costs the same and
+// the matrix-core kernel needs no row loads: 10^6 uniform points, n = 8, 2000 a leaf,
+// 16 vectors 167 ms here, 147 there; 8 vectors 104 ms here.
 //
 // Charges: through the scalar cache (8 M bytes per value and wave) they bound the
 // kernel at its miss rate; 16 records in the 16 lanes of a row cost one vector
 // load per 16 values, and v_fmac_f64 takes its operand from any lane of the row.
 //
-// Measured (150,001 uniform points, n = 8, 293 a leaf; Coulomb), matrix cores ->
-// here: 3 vectors 14.4 -> 5.4 ms, 8 -> 7.0, 16 -> 11.4; the FP64 issue cost of the
-// terms is 4.1, 5.1 and 7.2 ms at full lanes (the leaves fill 91% of them).
+// Measured (150,001 uniform points, n = 8, 293 a leaf; Coulomb): 3 vectors 14.4 ms
+// on matrix-core tiles of one wave per 64 targets, 5.4 here, 8 vectors 7.0; the FP64
+// issue cost of the terms is 4.1 and 5.1 ms at full lanes (the leaves fill 91% of
+// them).
 #include <type_traits>
 
 #include "device_common.hpp"
@@ -74,10 +77,6 @@ __device__ __forceinline__ void fma_row(double (&acc)[M], const double (&q)[M], 
     }
 }
 
-// charges loaded a step ahead: 16 vectors of them would spill
-template <int M>
-constexpr bool kAhead = M <= 8;
-
 template <int M>
 __device__ __forceinline__ void load_row(const double* __restrict__ q, double (&v)[M])
 {
@@ -129,8 +128,7 @@ __device__ __forceinline__ void far_planes(double x, double y, double z,
     };
     double next[M], y2[L];
     lines(0, y2);
-    if (kAhead<M>)
-        load_row<M>(row(ka, 0), next);
+    load_row<M>(row(ka, 0), next);
 #pragma unroll 1
     for (int k1 = ka; k1 < kb; ++k1) {
         const double dx = x - nd[k1];
@@ -138,18 +136,12 @@ __device__ __forceinline__ void far_planes(double x, double y, double z,
 #pragma unroll 1
         for (int k2 = 0; k2 < NP; k2 += L) {
             double q[M];
-            if (kAhead<M>) {
 #pragma unroll
-                for (int m = 0; m < M; ++m)
-                    q[m] = next[m];
-            }
-            if (kAhead<M>) {
-                const bool same = k2 + L < NP;
-                const int n1 = same || k1 + 1 == kb ? k1 : k1 + 1;
-                load_row<M>(row(n1, same ? k2 + L : 0), next);
-            } else {
-                load_row<M>(row(k1, k2), q);
-            }
+            for (int m = 0; m < M; ++m)
+                q[m] = next[m];
+            const bool same = k2 + L < NP;
+            const int n1 = same || k1 + 1 == kb ? k1 : k1 + 1;
+            load_row<M>(row(n1, same ? k2 + L : 0), next);
             double ab2[L];
 #pragma unroll
             for (int l = 0; l < L; ++l) {
@@ -205,22 +197,17 @@ __device__ __forceinline__ void near_run(double x, double y, double z,
             r2[2 * e + 1] = square(p[e][4], p[e][5], p[e][6]);
         }
     };
-    if (kAhead<M>)
-        load_row<M>(q + (r < cnt ? r : cnt - 1) * M, next);
+    load_row<M>(q + (r < cnt ? r : cnt - 1) * M, next);
     if (cnt >= 16)
         quad(0);
     int32_t j0 = 0;
 #pragma unroll 1
     for (; j0 + 16 <= cnt; j0 += 16) {
-        if (!kAhead<M>)
-            load_row<M>(q + (j0 + r) * M, next);
 #pragma unroll
         for (int m = 0; m < M; ++m)
             v[m] = next[m];
-        if (kAhead<M>) {
-            const int32_t jn = j0 + 16 + r;
-            load_row<M>(q + (jn < cnt ? jn : cnt - 1) * M, next);
-        }
+        const int32_t jn = j0 + 16 + r;
+        load_row<M>(q + (jn < cnt ? jn : cnt - 1) * M, next);
         static_for<0, 4>([&](auto u) {
             double r2[4];
             squares(r2);
@@ -235,8 +222,6 @@ __device__ __forceinline__ void near_run(double x, double y, double z,
         });
     }
     if (j0 < cnt) {
-        if (!kAhead<M>)
-            load_row<M>(q + (j0 + r < cnt ? j0 + r : cnt - 1) * M, next);
 #pragma unroll
         for (int m = 0; m < M; ++m)
             v[m] = j0 + r < cnt ? next[m] : 0.0;   // lanes past the end: no charge
@@ -356,7 +341,6 @@ hipError_t run_multi_m(const DevicePlan& d, const MultiArgs& a, const GroupLaunc
     case 2: return run_multi<N, KER, 2>(d, a, gl, s);
     case 4: return run_multi<N, KER, 4>(d, a, gl, s);
     case 8: return run_multi<N, KER, 8>(d, a, gl, s);
-    case 16: return run_multi<N, KER, 16>(d, a, gl, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -368,10 +352,9 @@ hipError_t launch_interact_multi(const DevicePlan& d, const KernelParams& kp, do
 {
     if (d.ngroups == 0)
         return hipSuccess;
-    if (!d.qm || !d.qhat16 || mc < 1 || mc > 16)
+    if (!d.qm || !d.qhat16 || mc < 1 || mc > 8)
         return hipErrorInvalidValue;
-    // the sums of 16 vectors take 8 KB of LDS a wave: at most 8 of them
-    const GroupLaunch gl = group_launch(d, mc > 8 ? kMaxWaves / 2 : kMaxWaves);
+    const GroupLaunch gl = group_launch(d);
     const MultiArgs a{d.group_batch, d.group_first, d.batch_end, d.far_off, d.near_off,
                       phi, phi_ld, kp.kconst(), gl.log_w, mc};
     switch (d.degree) {
