@@ -256,13 +256,13 @@ __device__ __forceinline__ double far_sum_hermite_f32(double x, double y, double
     return acc;
 }
 
-// LDS staging of the FP32 modified charges at n = 4 (1000 values, 4 KB per
-// one-wave workgroup): 4% faster there; at n = 2 and 3 the two barriers per
-// cluster cost more than the scalar loads save, and at n = 6 the LDS size
-// costs occupancy, so the other degrees read the charges through the scalar
-// cache
+// LDS staging of the FP32 modified charges at n = 3 to 5 (a plane of LDS per wave,
+// 2 to 7 KB), the other degrees read them through the scalar cache.  Far field and
+// direct terms of 10^6 points, staged against not: n = 2 3.6 and 2.7 ms, n = 3 6.1
+// and 7.5, n = 4 7.9 and 8.6, n = 5 12.5 and 15.3, n = 6 (11 KB, fewer waves) 22.6
+// and 18.1
 template <int N>
-constexpr bool kStageHermite = N == 4;
+constexpr bool kStageHermite = N >= 3 && N <= 5;
 
 template <int N, int KER>
 __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_mixed(
