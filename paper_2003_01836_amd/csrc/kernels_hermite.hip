@@ -352,7 +352,12 @@ hipError_t run_interact_hermite_mixed(const DevicePlan& d, double* phi, KernelCo
     if (d.ngroups == 0)
         return hipSuccess;
     const NearLists nl = near_lists(d);
-    const GroupLaunch gl = group_launch(d, kHermiteWaves);
+    // Charges through the scalar cache: waves of different clusters evict each other's,
+    // so a launch that fills the chip (1024 SIMDs, 8 waves each) with one wave a group
+    // does not share lists beyond threads_per_target (10^6 points: n = 2 2.7 ms at 4
+    // waves, 2.4 at 1; n = 6 17.9 and 16.2)
+    const bool fills = !kStageHermite<N> && d.nt >= 64 * 8192;
+    const GroupLaunch gl = group_launch(d, fills ? std::max(1, d.threads_per_target) : kHermiteWaves);
     const size_t stage = kStageHermite<N> ? sizeof(float) * 8 * (N + 1) * (N + 1) * (N + 1) : 0;
     const size_t lds = std::max(stage, gl.log_w ? 64 * sizeof(double) : size_t(0)) << gl.log_w;
     hipLaunchKernelGGL((interact_hermite_mixed<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w), lds,
