@@ -274,7 +274,10 @@ int bltc_internal_direct(const bltc_params* p, int64_t nt, const double* tx, con
                          double* phi, int64_t phi_ld, const bltc::DirectSplit& split, double* part,
                          hipStream_t s);
 // Whether phi shares memory with an input (potentials written over the
-// charges): the sums then go through `part`, so that every input is read first.
+// charges).  The sums of a launch then go through `part`, so that it reads its
+// sources and its up to kDirectVectors charge vectors before it writes a
+// potential; potentials over what a later launch reads (coordinates, later
+// charge vectors) change what that launch computes.
 bool bltc_internal_direct_overlap(int64_t nt, const double* tx, const double* ty, const double* tz,
                                   int64_t ns, const double* sx, const double* sy, const double* sz,
                                   const double* q, int32_t num_q, int64_t q_ld, const double* phi,

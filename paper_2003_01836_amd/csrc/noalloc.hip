@@ -2,8 +2,9 @@
 //
 // bltc_direct keeps the partial sums of its source pieces in a buffer it
 // allocates per call.  bltc_direct_noalloc runs the same kernels with that
-// buffer in a file-scope device array of fixed size, so that callers that
-// cannot allocate (code under HIP graph capture,
+// buffer in a file-scope device array of fixed size (or with the sources in it,
+// where the potentials are written over an input and outnumber the array), so
+// that callers that cannot allocate (code under HIP graph capture,
 // serving loops, harnesses that forbid hipMalloc) can use it.  Every GPU the
 // library runs on holds its own copy of the array until the process ends; the
 // host side keeps each device's address of it (hipGetSymbolAddress, once per
@@ -68,16 +69,38 @@ extern "C" int bltc_direct_noalloc(const bltc_params* p, int64_t nt, const doubl
     rc = scratch_for_current_device(&part);
     if (rc != BLTC_OK)
         return rc;
+    hipStream_t s = static_cast<hipStream_t>(stream);
     // partial sums as in bltc_direct (no sources: the sum writes zeros)
     const bltc::DirectSplit split = bltc::direct_split(nt, ns);
     const bool fits = split.pieces * nt * std::min(num_q, bltc::kDirectVectors) <=
                       bltc::kDirectPartials;
-    if (split.pieces == 1 &&
-        !(fits && bltc_internal_direct_overlap(nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi,
-                                               phi_ld)))
-        part = nullptr;
-    else if (!fits)
-        return fail(BLTC_EINTERNAL, "direct-sum partials exceed the fixed array");
-    return bltc_internal_direct(p, nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi, phi_ld,
-                                split, part, static_cast<hipStream_t>(stream));
+    const bool overlap = bltc_internal_direct_overlap(nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld,
+                                                      phi, phi_ld);
+    if (split.pieces > 1 || (overlap && fits)) {
+        if (!fits)
+            return fail(BLTC_EINTERNAL, "direct-sum partials exceed the fixed array");
+        return bltc_internal_direct(p, nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi, phi_ld,
+                                    split, part, s);
+    }
+    if (!overlap)
+        return bltc_internal_direct(p, nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi, phi_ld,
+                                    split, nullptr, s);
+    // potentials written over an input, and too many of them for the array: it
+    // holds the sources and one charge vector at a time instead, and a target's
+    // coordinates are read by the workgroup that writes its potential
+    static_assert(4 * kNoAllocSources <= bltc::kDirectPartials, "x, y, z and charges fit");
+    double* const staged[4] = {part, part + ns, part + 2 * ns, part + 3 * ns};
+    const double* const xyz[3] = {sx, sy, sz};
+    for (int l = 0; l < 3 && ns > 0; ++l)
+        HIP_TRY(hipMemcpyAsync(staged[l], xyz[l], ns * sizeof(double), hipMemcpyDeviceToDevice, s));
+    for (int32_t m = 0; m < num_q; ++m) {
+        if (ns > 0)
+            HIP_TRY(hipMemcpyAsync(staged[3], q + m * q_ld, ns * sizeof(double),
+                                   hipMemcpyDeviceToDevice, s));
+        rc = bltc_internal_direct(p, nt, tx, ty, tz, ns, staged[0], staged[1], staged[2], staged[3], 1,
+                                  ns, phi + m * phi_ld, phi_ld, split, nullptr, s);
+        if (rc != BLTC_OK)
+            return rc;
+    }
+    return BLTC_OK;
 }
