@@ -218,10 +218,10 @@ __global__ __launch_bounds__(64 * kDirectWaves) void direct_f64(
 
 // phi[m phi_ld + i] = the pieces' partial sums of (m, i) in piece order
 __global__ __launch_bounds__(256) void sum_direct(const double* __restrict__ part, int64_t nt,
-                                                  int32_t m_count, int32_t pieces,
+                                                  int32_t m_count, int32_t pieces, int64_t k0,
                                                   double* __restrict__ phi, int64_t phi_ld)
 {
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t k = k0 + static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (k >= nt * m_count)
         return;
     double v = part[k];
@@ -327,23 +327,36 @@ hipError_t launch_direct(int64_t nt, const double* tx, const double* ty, const d
 {
     if (nt == 0)
         return hipSuccess;
-    const int64_t groups = (nt + 63) / 64;
-    if (m < 1 || m > kDirectVectors || groups > INT32_MAX || split.pieces > 65535 ||
-        (!part && split.pieces > 1))
+    if (m < 1 || m > kDirectVectors || split.pieces > 65535 || (!part && split.pieces > 1))
         return hipErrorInvalidValue;
-    const dim3 grid(static_cast<unsigned>(groups), static_cast<unsigned>(split.pieces));
     const KernelConst kc = kp.kconst();
     double* out = part ? part : phi;
     const int64_t out_ld = part ? nt : phi_ld;
     const auto run = kp.kernel == 1 ? run_direct<1> : kp.kernel == 2 ? run_direct<2> : run_direct<0>;
-    run(m, grid, s, nt, tx, ty, tz, ns, sx, sy, sz, q, q_ld, split.per, out, out_ld, nt * m, kc);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !part)
-        return e;
+    // a launch has fewer than 2^32 threads a dimension: 2^29 targets (2^31 threads)
+    // at a time, then 2^31 sums
+    constexpr int64_t kTargets = int64_t(1) << 29, kSums = int64_t(1) << 31;
+    for (int64_t t0 = 0; t0 < nt; t0 += kTargets) {
+        const int64_t n = std::min(kTargets, nt - t0);
+        const dim3 grid(static_cast<unsigned>((n + 63) / 64), static_cast<unsigned>(split.pieces));
+        run(m, grid, s, n, tx + t0, ty + t0, tz + t0, ns, sx, sy, sz, q, q_ld, split.per, out + t0,
+            out_ld, nt * m, kc);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    if (!part)
+        return hipSuccess;
     const int64_t total = nt * m;
-    hipLaunchKernelGGL(sum_direct, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s,
-                       part, nt, m, split.pieces, phi, phi_ld);
-    return hipGetLastError();
+    for (int64_t k0 = 0; k0 < total; k0 += kSums) {
+        const int64_t n = std::min(kSums, total - k0);
+        hipLaunchKernelGGL(sum_direct, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s,
+                           part, nt, m, split.pieces, k0, phi, phi_ld);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace bltc
