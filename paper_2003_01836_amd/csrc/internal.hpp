@@ -7,6 +7,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -76,11 +78,24 @@ inline double4 target_record(double x, double y, double z, int64_t index)
     return make_double4(x, y, z, w);
 }
 
-// the caller indices of n target records on the device
+// the caller indices of n target records on the device (whole records, a block at
+// a time: a strided copy of the fourth words goes row by row, 6.7 s for 10^6 targets
+// against 9 ms)
 inline hipError_t copy_target_order(int64_t* out, const double4* tgt, int64_t n)
 {
-    return hipMemcpy2D(out, sizeof(int64_t), &tgt->w, sizeof(double4), sizeof(int64_t),
-                       static_cast<size_t>(n), hipMemcpyDeviceToHost);
+    constexpr int64_t kBlock = int64_t(1) << 18;   // 8 MiB
+    const std::unique_ptr<double4[]> rec(new (std::nothrow) double4[std::min(n, kBlock)]);
+    if (!rec)
+        return hipErrorOutOfMemory;
+    for (int64_t i = 0; i < n; i += kBlock) {
+        const int64_t m = std::min(kBlock, n - i);
+        const hipError_t e = hipMemcpy(rec.get(), tgt + i, m * sizeof(double4), hipMemcpyDeviceToHost);
+        if (e != hipSuccess)
+            return e;
+        for (int64_t k = 0; k < m; ++k)
+            std::memcpy(out + i + k, &rec[k].w, sizeof(int64_t));
+    }
+    return hipSuccess;
 }
 
 }  // namespace bltc_detail
