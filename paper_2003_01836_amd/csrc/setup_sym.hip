@@ -6,7 +6,8 @@
 // here, over the direct lists that are on the device anyway.
 //
 //  1. match: for every entry (b, leaf c) the entry (c, leaf b), if there is one
-//     (c's list searched by the lane), and per-batch counts;
+//     (c's list bisected by the lane: the lists are in depth-first order, so the
+//     first sources of their leaves ascend), and per-batch counts;
 //  2. the host adds up the counts of the batches and sizes the arrays;
 //  3. fill: the entries that stay, in list order; for the lower batch of a pair its
 //     sub-units and the offsets of its rows and column blocks;
@@ -45,7 +46,7 @@ struct SymCount {
     int64_t cut;          // direct evaluations per target taken out of its lists
     int64_t largest;      // result values of its largest unit
     int32_t kept, units, results;
-    int32_t bad;          // an entry that is no batch's leaf
+    int32_t bad;          // an entry that is no batch's leaf, or out of order
 };
 
 struct SymOffsets {
@@ -95,7 +96,8 @@ __global__ void __launch_bounds__(256) clear_buckets(int32_t* __restrict__ hist)
 
 __global__ void __launch_bounds__(64 * kSymWaves)
 match_pairs(int32_t nb, const SymBatch* __restrict__ batches, const int32_t* __restrict__ near_leaf,
-            const int32_t* __restrict__ batch_of, int64_t sub, double scale,
+            const int64_t* __restrict__ near_begin, const int32_t* __restrict__ batch_of, int64_t sub,
+            double scale,
             int32_t* __restrict__ match, SymCount* __restrict__ counts, int32_t* __restrict__ hist)
 {
     const int32_t b = blockIdx.x * kSymWaves + threadIdx.x / 64;
@@ -108,15 +110,19 @@ match_pairs(int32_t nb, const SymBatch* __restrict__ batches, const int32_t* __r
     for (int32_t e = B.off + lane; e < end; e += 64) {
         const int32_t c = batch_of[near_leaf[e]];
         int32_t at = -1;
-        if (c < 0) {
+        if (c < 0 || (e > B.off && near_begin[e] <= near_begin[e - 1])) {
             bad = 1;
         } else if (c != b) {
-            const int32_t last = batches[c + 1].off;
-            for (int32_t k = batches[c].off; k < last; ++k)
-                if (near_leaf[k] == B.node) {
-                    at = k;
-                    break;
-                }
+            int32_t k = batches[c].off, last = batches[c + 1].off;
+            while (k < last) {
+                const int32_t mid = k + (last - k) / 2;
+                if (near_begin[mid] < B.begin)
+                    k = mid + 1;
+                else
+                    last = mid;
+            }
+            if (k < batches[c + 1].off && near_leaf[k] == B.node)
+                at = k;
         }
         match[e] = at;
         if (at < 0) {
@@ -347,8 +353,8 @@ hipError_t plan_symmetric_device(const DirectLists& dl, const DevicePlan& lists,
     const double scale = kBuckets / (static_cast<double>(std::min(sub, most)) * most + 1.0);
     const uint32_t grid = static_cast<uint32_t>((nb + kSymWaves - 1) / kSymWaves);
     const int32_t n = static_cast<int32_t>(nb);
-    match_pairs<<<grid, 64 * kSymWaves, 0, s>>>(n, batches_d, lists.near_leaf, batch_of_d, sub, scale,
-                                                match, counts_d, hist_d);
+    match_pairs<<<grid, 64 * kSymWaves, 0, s>>>(n, batches_d, lists.near_leaf, lists.near_begin, batch_of_d,
+                                                sub, scale, match, counts_d, hist_d);
     SYM_TRY(hipGetLastError());
     SYM_TRY(hipMemcpyAsync(counts.data(), counts_d, counts.size() * sizeof(SymCount),
                            hipMemcpyDeviceToHost, s));
