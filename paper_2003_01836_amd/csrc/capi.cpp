@@ -211,7 +211,7 @@ void schedule_single_vector(bltc_plan* plan)
     }
     bltc::group_schedule(hp.batch_begin, hp.batch_count, cost, hp.prm.group_size,
                          hp.prm.xcds, hp.group_batch, hp.group_first);
-    plan->d.ngroups = static_cast<int64_t>(hp.group_batch.size());
+    plan->d.set_groups(hp.group_batch);
 }
 
 }  // namespace
@@ -229,7 +229,7 @@ int upload_particle_cluster(bltc_plan* plan, hipStream_t s)
     d.ns = hp.src.n;
     d.nslots = static_cast<int64_t>(hp.slot_cluster.size());
     d.nchunks = static_cast<int64_t>(hp.chunk_slot.size());
-    d.ngroups = static_cast<int64_t>(hp.group_batch.size());
+    d.set_groups(hp.group_batch);
     d.nbatches = static_cast<int64_t>(hp.batch_begin.size());
     d.threads_per_target = std::max(1, plan->prm.threads_per_target);
 
@@ -906,6 +906,13 @@ int bltc_internal_direct(const bltc_params* p, int64_t nt, const double* tx, con
 }
 
 extern "C" {
+
+// the waves of an interaction workgroup (group_log_waves), for the tests
+int32_t bltc_internal_waves(int64_t targets, int64_t groups, int32_t asked, int32_t max_waves,
+                            int32_t early)
+{
+    return 1 << bltc::group_log_waves(targets, groups, asked, max_waves, early != 0);
+}
 
 void bltc_params_default(bltc_params* p)
 {

@@ -171,7 +171,7 @@ int upload(bltc_plan* plan, hipStream_t s)
     px.ns = dd.ns = ns;
     px.nt = nts * P;
     px.nbatches = nts;
-    px.ngroups = static_cast<int64_t>(cc.pg_batch.size());
+    px.set_groups(cc.pg_batch);
     HIP_TRY(plan->put(&px.tgt, tgrid, s));
     HIP_TRY(plan->put(&px.group_batch, cc.pg_batch, s));
     HIP_TRY(plan->put(&px.group_first, cc.pg_first, s));
@@ -189,7 +189,7 @@ int upload(bltc_plan* plan, hipStream_t s)
     // ---- targets by target leaf
     dd.nt = nt;
     dd.nbatches = ntl;
-    dd.ngroups = static_cast<int64_t>(cc.dg_batch.size());
+    dd.set_groups(cc.dg_batch);
     HIP_TRY(plan->put(&dd.group_batch, cc.dg_batch, s));
     HIP_TRY(plan->put(&dd.group_first, cc.dg_first, s));
     HIP_TRY(plan->put(&dd.batch_end, leaf_end, s));
@@ -249,7 +249,7 @@ int upload(bltc_plan* plan, hipStream_t s)
                                  cc.prm.xcds, cc.dg_batch, cc.dg_first);
             HIP_TRY(plan->put(&dd.group_batch, cc.dg_batch, s));
             HIP_TRY(plan->put(&dd.group_first, cc.dg_first, s));
-            dd.ngroups = static_cast<int64_t>(cc.dg_batch.size());
+            dd.set_groups(cc.dg_batch);
         }
     }
     // host staging vectors die at return: finish the copies first

@@ -209,7 +209,7 @@ int upload(bltc_plan* plan, hipStream_t s)
     dd.nt = nt;
     dd.nslots = 0;
     dd.nbatches = ntl;
-    dd.ngroups = static_cast<int64_t>(cp.dg_batch.size());
+    dd.set_groups(cp.dg_batch);
     HIP_TRY(plan->put(&dd.group_batch, cp.dg_batch, s));
     HIP_TRY(plan->put(&dd.group_first, cp.dg_first, s));
     HIP_TRY(plan->put(&dd.batch_end, leaf_end, s));
@@ -268,7 +268,7 @@ int upload(bltc_plan* plan, hipStream_t s)
                                  cp.prm.xcds, cp.dg_batch, cp.dg_first);
             HIP_TRY(plan->put(&dd.group_batch, cp.dg_batch, s));
             HIP_TRY(plan->put(&dd.group_first, cp.dg_first, s));
-            dd.ngroups = static_cast<int64_t>(cp.dg_batch.size());
+            dd.set_groups(cp.dg_batch);
         }
     }
     // host staging vectors die at return: finish the copies first

@@ -259,7 +259,7 @@ hipError_t run_interact(const DevicePlan& d, double* phi, KernelConst kc, hipStr
     if (d.ngroups == 0)
         return hipSuccess;
     const NearLists nl = near_lists(d);
-    const GroupLaunch gl = group_launch(d);
+    const GroupLaunch gl = group_launch(d, kMaxWaves, true);
     hipLaunchKernelGGL((interact_f64<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w),
                        gl.log_w ? sizeof(double) * (64u << gl.log_w) : 0, s,
                        gl.log_w, d.tgt, d.src, d.group_batch,

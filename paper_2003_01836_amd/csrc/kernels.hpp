@@ -3,7 +3,9 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <vector>
 
 namespace bltc {
 
@@ -50,6 +52,12 @@ struct DevicePlan {
     int32_t degree = 0;
     int32_t hermite = 0;              // Hermite interpolation: 8 (n+1)^3 values per slot
     int64_t nt = 0, ns = 0, nslots = 0, nchunks = 0, ngroups = 0, nbatches = 0;
+    int64_t groups = 0;               // of the ngroups workgroups, those with targets
+    void set_groups(const std::vector<int32_t>& batch)   // the schedule's group_batch
+    {
+        ngroups = static_cast<int64_t>(batch.size());
+        groups = ngroups - std::count(batch.begin(), batch.end(), -1);
+    }
     // sources in tree order: x, y, z, charge of the current vector
     double4* src = nullptr;
     // targets in batch order: x, y, z, caller index (int64 bits)
@@ -113,32 +121,60 @@ struct DevicePlan {
     double* sym_acc = nullptr;
 };
 
-// Launch of a single-vector interaction kernel: a workgroup of 1 << log_w waves
-// per group of the schedule.
+// Launch of an interaction kernel: a workgroup of 1 << log_w waves per group of the
+// schedule.
 //
 // Waves per workgroup: a target's lists are one serial chain per lane, so a
-// problem of few targets leaves the chip (1024 SIMDs, up to 8 waves each) idle,
-// and one of many ends in a tail as long as its heaviest workgroup.  The waves
-// are doubled until about kWavesWanted of them are launched (four times what is
-// resident), up to 8 per workgroup, or 16 where 8 would still leave SIMDs with
-// less than four waves: 16 waves leave slots of a CU unused when the registers
-// allow fewer than 32 (Yukawa at n = 6, 2 10^5 targets: 17.5 ms at 16, 16.3 at 8,
-// 21.4 at 1; 30,011 regularized targets: 14.0 ms at 1, 3.2 at 16).
+// problem of few targets leaves the chip (1024 SIMDs, up to 8 waves each: 8192
+// resident) idle, and one of many ends in a tail as long as its heaviest workgroup.
+// 16 waves leave slots of a CU unused when the registers allow fewer than 32, 2 were
+// not faster than 1 and 4 anywhere.  One evaluation at 1, 2, 4, 8, 16 waves, ms:
+//   512 groups (30,011 regularized targets) 14.0 at 1, 3.2 at 16; 3.5 10^3 groups
+//   (2 10^5 Yukawa targets, n = 6) 21.4 at 1, 16.3 at 8, 17.5 at 16
+//   8100 (5 10^5 points, n = 4) FP64 5.82 5.76 5.68 5.96 7.01, eight vectors 11.9 12.0
+//   11.4 11.3 13.0
+//   20,480 (1.1 10^6) FP64 12.85 12.77 12.76 13.06, three vectors 22.6 22.9 22.1 22.1
+//   32,768 (2 10^6) FP64 30.3 30.4 30.3 31.8, three vectors 50.3 51.0 49.8 49.8
+// So the FP64 one-vector and the Hermite kernels (`early`) go from 8 to 4 waves a
+// little below the resident waves, in groups; the others at as many full groups.
+// Groups less than half full on average (small leaves) have lists of many short
+// entries, and every wave's search for its cuts weighs more, so fewer waves share:
+//   1.3 10^3 groups (3 10^4 points, 64 a leaf) FP32-mixed 0.235 0.201 0.187 0.153 0.126,
+//   FP64 0.260 0.209 0.169 0.152 0.168
+//   3.7 10^3 (3 10^4 points, 32 a leaf) FP32-mixed 0.286 0.267 0.282 0.305 0.311, FP64
+//   0.417 0.392 0.374 0.359 0.423
+//   3.1 10^4 (10^5 points, 8 a leaf) FP32-mixed 3.15 3.16 3.39 4.10 5.41
 constexpr int64_t kWavesWanted = 32768;
-constexpr int64_t kWavesFew = 4096;
+constexpr int64_t kWavesResident = 8192;
+constexpr int64_t kGroupsFill = kWavesResident * 7 / 8;   // groups that nearly fill the chip
+inline int32_t group_log_waves(int64_t targets, int64_t groups, int32_t asked, int32_t max_waves,
+                               bool early)
+{
+    const int64_t full = (targets + 63) / 64;   // groups if all were full
+    int32_t log_w;
+    if (full < 512 && groups < 1536)
+        log_w = 4;
+    else if (groups > 2 * full)
+        log_w = groups < kWavesResident / 4 ? 3 : groups < kGroupsFill ? 2 : 0;
+    else if (early ? groups < kGroupsFill : full < kWavesResident)
+        log_w = 3;
+    else
+        log_w = full < kWavesWanted ? 2 : 0;
+    while ((1 << log_w) > max_waves)
+        --log_w;
+    while ((1 << log_w) < asked && (2 << log_w) <= max_waves)
+        ++log_w;
+    return log_w;
+}
 struct GroupLaunch {
     uint32_t blocks;
     int32_t log_w;
 };
-inline GroupLaunch group_launch(const DevicePlan& d, int max_waves = kMaxWaves)
+inline GroupLaunch group_launch(const DevicePlan& d, int32_t max_waves = kMaxWaves,
+                                bool early = false)
 {
-    GroupLaunch g{static_cast<uint32_t>(d.ngroups), 0};
-    const int64_t targets = (d.nt + 63) / 64;
-    while ((2 << g.log_w) <= max_waves &&
-           ((1 << g.log_w) < d.threads_per_target ||
-            (targets << g.log_w) < (g.log_w < 3 ? kWavesWanted : kWavesFew)))
-        ++g.log_w;
-    return g;
+    return GroupLaunch{static_cast<uint32_t>(d.ngroups),
+                       group_log_waves(d.nt, d.groups, d.threads_per_target, max_waves, early)};
 }
 
 // Constants of the kernel G passed to the interaction kernels: kappa of the
