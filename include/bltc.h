@@ -143,7 +143,9 @@ typedef struct {
                                  /* BLTC_PARTICLE_CLUSTER and BLTC_HERMITE with         */
                                  /* max_q = 1 only.  0: picked by the tuner among 1, 2, */
                                  /* 4 for those plans when created from device          */
-                                 /* coordinates; one lane otherwise                     */
+                                 /* coordinates; one lane otherwise.  A plan left to    */
+                                 /* the tuner for several vectors is tuned on passes of */
+                                 /* min(max_q, 16)                                      */
     int32_t method;              /* bltc_method                                         */
     double delta;                /* BLTC_REGULARIZED_COULOMB length, >= 0               */
     int32_t no_symmetry;         /* 0: when the targets are the sources (same arrays,   */
@@ -363,11 +365,11 @@ void bltc_batch_destroy(bltc_batch* batch);
  * into out->leaf_size and out->batch_size (the other fields are copied from
  * *p) and its device time into *best_ms.  For BLTC_PARTICLE_CLUSTER and
  * BLTC_HERMITE with num_q = 1 and p->threads_per_target = 0 it then times 2
- * and 4 threads per target at that size and writes the fastest of 1, 2, 4
- * into out->threads_per_target.  With use_cache != 0 the choice is looked up
+ * and 4 threads per target at that size, where they change the launch, and
+ * writes the fastest of 1, 2, 4 into out->threads_per_target.  With use_cache != 0 the choice is looked up
  * in / appended to a text cache keyed by the problem class (method, log2 of
- * the counts, theta, degree, kernel, precision, one or several vectors,
- * whether threads per target are searched); the file is
+ * the counts, theta, degree, kernel, precision, the vectors of a pass
+ * rounded up as they are evaluated, whether threads per target are searched); the file is
  * $BLTC_TUNE_CACHE, else $HOME/.bltc_tune_cache.  Synchronises `stream`.
  * Theta and n set the accuracy; the leaf size only moves which pairs are
  * approximated.  Candidates below (n+1)^3 can never be approximated as

@@ -6,10 +6,11 @@
 // one evaluation of each on the GPU (HIP events on the caller's stream, after
 // one warm-up), and keeps the fastest; for one-vector BLTC and Hermite plans
 // whose threads per target are left to it (0) it then times 2 and 4 lanes
-// per target at that size and keeps the fastest of 1, 2, 4.  Choices are
+// per target at that size, where they change the launch, and keeps the fastest
+// of 1, 2, 4 (1 where they do not).  Choices are
 // cached in a text file keyed by the problem class (method, log2 of the
-// particle counts, theta, degree, kernel and its parameter, precision, one or
-// several charge vectors), so later calls with a
+// particle counts, theta, degree, kernel and its parameter, precision, the padded
+// number of charge vectors of a pass), so later calls with a
 // similar problem skip the search.  The accuracy of the treecode is set by
 // theta and n; the leaf size changes which pairs are approximated and hence
 // the error slightly, never the bound the MAC enforces.
@@ -41,10 +42,11 @@ std::string cache_path()
 std::string class_key(const bltc_params* p, int64_t nt, int64_t ns, int32_t num_q)
 {
     std::ostringstream k;
-    k << "v2 nt2=" << (nt > 0 ? static_cast<int>(std::lround(std::log2(static_cast<double>(nt)))) : 0)
+    k << "v3 nt2=" << (nt > 0 ? static_cast<int>(std::lround(std::log2(static_cast<double>(nt)))) : 0)
       << " ns2=" << (ns > 0 ? static_cast<int>(std::lround(std::log2(static_cast<double>(ns)))) : 0)
       << " theta=" << p->theta << " n=" << p->degree << " kernel=" << p->kernel
-      << " prec=" << p->precision << " q=" << (num_q > 1 ? 16 : 1) << " method=" << p->method
+      << " prec=" << p->precision
+      << " q=" << (num_q > 1 ? bltc::multi_ld(p->precision, p->degree, num_q) : 1) << " method=" << p->method
       << " delta=" << p->delta << " kappa=" << p->kappa;
     return k.str();
 }
@@ -128,7 +130,7 @@ int autotune_impl(const bltc_params* p, int64_t nt, const double* tx, const doub
     double* phi = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = BLTC_OK;
-    int32_t best = -1, best_tpt = 1;
+    int32_t best = -1, best_tpt = 1, best_waves = 1;
     double best_t = 0.0;
     std::vector<double> ones(static_cast<size_t>(ns) * num_q, 1.0);
     do {
@@ -146,7 +148,8 @@ int autotune_impl(const bltc_params* p, int64_t nt, const double* tx, const doub
             break;
         }
         // candidate sizes at the caller's threads per target, then (tune_tpt)
-        // 2 and 4 lanes per target at the best size
+        // 2 and 4 lanes per target at the best size, unless as many waves share
+        // the lists anyway
         const int32_t nsteps = ncand + (tune_tpt ? 2 : 0);
         for (int32_t c = 0; c < nsteps && rc == BLTC_OK; ++c) {
             bltc_params trial = *p;
@@ -157,6 +160,8 @@ int autotune_impl(const bltc_params* p, int64_t nt, const double* tx, const doub
                 trial.batch_size = leaf;
             }
             trial.threads_per_target = tpt;
+            if (c >= ncand && tpt <= best_waves)
+                continue;
             bltc_plan* plan = nullptr;
             rc = bltc_plan_create(&plan, &trial, nt, tx, ty, tz, ns, sx, sy, sz,
                                   num_q > 1 ? 16 : 1, stream);
@@ -177,8 +182,11 @@ int autotune_impl(const bltc_params* p, int64_t nt, const double* tx, const doub
                 if (e != hipSuccess)
                     rc = bltc_detail::hip_fail(e, "autotune timing");
             }
+            const int32_t waves = bltc::one_vector_waves(plan->d, trial.precision);
             bltc_plan_destroy(plan);
             if (rc == BLTC_OK && (best < 0 || ms < best_t)) {
+                if (c < ncand)
+                    best_waves = waves;
                 best = leaf;
                 best_tpt = std::max(1, tpt);
                 best_t = ms;
@@ -240,7 +248,7 @@ int bltc_internal_tune(const bltc_params* p, int64_t nt, const double* tx, const
                        const double* sz, int32_t max_q, bltc_params* out, void* stream)
 {
     static const int32_t kSizes[] = {1000, 2000, 3000, 4000};
-    const int32_t num_q = max_q > 1 ? 16 : 1;
+    const int32_t num_q = std::min(max_q, 16);   // a pass of the plan
     const bool tpt_open = p->threads_per_target == 0 && max_q == 1 &&
                           (p->method == BLTC_PARTICLE_CLUSTER || p->method == BLTC_HERMITE);
     *out = *p;

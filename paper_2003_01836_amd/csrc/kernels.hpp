@@ -177,6 +177,31 @@ inline GroupLaunch group_launch(const DevicePlan& d, int32_t max_waves = kMaxWav
                        group_log_waves(d.nt, d.groups, d.threads_per_target, max_waves, early)};
 }
 
+// Hermite kernels: up to 256 VGPRs a wave (the larger degrees need over 128).  The
+// FP32-mixed one stages the charges of a cluster in LDS at n = 3 to 5.
+constexpr int kHermiteWaves = 8;
+constexpr bool stage_hermite(int32_t degree) { return degree >= 3 && degree <= 5; }
+// Charges through the scalar cache: waves of different clusters evict each other's,
+// so the lists are shared by fewer waves the more of the chip (8192 waves) the
+// groups fill by themselves.  1, 2, 4, 8 waves, ms: 2048 groups (10^5 points, n = 2)
+// 1.76 1.15 0.83 0.64; 3584 (2 10^5, n = 6) 4.81 4.49 4.35 4.59; 5632 (3.5 10^5)
+// n = 6 7.09 6.74 6.99 7.31, n = 7 8.35 7.80 8.11 8.51; 8100 (5 10^5) n = 1 1.47 1.53
+// 1.54 1.58, n = 2 2.93 2.99 3.01 3.16, n = 6 11.8 11.9 12.4 12.7, n = 7 13.0 13.3 13.9
+// 14.5, n = 8 16.2 16.1 17.0 17.9, but 7872 n = 9 33.7 31.1 31.2 31.7; 10^6 points n = 6
+// to 10 5% less at 1 than at 4.
+inline int32_t hermite_mixed_waves(const DevicePlan& d)
+{
+    return stage_hermite(d.degree) || d.groups < 3072 ? kHermiteWaves : d.groups < 8000 ? 4 : 1;
+}
+
+// Waves that the one-vector kernel of a plan takes when no lanes are asked for (the
+// FP32-mixed one may take 16 for 8).  Lanes asked for up to this many change nothing.
+inline int32_t one_vector_waves(const DevicePlan& d, int32_t precision)
+{
+    const int32_t most = d.hermite && precision == 1 ? hermite_mixed_waves(d) : kHermiteWaves;
+    return 1 << group_log_waves(d.nt, d.groups, 1, most, d.hermite || precision == 0);
+}
+
 // Constants of the kernel G passed to the interaction kernels: kappa of the
 // Yukawa kernel and delta^2 of the regularized Coulomb kernel.
 struct KernelConst {

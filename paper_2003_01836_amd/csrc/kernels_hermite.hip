@@ -28,9 +28,6 @@ namespace {
 
 using namespace dev;
 
-// waves of a workgroup: up to 256 VGPRs each (the larger degrees need over 128)
-constexpr int kHermiteWaves = 8;
-
 // G, g1, g2, g3 at r^2 > 0 (well-separated points; 1/sqrt by one Newton step)
 template <int KER>
 __device__ __forceinline__ void green_derivatives(double r2, const KernelArg& ka, double& g0,
@@ -262,7 +259,7 @@ __device__ __forceinline__ double far_sum_hermite_f32(double x, double y, double
 // and 7.5, n = 4 7.9 and 8.6, n = 5 12.5 and 15.3, n = 6 (11 KB, fewer waves) 22.6
 // and 18.1
 template <int N>
-constexpr bool kStageHermite = N >= 3 && N <= 5;
+constexpr bool kStageHermite = stage_hermite(N);
 
 template <int N, int KER>
 __global__ __launch_bounds__(64 * kHermiteWaves) void interact_hermite_mixed(
@@ -352,18 +349,8 @@ hipError_t run_interact_hermite_mixed(const DevicePlan& d, double* phi, KernelCo
     if (d.ngroups == 0)
         return hipSuccess;
     const NearLists nl = near_lists(d);
-    // Charges through the scalar cache: waves of different clusters evict each other's,
-    // so the lists are shared by fewer waves the more of the chip (8192 waves) the
-    // groups fill by themselves.  1, 2, 4, 8 waves, ms: 2048 groups (10^5 points, n = 2)
-    // 1.76 1.15 0.83 0.64; 3584 (2 10^5, n = 6) 4.81 4.49 4.35 4.59; 5632 (3.5 10^5)
-    // n = 6 7.09 6.74 6.99 7.31, n = 7 8.35 7.80 8.11 8.51; 8100 (5 10^5) n = 1 1.47 1.53
-    // 1.54 1.58, n = 2 2.93 2.99 3.01 3.16, n = 6 11.8 11.9 12.4 12.7, n = 7 13.0 13.3 13.9
-    // 14.5, n = 8 16.2 16.1 17.0 17.9, but 7872 n = 9 33.7 31.1 31.2 31.7; 10^6 points n = 6
-    // to 10 5% less at 1 than at 4.
-    const int32_t most = kStageHermite<N> || d.groups < 3072 ? kHermiteWaves
-                         : d.groups < 8000                   ? 4
-                                                             : 1;
-    const GroupLaunch gl = group_launch(d, std::max(most, d.threads_per_target), true);
+    const GroupLaunch gl = group_launch(
+        d, std::max(hermite_mixed_waves(d), d.threads_per_target), true);
     const size_t stage = kStageHermite<N> ? sizeof(float) * 8 * (N + 1) * (N + 1) * (N + 1) : 0;
     const size_t lds = std::max(stage, gl.log_w ? 64 * sizeof(double) : size_t(0)) << gl.log_w;
     hipLaunchKernelGGL((interact_hermite_mixed<N, KER>), dim3(gl.blocks), dim3(64u << gl.log_w), lds,
