@@ -316,6 +316,15 @@ int bltc_plan_view_get(const bltc_plan* plan, bltc_plan_view* out);
 
 void bltc_plan_destroy(bltc_plan* plan);
 
+/* Device memory of destroyed plans (and of the setup phase) is kept for the next
+ * plan of the process: at most 2 GiB of idle blocks, over all devices, those idle
+ * for more than 10 s given back when the next plan is destroyed, and all of them
+ * when an allocation of the library finds the device out of memory.  This call
+ * frees every idle block now, for programs whose other parts need the memory or
+ * that reset the device.  Waits for the device, as hipFree does; from any
+ * thread, not during a stream capture. */
+void bltc_release_memory(void);
+
 /* Many independent systems in one evaluation.  A batch is built from plans
  * (one per system; each created with max_q >= 2, all with the same kernel and
  * precision; the plans stay owned by the caller and must outlive the batch).

@@ -18,7 +18,7 @@ from . import _capi
 from ._capi import BLTCError, InvalidArgument  # noqa: F401
 
 __all__ = ["params", "Plan", "Batch", "batch_potential", "autotune", "potential", "direct",
-           "BLTCError", "InvalidArgument", "library_path", "version"]
+           "BLTCError", "InvalidArgument", "library_path", "release_memory", "version"]
 
 _KERNELS = {"coulomb": _capi.COULOMB, "yukawa": _capi.YUKAWA, "regularized": _capi.REGULARIZED}
 _PRECISIONS = {"fp64": _capi.FP64, "fp32_mixed": _capi.FP32_MIXED, "mixed": _capi.FP32_MIXED}
@@ -37,6 +37,12 @@ def library_path() -> str:
 
 def version() -> str:
     return _capi.load().bltc_version().decode()
+
+
+def release_memory() -> None:
+    """Frees the idle device memory that the library keeps from destroyed plans for the
+    next ones (at most 2 GiB; `bltc_release_memory`).  Waits for the device."""
+    _capi.load().bltc_release_memory()
 
 
 def params(kernel="coulomb", kappa=0.0, theta=0.7, degree=8, leaf_size=2000, batch_size=2000,

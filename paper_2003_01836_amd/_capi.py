@@ -31,7 +31,7 @@ EXPORTS = (
     "bltc_plan_set_timing", "bltc_plan_phase_times", "bltc_plan_destroy", "bltc_direct",
     "bltc_batch_create", "bltc_batch_execute", "bltc_batch_set_graph", "bltc_batch_info_get",
     "bltc_batch_destroy", "bltc_batch_potential", "bltc_autotune", "bltc_status_string",
-    "bltc_last_error", "bltc_version", "bltc_direct_noalloc",
+    "bltc_last_error", "bltc_version", "bltc_direct_noalloc", "bltc_release_memory",
 )
 
 
@@ -135,6 +135,8 @@ def load():
     lib.bltc_plan_phase_times.argtypes = [vp, ctypes.POINTER(ctypes.c_double)]
     lib.bltc_plan_destroy.argtypes = [vp]
     lib.bltc_plan_destroy.restype = None
+    lib.bltc_release_memory.argtypes = []
+    lib.bltc_release_memory.restype = None
     lib.bltc_direct.argtypes = [PP, i64, vp, vp, vp, i64, vp, vp, vp, vp, i32, i64, vp, i64, vp]
     lib.bltc_direct_noalloc.argtypes = lib.bltc_direct.argtypes
     lib.bltc_batch_create.argtypes = [ctypes.POINTER(vp), ctypes.POINTER(vp), i32, vp]

@@ -907,7 +907,21 @@ int bltc_internal_direct(const bltc_params* p, int64_t nt, const double* tx, con
 
 extern "C" {
 
-// the waves of an interaction workgroup (group_log_waves), for the tests
+// For the tests: the block that `bytes` of a plan take, an asynchronous allocation
+// of `bytes` that is freed again, the waves of an interaction workgroup.
+int64_t bltc_internal_block_bytes(int64_t bytes)
+{
+    return static_cast<int64_t>(bltc::block_bytes(static_cast<size_t>(bytes)));
+}
+
+int bltc_internal_try_alloc(int64_t bytes)
+{
+    void* p = nullptr;
+    HIP_TRY(bltc::device_malloc_async(&p, static_cast<size_t>(bytes), nullptr));
+    HIP_TRY(hipFreeAsync(p, nullptr));
+    return BLTC_OK;
+}
+
 int32_t bltc_internal_waves(int64_t targets, int64_t groups, int32_t asked, int32_t max_waves,
                             int32_t early)
 {
@@ -1249,9 +1263,10 @@ int bltc_direct(const bltc_params* p, int64_t nt, const double* tx, const double
     double* part = nullptr;
     if (split.pieces > 1 ||
         bltc_internal_direct_overlap(nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi, phi_ld))
-        HIP_TRY(hipMallocAsync(reinterpret_cast<void**>(&part),
-                               static_cast<size_t>(split.pieces) * nt *
-                                   std::min(num_q, bltc::kDirectVectors) * sizeof(double), s));
+        HIP_TRY(bltc::device_malloc_async(reinterpret_cast<void**>(&part),
+                                          static_cast<size_t>(split.pieces) * nt *
+                                              std::min(num_q, bltc::kDirectVectors) * sizeof(double),
+                                          s));
     const int rc_run = bltc_internal_direct(p, nt, tx, ty, tz, ns, sx, sy, sz, q, num_q, q_ld, phi,
                                             phi_ld, split, part, s);
     if (part) {
@@ -1260,6 +1275,11 @@ int bltc_direct(const bltc_params* p, int64_t nt, const double* tx, const double
             return hip_fail(f, "hipFreeAsync");
     }
     return rc_run;
+}
+
+void bltc_release_memory(void)
+{
+    (void)bltc::release_idle_blocks();
 }
 
 const char* bltc_status_string(int code)

@@ -8,8 +8,10 @@
 // 0.81 to 0.67 ms, and 0.50 ms with the small tables in one copy each (Pack).
 //
 // The pool holds at most kPoolBytes of idle blocks (least recently used ones are
-// freed first), gives back blocks that stayed idle for kPoolIdle when the next
-// object is released, and everything when the device runs out of memory.  Blocks
+// freed first).  It gives back blocks that stayed idle for kPoolIdle when the next
+// object is released, and all of them when an allocation of this library finds the
+// device out of memory or when the caller asks for it (bltc_release_memory); other
+// allocators of the process have no way to reclaim them.  Blocks
 // enter it only after a wait for the device (DeviceBlocks::release), so any thread
 // and any stream may take them.  Its memory is not cleared: like hipMalloc's, a
 // block's contents are undefined.
@@ -108,26 +110,49 @@ Pool& pool()
     return *p;
 }
 
+}  // namespace
+
 // steps of 1/16 of the power of two below: sizes that differ a little (another set
-// of points) fit each other's blocks
-size_t rounded(size_t n)
+// of points) fit each other's blocks; blocks that never enter the pool as they are
+size_t block_bytes(size_t n)
 {
+    if (n > kPoolBytes)
+        return n;
     size_t step = 512;
     while (step * 32 <= n)
         step *= 2;
     return (n + step - 1) / step * step;
 }
 
+bool release_idle_blocks()
+{
+    return pool().trim(0, Clock::time_point::max());
+}
+
+namespace {
+
+template <class F>
+hipError_t with_retry(F&& allocate)
+{
+    hipError_t e = allocate();
+    if (e == hipErrorOutOfMemory && release_idle_blocks())
+        e = allocate();
+    // the error is the caller's to report, not for the next launch's check to find
+    if (e != hipSuccess || hipPeekAtLastError() == hipErrorOutOfMemory)
+        (void)hipGetLastError();
+    return e;
+}
+
 }  // namespace
 
 hipError_t device_malloc(void** p, size_t bytes)
 {
-    hipError_t e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory && pool().trim(0, Clock::time_point::max())) {
-        (void)hipGetLastError();
-        e = hipMalloc(p, bytes);
-    }
-    return e;
+    return with_retry([&] { return hipMalloc(p, bytes); });
+}
+
+hipError_t device_malloc_async(void** p, size_t bytes, hipStream_t s)
+{
+    return with_retry([&] { return hipMallocAsync(p, bytes, s); });
 }
 
 hipError_t DeviceBlocks::get(void** p, size_t bytes)
@@ -137,7 +162,7 @@ hipError_t DeviceBlocks::get(void** p, size_t bytes)
     if (e != hipSuccess)
         return e;
     held_.emplace_back();   // may throw: before there is a block to lose
-    size_t size = rounded(std::max<size_t>(bytes, 1));
+    size_t size = block_bytes(std::max<size_t>(bytes, 1));
     if (!pool().take(device, size, p, &size)) {
         e = hipMalloc(p, size);
         if (e == hipErrorOutOfMemory) {

@@ -14,6 +14,12 @@ namespace bltc {
 // hipMalloc; when the device is out of memory the pool's idle blocks are given
 // back and the allocation is tried once more.
 hipError_t device_malloc(void** p, size_t bytes);
+// the same for hipMallocAsync
+hipError_t device_malloc_async(void** p, size_t bytes, hipStream_t s);
+// Frees the pool's idle blocks on every device; whether there were any.
+bool release_idle_blocks();
+// Size of the block taken for `n` bytes.
+size_t block_bytes(size_t n);
 
 // The device memory of one object, taken piece by piece and released together by
 // the destructor.  One hipFree there waits for the device, as freeing every block
