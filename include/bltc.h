@@ -343,7 +343,7 @@ typedef struct bltc_batch bltc_batch;
 
 typedef struct {
     int32_t systems;         /* plans in the batch                                  */
-    int32_t units;           /* work-queue units (system, 256-target group)         */
+    int32_t units;           /* work-queue units (system, 64-target group)          */
     int32_t upward_units;    /* upward-pass chunks over all systems                 */
     int32_t workgroups;      /* persistent workgroups of the work-queue launch      */
     int64_t graph_captures;  /* hipGraphs captured so far                           */

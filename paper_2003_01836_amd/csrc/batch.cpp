@@ -6,7 +6,7 @@
 // the gather of its charge vectors into tree order; one matrix-core upward
 // launch over the chunks of all systems; per system the fixed-order chunk
 // reduction; and ONE persistent work-queue launch that runs every
-// (system, 256-target group) unit of every system, heaviest first.  The whole
+// (system, 64-target group) unit of every system, heaviest first.  The whole
 // sequence is captured once into a hipGraph per set of caller buffers and
 // replayed afterwards.
 #include <cstring>

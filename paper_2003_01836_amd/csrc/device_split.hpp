@@ -2,7 +2,7 @@
 // interaction lists of their targets.
 //
 // A workgroup holds 64 targets of one batch, one per lane, in each of its W
-// waves (W = 1, 2, 4, 8 or 16, chosen per launch: interact_waves).  Wave w
+// waves (W = 1, 2, 4, 8 or 16, chosen per launch: group_log_waves).  Wave w
 // takes the w-th of W parts of equal estimated work of the batch's lists laid
 // end to end -- the (n+1) planes of every approximated cluster, the direct
 // entries in blocks of kSplitBlock sources, the mutual-pair results -- and the

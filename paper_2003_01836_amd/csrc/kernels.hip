@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void gather_charges(double4* __restrict__ src,
 // charge vectors.  Bound: FP64 issue (about 60 SIMD cycles per value and 64
 // targets).  With few targets the sources are cut into gridDim.y pieces
 // (launch_direct): 1000 targets against 2 10^6 sources took 188 ms with one
-// lane per target and every source in it (16 waves on the chip), 1.0 ms so.
+// lane per target and every source in it (16 waves on the chip), 1.12 ms so.
 // Sums run in a fixed order: within a wave, over the waves, over the pieces.
 // ---------------------------------------------------------------------------
 constexpr int kDirectWaves = 4;
@@ -304,7 +304,7 @@ hipError_t launch_interact(const DevicePlan& d, const KernelParams& kp, double* 
 // waves on the chip is short (8192 of four waves, four times what is resident
 // at once), pieces of at least 64 sources per wave, one piece when the targets
 // alone give that many workgroups.  1000 targets, 2 10^6 sources: 188 ms in
-// one piece, 1.1 ms cut.
+// one piece, 1.12 ms cut.
 DirectSplit direct_split(int64_t nt, int64_t ns)
 {
     DirectSplit d;

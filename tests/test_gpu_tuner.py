@@ -46,19 +46,22 @@ def _milliseconds(plan, q):
 
 def test_several_vectors_are_timed_as_they_run(dev, tmp_path, monkeypatch):
     import paper_2003_01836_amd as bltc
-    cache = tmp_path / "tune.txt"
-    monkeypatch.setenv("BLTC_TUNE_CACHE", str(cache))
     t = _soa(100000, 1050, dev)
     kw = dict(theta=0.7, degree=6)
     for m, padded in ((3, 4), (16, 16)):
-        plan = bltc.Plan(t, t, max_q=m, leaf_size=0, batch_size=0, **kw)
-        (key, (leaf, ms, lanes)), = [e for e in _lines(cache).items() if f" q={padded} " in e[0]]
-        assert key.startswith("v3 ") and lanes == 1
-        assert plan.stats()["leaf_size"] == leaf
-        q = torch.ones((m, 100000), dtype=torch.float64, device=dev)
+        ratios = []
+        for attempt in range(3):   # one timing each: the least disturbed counts
+            cache = tmp_path / f"tune{m}-{attempt}.txt"
+            monkeypatch.setenv("BLTC_TUNE_CACHE", str(cache))
+            plan = bltc.Plan(t, t, max_q=m, leaf_size=0, batch_size=0, **kw)
+            (key, (leaf, ms, lanes)), = _lines(cache).items()
+            assert key.startswith("v3 ") and f" q={padded} " in key and lanes == 1
+            assert plan.stats()["leaf_size"] == leaf
+            q = torch.ones((m, 100000), dtype=torch.float64, device=dev)
+            ratios.append(ms / _milliseconds(plan, q))
+            plan.close()
         # the recorded time is that of m vectors (16 take twice as long as 3)
-        assert 0.6 <= ms / _milliseconds(plan, q) <= 1.6
-        plan.close()
+        assert 0.6 <= min(ratios) <= 1.4
 
 
 def test_identical_launches_are_not_compared(dev):
