@@ -24,6 +24,8 @@
 // once to FP32 like every other value: the FP64 branch removes the coordinate
 // rounding that 1/r amplifies for close pairs, and what is left is one FP32
 // rounding of the value and one of its product with the charge.
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "device_common.hpp"
 
@@ -445,6 +447,17 @@ hipError_t launch_near_pairs(const DevicePlan& d, int64_t first, int64_t count,
         return hipSuccess;
     if (!d.sym_unit || !d.sym_out || first < 0 || first + count > d.sym_units)
         return hipErrorInvalidValue;
+    // a launch has fewer than 2^32 threads: 2^25 units (2^31 threads) at a time
+    constexpr int64_t kUnits = int64_t(1) << 25;
+    if (count > kUnits) {
+        for (int64_t k = 0; k < count; k += kUnits) {
+            const hipError_t e =
+                launch_near_pairs(d, first + k, std::min(kUnits, count - k), kp, s);
+            if (e != hipSuccess)
+                return e;
+        }
+        return hipSuccess;
+    }
     const KernelConst kc = kp.kconst();
     const bool mixed = kp.precision == 1;
     if (mixed && (!d.src32 || !d.node_info || !d.batch_info))
