@@ -333,9 +333,7 @@ hipError_t launch_direct(int64_t nt, const double* tx, const double* ty, const d
     double* out = part ? part : phi;
     const int64_t out_ld = part ? nt : phi_ld;
     const auto run = kp.kernel == 1 ? run_direct<1> : kp.kernel == 2 ? run_direct<2> : run_direct<0>;
-    // a launch has fewer than 2^32 threads a dimension: 2^29 targets (2^31 threads)
-    // at a time, then 2^31 sums
-    constexpr int64_t kTargets = int64_t(1) << 29, kSums = int64_t(1) << 31;
+    constexpr int64_t kTargets = kLaunchThreads / (64 * kDirectWaves) * 64;
     for (int64_t t0 = 0; t0 < nt; t0 += kTargets) {
         const int64_t n = std::min(kTargets, nt - t0);
         const dim3 grid(static_cast<unsigned>((n + 63) / 64), static_cast<unsigned>(split.pieces));
@@ -348,8 +346,8 @@ hipError_t launch_direct(int64_t nt, const double* tx, const double* ty, const d
     if (!part)
         return hipSuccess;
     const int64_t total = nt * m;
-    for (int64_t k0 = 0; k0 < total; k0 += kSums) {
-        const int64_t n = std::min(kSums, total - k0);
+    for (int64_t k0 = 0; k0 < total; k0 += kLaunchThreads) {
+        const int64_t n = std::min(kLaunchThreads, total - k0);
         hipLaunchKernelGGL(sum_direct, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s,
                            part, nt, m, split.pieces, k0, phi, phi_ld);
         const hipError_t e = hipGetLastError();

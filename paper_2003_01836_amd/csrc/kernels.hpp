@@ -18,6 +18,9 @@ constexpr int kMaxHermiteDegree = 10;   // Hermite treecode: 8 (n+1)^3 charges p
 // a third of the CUs idle.
 constexpr int kGroupSize = 64;
 constexpr int kMaxWaves = 16;        // waves of an interaction workgroup
+// A grid has fewer than 2^32 threads a dimension (more are cut off without an error):
+// larger element-wise launches go in parts of this many.
+constexpr int64_t kLaunchThreads = int64_t(1) << 31;
 
 // The direct lists the single-vector interaction kernels walk: the plan's own,
 // or, when mutual leaf pairs are evaluated by launch_near_pairs, the reduced
@@ -164,6 +167,9 @@ inline int32_t group_log_waves(int64_t targets, int64_t groups, int32_t asked, i
         --log_w;
     while ((1 << log_w) < asked && (2 << log_w) <= max_waves)
         ++log_w;
+    // within the threads of a grid (an eighth left for the schedule's empty slots)
+    while (log_w > 0 && (groups << (6 + log_w)) > 2 * kLaunchThreads / 8 * 7)
+        --log_w;
     return log_w;
 }
 struct GroupLaunch {

@@ -663,9 +663,9 @@ __global__ __launch_bounds__(256) void gather_charges_multi(double* __restrict__
                                                             const int64_t* __restrict__ order,
                                                             const double* __restrict__ q,
                                                             int64_t q_ld, int32_t mc, int log_ld,
-                                                            int64_t ns)
+                                                            int64_t ns, int64_t idx0)
 {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t idx = idx0 + static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (idx >= ns << log_ld)
         return;
     const int64_t j = idx >> log_ld;
@@ -687,9 +687,15 @@ hipError_t launch_gather_charges_multi(const DevicePlan& d, const double* q, int
     if (ld != 1 << log_ld || mc > ld)
         return hipErrorInvalidValue;
     const int64_t total = d.ns << log_ld;
-    hipLaunchKernelGGL(gather_charges_multi, dim3(static_cast<unsigned>((total + 255) / 256)),
-                       dim3(256), 0, s, d.qm, d.qm32, d.src_order, q, q_ld, mc, log_ld, d.ns);
-    return hipGetLastError();
+    for (int64_t i = 0; i < total; i += kLaunchThreads) {
+        const int64_t n = std::min(kLaunchThreads, total - i);
+        hipLaunchKernelGGL(gather_charges_multi, dim3(static_cast<unsigned>((n + 255) / 256)),
+                           dim3(256), 0, s, d.qm, d.qm32, d.src_order, q, q_ld, mc, log_ld, d.ns, i);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 MrhsDesc make_mrhs_desc(const DevicePlan& d, const KernelParams& kp, double* phi, int64_t phi_ld,

@@ -447,8 +447,7 @@ hipError_t launch_near_pairs(const DevicePlan& d, int64_t first, int64_t count,
         return hipSuccess;
     if (!d.sym_unit || !d.sym_out || first < 0 || first + count > d.sym_units)
         return hipErrorInvalidValue;
-    // a launch has fewer than 2^32 threads: 2^25 units (2^31 threads) at a time
-    constexpr int64_t kUnits = int64_t(1) << 25;
+    constexpr int64_t kUnits = kLaunchThreads / 64;
     if (count > kUnits) {
         for (int64_t k = 0; k < count; k += kUnits) {
             const hipError_t e =

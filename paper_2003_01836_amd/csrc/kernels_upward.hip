@@ -918,9 +918,9 @@ __global__ __launch_bounds__(256) void upward_mfma_f64_many(const UpwardDesc* __
 __global__ __launch_bounds__(256) void upward_mfma_reduce(
     const int32_t* __restrict__ slot_chunk_off, const int64_t* __restrict__ chunk_dst,
     double* __restrict__ buf, float* __restrict__ qhat32, int64_t nslots, int64_t per_slot,
-    int64_t range_stride, int32_t ranges)
+    int64_t range_stride, int32_t ranges, int64_t idx0)
 {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t idx = idx0 + static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (idx >= nslots * per_slot)
         return;
     const int64_t slot = idx / per_slot;
@@ -1015,10 +1015,16 @@ hipError_t launch_upward_reduce(const DevicePlan& d, int32_t mw, double* buf, fl
                            d.nslots, d.degree + 1);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(upward_mfma_reduce, dim3(static_cast<unsigned>((total + 255) / 256)),
-                       dim3(256), 0, s, d.slot_chunk_off, d.chunk_dst, buf, qhat32, d.nslots,
-                       per_slot, d.qhat_rows * per_slot, ranges);
-    return hipGetLastError();
+    for (int64_t i = 0; i < total; i += kLaunchThreads) {
+        const int64_t n = std::min(kLaunchThreads, total - i);
+        hipLaunchKernelGGL(upward_mfma_reduce, dim3(static_cast<unsigned>((n + 255) / 256)),
+                           dim3(256), 0, s, d.slot_chunk_off, d.chunk_dst, buf, qhat32, d.nslots,
+                           per_slot, d.qhat_rows * per_slot, ranges, i);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_upward_mfma(const DevicePlan& d, int32_t mw, double* buf, float* qhat32,

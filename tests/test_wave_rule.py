@@ -37,3 +37,10 @@ def test_bounds_and_lanes_asked_for():
     assert [waves(10 ** 8, 10 ** 7, asked=a) for a in (1, 2, 4)] == [1, 2, 4]
     assert [waves(10 ** 6, 16000, asked=a) for a in (1, 2, 4)] == [4, 4, 4]
     assert waves(10 ** 8, 10 ** 7, asked=4, most=2) == 2
+
+
+def test_within_the_threads_of_a_grid():
+    # 2^32 threads a dimension at most, a wave has 64
+    assert waves(2 ** 27, 2 ** 23, asked=4) == 4
+    assert waves(2 ** 27, 2 ** 24, asked=4) == 2
+    assert waves(2 ** 28, 2 ** 25, asked=4) == 1
